@@ -116,6 +116,7 @@ struct MatView {
   float* X;      const void* G;
   // workspace
   float* Mbar;   float* Q;     float* Qpart; float* lam_part;
+  float* amax;     // largest |Mbar| of each block of the worker mean (ef_mean_blocks of them)
   float* W;      float* Utw;   double* Apk;  double* Apk2; float* Vrot;   double* V64;   int* skip;
   double* gpart;   // split-contraction partials of the Gram (or null)
   JacCtl* ctl;   float* sigma_w; int* perm;
@@ -128,6 +129,15 @@ struct MatView {
   float* rr_Utw; float* rr_Y; double* rr_Apk; float* rr_V; double* rr_V64; int* rr_skip;
   JacCtl* rr_ctl; float* rr_sigw; int* rr_perm; double* rr_gpart;
 };
+
+// Blocks of the worker mean over mn elements: about one float4 per thread, at
+// most 2048 (eight blocks of four waves on each of 256 CUs), each of which
+// leaves one partial maximum.
+constexpr int kEfMeanMax = 2048;
+__host__ __device__ inline int ef_mean_blocks(int64_t mn) {
+  const int64_t g = (mn + 1023) / 1024;
+  return (int)(g < 1 ? 1 : g > kEfMeanMax ? kEfMeanMax : g);
+}
 
 // Optional timing brackets around launch groups (glr_prof_group ids); a
 // no-op unless the host runtime installs a callback.

@@ -35,7 +35,7 @@ inline uint64_t align_up(uint64_t x) { return (x + kAlign - 1) / kAlign * kAlign
 thread_local std::string g_create_error;
 
 struct WsLayout {
-  uint64_t off_Mbar, off_Q, off_Qpart, off_lam, off_W, off_Utw, off_gram, off_gram2, off_V, off_V64, off_gpart, off_skip,
+  uint64_t off_Mbar, off_Q, off_Qpart, off_lam, off_amax, off_W, off_Utw, off_gram, off_gram2, off_V, off_V64, off_gpart, off_skip,
       off_ctl, off_sigw, off_perm;
   uint64_t off_sP, off_sPn, off_sZ, off_sZt, off_sR, off_spart, off_sS, off_sL, off_sDinv, off_sLi,
       off_sT, off_sLinv, off_sC, off_ssums, off_sctl, off_sbad;
@@ -220,6 +220,7 @@ WsLayout ws_layout(const glr_config* c, int first, int last) {
   w.off_Q = take(mx_Q * 4);
   w.off_Qpart = take(mx_Qp * 4);
   w.off_lam = take(mx_lam * 4);
+  w.off_amax = take((uint64_t)ef_mean_blocks((int64_t)mx_mn) * 4);
   w.off_W = take(mx_dD * 4);
   w.off_Utw = take(mx_dd * 4);
   w.off_gram = take(mx_gram * 8);
@@ -421,6 +422,7 @@ MatView view_of(glr_handle* h, int mat, float* X, const void* G, int lane) {
   v.Q = (float*)(w + WL.off_Q);
   v.Qpart = (float*)(w + WL.off_Qpart);
   v.lam_part = (float*)(w + WL.off_lam);
+  v.amax = (float*)(w + WL.off_amax);
   v.W = (float*)(w + WL.off_W);
   v.Utw = (float*)(w + WL.off_Utw);
   v.Apk = (double*)(w + WL.off_gram);

@@ -4,6 +4,7 @@
 //   fused residual + worker mean + reconstruction + optimizer.
 #include "glr_device.hpp"
 #include "glr_internal.hpp"
+#include "glr_split.hpp"
 
 namespace glr {
 
@@ -50,9 +51,10 @@ hipError_t launch_eye(float* Ut, int64_t d, hipStream_t s) {
 template <class ST>
 __device__ __forceinline__ void ef_mean_at(const ST* __restrict__ G, const float* __restrict__ Ebar,
                                            float* __restrict__ Mbar, int64_t mn, int N, uint32_t* status, int check,
-                                           int64_t bx, int64_t gx) {
+                                           float* __restrict__ amax, int64_t bx, int64_t gx) {
   const int64_t stride = (int64_t)gx * blockDim.x;
   bool bad = false;
+  float mx = 0.f;   // the largest |Mbar| (fmaxf drops a NaN: Mbar itself still carries it)
   if ((mn & 3) == 0) {
     const int64_t q = mn >> 2;
     for (int64_t i = bx * (int64_t)blockDim.x + threadIdx.x; i < q; i += stride) {
@@ -68,6 +70,7 @@ __device__ __forceinline__ void ef_mean_at(const ST* __restrict__ G, const float
       o.y = e.y + acc.y / (float)N;
       o.z = e.z + acc.z / (float)N;
       o.w = e.w + acc.w / (float)N;
+      mx = fmaxf(fmaxf(fmaxf(mx, fabsf(o.x)), fmaxf(fabsf(o.y), fabsf(o.z))), fabsf(o.w));
       reinterpret_cast<float4*>(Mbar)[i] = o;
     }
   } else {
@@ -78,26 +81,37 @@ __device__ __forceinline__ void ef_mean_at(const ST* __restrict__ G, const float
         if (check) bad |= !isfinite(g);
         acc += g;
       }
-      Mbar[i] = Ebar[i] + acc / (float)N;
+      const float o = Ebar[i] + acc / (float)N;
+      mx = fmaxf(mx, fabsf(o));
+      Mbar[i] = o;
     }
   }
   if (check && bad) atomicOr(status, 1u);
+  __shared__ float red[kThreads / 64];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+  if (lane_id() == 0) red[wave_id()] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kThreads / 64; ++w) mx = fmaxf(mx, red[w]);
+    amax[bx] = mx;
+  }
 }
 template <class ST>
 __global__ void k_ef_mean(const ST* __restrict__ G, const float* __restrict__ Ebar,
                           float* __restrict__ Mbar, int64_t mn, int N, uint32_t* status,
-                          int check) {
-  ef_mean_at(G, Ebar, Mbar, mn, N, status, check, blockIdx.x, gridDim.x);
+                          int check, float* __restrict__ amax) {
+  ef_mean_at(G, Ebar, Mbar, mn, N, status, check, amax, blockIdx.x, gridDim.x);
 }
 
 hipError_t launch_ef_mean(const MatView& v, bool check_finite, hipStream_t s) {
   const int64_t mn = v.m * v.n;
   if (v.st16)
-    hipLaunchKernelGGL(k_ef_mean<bf16_t>, dim3(grid_for(mn, 4)), dim3(kThreads), 0, s, (const bf16_t*)v.G, v.Ebar,
-                       v.Mbar, mn, v.N, v.status, check_finite ? 1 : 0);
+    hipLaunchKernelGGL(k_ef_mean<bf16_t>, dim3(ef_mean_blocks(mn)), dim3(kThreads), 0, s, (const bf16_t*)v.G, v.Ebar,
+                       v.Mbar, mn, v.N, v.status, check_finite ? 1 : 0, v.amax);
   else
-    hipLaunchKernelGGL(k_ef_mean<float>, dim3(grid_for(mn, 4)), dim3(kThreads), 0, s, (const float*)v.G, v.Ebar,
-                       v.Mbar, mn, v.N, v.status, check_finite ? 1 : 0);
+    hipLaunchKernelGGL(k_ef_mean<float>, dim3(ef_mean_blocks(mn)), dim3(kThreads), 0, s, (const float*)v.G, v.Ebar,
+                       v.Mbar, mn, v.N, v.status, check_finite ? 1 : 0, v.amax);
   return hipGetLastError();
 }
 
@@ -105,31 +119,53 @@ hipError_t launch_ef_mean(const MatView& v, bool check_finite, hipStream_t s) {
 // S3b: selection scores.  C[b][j] = sum_a Mo[a][b] Ut[j][a]  (C = Mo^T U,
 // D x d), never stored: the epilogue folds each column j with v_j (approx:
 // lambdabar_j = u_j^T Mbar v_j) or with itself (exact: ||u_j^T Mbar||^2) and
-// writes one partial per 128-row tile: part[tile][j].
+// writes one partial per 128-row tile: part[tile][j].  Bound by the matrix
+// cores, so the product runs on the fp16 ones (kF16x2): only its size against
+// the rest of the same matrix matters here, so one scale for all of Mbar
+// serves, from the maxima the worker mean leaves (at most 2048 floats, 2 us of
+// reading).  4096 x 4096: 1332 -> 573 us (103 -> 240 TFLOP/s of fp32 products),
+// 4096 x 11008: 3430 -> 1378 us, 768 x 768: 85 -> 52 us, against the fp32 MFMA
+// with 16-byte loads; the scores' error against 64 bits 8.1e-7 -> 2.3e-7.
 // ---------------------------------------------------------------------------
 constexpr int SEL_BM = 128, SEL_BN = 128;
 
-template <bool RIGHT, bool APPROX, bool BF16, bool VEC = false>
+template <bool RIGHT, bool APPROX, bool BF16>
 __device__ __forceinline__ void sel_scores_at(const float* __restrict__ Mbar, const float* __restrict__ Ut, int64_t d,
                                               int64_t D, float* __restrict__ part, uint32_t mat, uint32_t tstep,
-                                              uint32_t key0, uint32_t key1, int bx, int by) {
-  using T = MfmaTile<SEL_BM, SEL_BN, 2, 2>;
-  __shared__ __align__(16) float smem[T::LDS_FLOATS];
+                                              uint32_t key0, uint32_t key1, const float* __restrict__ amax, int bx,
+                                              int by) {
+  using T = SplitTile<SEL_BM, SEL_BN, 2, 2, BF16 ? kBf16 : kF16x2, !BF16>;
+  __shared__ __align__(16) char smem[T::LDS_BYTES];
   __shared__ float red[2][SEL_BN];
   const int m0 = by * SEL_BM;   // rows: b in [0, D)
   const int n0 = bx * SEL_BN;   // cols: j in [0, d)
+  // the exponents of the operands' scales: |u| is at most 1 (2^8 leaves room
+  // for a basis that is not quite), Mbar's from its largest value
+  int em = 0;
+  if (!BF16) {
+    float mx = 0.f;
+    for (int i = threadIdx.x; i < ef_mean_blocks(d * D); i += kThreads) mx = fmaxf(mx, amax[i]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    if (lane_id() == 0) red[0][wave_id()] = mx;
+    __syncthreads();
+    em = split_exp(fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3])));
+    __syncthreads();
+  }
+  const float sm = BF16 ? 1.f : ldexpf(1.f, em), su = BF16 ? 1.f : 0x1p8f;
   T tile;
-  LoadK<SEL_BN, 32, false, false, float, VEC> lb(Ut, nullptr, d, n0, (int)d, (int)d, nullptr);
+  SplitK<SEL_BN, false, false> lb(Ut, nullptr, d * d, d, n0, (int)d, (int)d);
   if (RIGHT) {
     // Mo[a][b] = Mbar[b][a] : A[b][a] contiguous along a
-    LoadK<SEL_BM, 32, false, false, float, VEC> la(Mbar, nullptr, d, m0, (int)D, (int)d, nullptr);
-    tile.template run<BF16>(la, lb, (int)d, smem);
+    SplitK<SEL_BM, false, false> la(Mbar, nullptr, d * D, d, m0, (int)D, (int)d);
+    tile.run(la, lb, (int)d, smem, sm, su);
   } else {
     // Mo[a][b] = Mbar[a][b] : A[b][a] contiguous along b
-    LoadR<SEL_BM, 32, false, false, float, VEC> la(Mbar, nullptr, D, m0, (int)D, (int)d);
-    tile.template run<BF16>(la, lb, (int)d, smem);
+    SplitR<SEL_BM, false, false> la(Mbar, nullptr, d * D, D, m0, (int)D, (int)d);
+    tile.run(la, lb, (int)d, smem, sm, su);
   }
   const int lane = lane_id();
+  const float unscale = BF16 ? 1.f : ldexpf(1.f, -em - 8);
 #pragma unroll
   for (int tn = 0; tn < T::TN; ++tn) {
     const int j = n0 + tile.col(tn);
@@ -146,12 +182,12 @@ __device__ __forceinline__ void sel_scores_at(const float* __restrict__ Mbar, co
             normals4((uint32_t)(b0 >> 2), (uint32_t)j, mat, tstep, key0, key1, z);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if (b0 + e < D) acc += tile.acc[tm][tn][4 * g + e] * z[e];
+              if (b0 + e < D) acc += tile.acc[tm][tn][4 * g + e] * unscale * z[e];
           } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              const float c = tile.acc[tm][tn][4 * g + e];
-              acc += c * c;
+              const float c = tile.acc[tm][tn][4 * g + e] * unscale;
+              if (b0 + e < D) acc += c * c;
             }
           }
         }
@@ -166,13 +202,12 @@ __device__ __forceinline__ void sel_scores_at(const float* __restrict__ Mbar, co
     if (j < d) part[(int64_t)by * d + j] = red[0][threadIdx.x] + red[1][threadIdx.x];
   }
 }
-// VEC: d and D multiples of 4 and both operands 16-byte aligned, so every
-// operand slice loads as whole float4s
-template <bool RIGHT, bool APPROX, bool BF16, bool VEC>
-__global__ void __launch_bounds__(256)
+template <bool RIGHT, bool APPROX, bool BF16>
+__global__ void __launch_bounds__(256, 2)
 k_sel_scores(const float* __restrict__ Mbar, const float* __restrict__ Ut, int64_t d, int64_t D,
-             float* __restrict__ part, uint32_t mat, uint32_t tstep, uint32_t key0, uint32_t key1) {
-  sel_scores_at<RIGHT, APPROX, BF16, VEC>(Mbar, Ut, d, D, part, mat, tstep, key0, key1, blockIdx.x, blockIdx.y);
+             float* __restrict__ part, uint32_t mat, uint32_t tstep, uint32_t key0, uint32_t key1,
+             const float* __restrict__ amax) {
+  sel_scores_at<RIGHT, APPROX, BF16>(Mbar, Ut, d, D, part, mat, tstep, key0, key1, amax, blockIdx.x, blockIdx.y);
 }
 
 // lambdabar / scores from the tile partials, summed in a fixed order
@@ -194,16 +229,9 @@ hipError_t launch_sel_scores(const MatView& v, bool approx, bool bf16, uint64_t 
   dim3 grid((unsigned)((v.d + SEL_BN - 1) / SEL_BN), (unsigned)((v.D + SEL_BM - 1) / SEL_BM));
   const uint32_t k0 = (uint32_t)(seed & 0xFFFFFFFFu), k1 = (uint32_t)(seed >> 32);
   const uint32_t tt = (uint32_t)((uint64_t)t & 0xFFFFFFFFu);
-  const bool vec = v.d % 4 == 0 && v.D % 4 == 0 && (reinterpret_cast<uintptr_t>(v.Ut) & 15) == 0 &&
-                   (reinterpret_cast<uintptr_t>(v.Mbar) & 15) == 0;
-#define GLR_SEL1(R, A, B, VE)                                                                         \
-  hipLaunchKernelGGL((k_sel_scores<R, A, B, VE>), grid, dim3(kThreads), 0, s, v.Mbar, v.Ut, v.d, v.D, \
-                     v.lam_part, (uint32_t)v.mat, tt, k0, k1)
-#define GLR_SEL(R, A, B)                       \
-  do {                                         \
-    if (vec) GLR_SEL1(R, A, B, true);          \
-    else GLR_SEL1(R, A, B, false);             \
-  } while (0)
+#define GLR_SEL(R, A, B)                                                                         \
+  hipLaunchKernelGGL((k_sel_scores<R, A, B>), grid, dim3(kThreads), 0, s, v.Mbar, v.Ut, v.d, v.D, \
+                     v.lam_part, (uint32_t)v.mat, tt, k0, k1, v.amax)
   if (v.right) {
     if (bf16) GLR_SEL(true, true, true);
     else if (approx) GLR_SEL(true, true, false);
@@ -213,7 +241,6 @@ hipError_t launch_sel_scores(const MatView& v, bool approx, bool bf16, uint64_t 
     else if (approx) GLR_SEL(false, true, false);
     else GLR_SEL(false, false, false);
   }
-#undef GLR_SEL1
 #undef GLR_SEL
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -967,19 +994,19 @@ template <class ST>
 __global__ void k_g_ef_mean(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num, int check) {
   const int m = group_find(first, num, blockIdx.x);
   const MatView& v = gm[m].v;
-  ef_mean_at(static_cast<const ST*>(v.G), v.Ebar, v.Mbar, v.m * v.n, v.N, v.status, check, blockIdx.x - first[m],
-             first[m + 1] - first[m]);
+  ef_mean_at(static_cast<const ST*>(v.G), v.Ebar, v.Mbar, v.m * v.n, v.N, v.status, check, v.amax,
+             blockIdx.x - first[m], first[m + 1] - first[m]);
 }
 
 template <bool RIGHT, bool APPROX, bool BF16>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, 2)
 k_g_sel_scores(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num, uint32_t tstep,
                uint32_t key0, uint32_t key1) {
   const int m = group_find(first, num, blockIdx.x);
   const MatView& v = gm[m].v;
   const int local = blockIdx.x - first[m], gx = (int)((v.d + SEL_BN - 1) / SEL_BN);
   sel_scores_at<RIGHT, APPROX, BF16>(v.Mbar, v.Ut, v.d, v.D, v.lam_part, (uint32_t)v.mat, tstep, key0, key1,
-                                     local % gx, local / gx);
+                                     v.amax, local % gx, local / gx);
 }
 
 __global__ void k_g_sel_finish(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num, int approx) {
@@ -1041,7 +1068,7 @@ void group_fill(GroupMat& g, int (&blocks)[kGrpKinds]) {
   const int r = v.r;
   g.splits = proj_splits(v.d, v.D, r, v.N);
   g.kslice = proj_kslice(v.d, v.D, r, v.N);
-  blocks[kGrpEfMean] = grid_for(v.m * v.n, 4);
+  blocks[kGrpEfMean] = ef_mean_blocks(v.m * v.n);
   blocks[kGrpSelScores] = (int)(((v.d + SEL_BN - 1) / SEL_BN) * ((v.D + SEL_BM - 1) / SEL_BM));
   blocks[kGrpSelFinish] = grid_for(v.d);
   int proj = 0;
