@@ -280,6 +280,7 @@ hipError_t launch_jac_solve(const MatView& v, int round, float tol, int max_inne
 hipError_t launch_jac_check(const MatView& v, float tol, hipStream_t s);
 hipError_t launch_jac_finish(const MatView& v, int max_sweeps, hipStream_t s);
 hipError_t launch_reorth(const MatView& v, hipStream_t s);
+hipError_t launch_warm_product(const MatView& v, hipStream_t s);
 
 // A (packed fp64 blocks, zero padded) = W W^T for n rows of length Kc (ld)
 int gram_splits(int64_t n, int64_t Kc);

@@ -139,38 +139,6 @@ __global__ void k_ctl_reset(JacCtl* ctl) {
   }
 }
 
-// W (d x D) = Ut (d x d) Mo (d x D), MFMA tiles 128 x 128
-template <bool RIGHT>
-__global__ void __launch_bounds__(256)
-k_jac_warm(const float* __restrict__ Mbar, const float* __restrict__ Ut, float* __restrict__ W,
-           int64_t d, int64_t D) {
-  using T = MfmaTile<128, 128, 2, 2>;
-  __shared__ __align__(16) float smem[T::LDS_FLOATS];
-  const int n0 = blockIdx.x * 128;  // b
-  const int m0 = blockIdx.y * 128;  // j
-  T tile;
-  LoadK<128, 32, false, false> la(Ut, nullptr, d, m0, (int)d, (int)d, nullptr);
-  if (RIGHT) {
-    LoadK<128, 32, false, false> lb(Mbar, nullptr, d, n0, (int)D, (int)d, nullptr);
-    tile.run(la, lb, (int)d, smem);
-  } else {
-    LoadR<128, 32, false> lb(Mbar, nullptr, D, n0, (int)D, (int)d);
-    tile.run(la, lb, (int)d, smem);
-  }
-#pragma unroll
-  for (int tm = 0; tm < T::TM; ++tm)
-#pragma unroll
-    for (int tn = 0; tn < T::TN; ++tn) {
-      const int b = n0 + tile.col(tn);
-      if (b >= D) continue;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int j = m0 + tile.row(tm, v);
-        if (j < d) W[(int64_t)j * D + b] = tile.acc[tm][tn][v];
-      }
-    }
-}
-
 static inline int grid1(int64_t n) {
   int64_t g = (n + 1023) / 1024;
   if (g < 1) g = 1;
@@ -187,11 +155,8 @@ hipError_t launch_jac_init(const MatView& v, bool warm, hipStream_t s) {
   hipLaunchKernelGGL(k_ctl_reset, dim3(1), dim3(64), 0, s, v.ctl);
   if (warm) {
     hipLaunchKernelGGL(k_copy, dim3(grid1(v.d * v.d)), dim3(256), 0, s, v.Ut, v.Utw, v.d * v.d);
-    dim3 grid((unsigned)((v.D + 127) / 128), (unsigned)((v.d + 127) / 128));
-    if (v.right)
-      hipLaunchKernelGGL(k_jac_warm<true>, grid, dim3(256), 0, s, v.Mbar, v.Ut, v.W, v.d, v.D);
-    else
-      hipLaunchKernelGGL(k_jac_warm<false>, grid, dim3(256), 0, s, v.Mbar, v.Ut, v.W, v.d, v.D);
+    const hipError_t e = launch_warm_product(v, s);
+    if (e != hipSuccess) return e;
   } else {
     hipError_t e = launch_eye(v.Utw, v.d, s);
     if (e != hipSuccess) return e;

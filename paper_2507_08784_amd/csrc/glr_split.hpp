@@ -80,6 +80,33 @@ __device__ __forceinline__ int split_exp(float amax) {
   return e < 126 ? e : 126;
 }
 
+// Where an operand's scale comes from (kF16x2): the exponent `fixed`, or with
+// `amax` the one of the largest of n partial maxima times `mul` (a bound on
+// the operand's largest value).
+struct SplitScale {
+  const float* amax;
+  int n;
+  float mul;
+  int fixed;
+};
+// rows of an orthonormal basis: |u| <= 1, with room for a basis that is not
+// quite one (fp16 ends at 2^16)
+constexpr int kUnitExp = 6;
+inline SplitScale split_unit() { return {nullptr, 0, 1.f, kUnitExp}; }
+// the exponent, by a whole workgroup (red: one float per wave)
+__device__ __forceinline__ int split_block_exp(const SplitScale& sc, float* red) {
+  if (!sc.amax) return sc.fixed;
+  float mx = 0.f;
+  for (int i = threadIdx.x; i < sc.n; i += kThreads) mx = fmaxf(mx, sc.amax[i]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+  if (lane_id() == 0) red[wave_id()] = mx;
+  __syncthreads();
+  mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])) * sc.mul;
+  __syncthreads();
+  return split_exp(mx);
+}
+
 // A slice of one operand in LDS: PIECES planes of R rows (the operand's M or
 // N index) of kSplitBK bf16 along k, 64 bytes a row.  The 16-byte groups of a
 // row (8 values of k, one lane's operand of one MFMA) are permuted by the

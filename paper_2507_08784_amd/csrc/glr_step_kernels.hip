@@ -139,20 +139,8 @@ __device__ __forceinline__ void sel_scores_at(const float* __restrict__ Mbar, co
   __shared__ float red[2][SEL_BN];
   const int m0 = by * SEL_BM;   // rows: b in [0, D)
   const int n0 = bx * SEL_BN;   // cols: j in [0, d)
-  // the exponents of the operands' scales: |u| is at most 1 (2^8 leaves room
-  // for a basis that is not quite), Mbar's from its largest value
-  int em = 0;
-  if (!BF16) {
-    float mx = 0.f;
-    for (int i = threadIdx.x; i < ef_mean_blocks(d * D); i += kThreads) mx = fmaxf(mx, amax[i]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    if (lane_id() == 0) red[0][wave_id()] = mx;
-    __syncthreads();
-    em = split_exp(fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3])));
-    __syncthreads();
-  }
-  const float sm = BF16 ? 1.f : ldexpf(1.f, em), su = BF16 ? 1.f : 0x1p8f;
+  const int em = BF16 ? 0 : split_block_exp({amax, ef_mean_blocks(d * D), 1.f, 0}, red[0]);
+  const float sm = ldexpf(1.f, em), su = BF16 ? 1.f : ldexpf(1.f, kUnitExp);
   T tile;
   SplitK<SEL_BN, false, false> lb(Ut, nullptr, d * d, d, n0, (int)d, (int)d);
   if (RIGHT) {
@@ -165,7 +153,7 @@ __device__ __forceinline__ void sel_scores_at(const float* __restrict__ Mbar, co
     tile.run(la, lb, (int)d, smem, sm, su);
   }
   const int lane = lane_id();
-  const float unscale = BF16 ? 1.f : ldexpf(1.f, -em - 8);
+  const float unscale = BF16 ? 1.f : ldexpf(1.f, -em - kUnitExp);
 #pragma unroll
   for (int tn = 0; tn < T::TN; ++tn) {
     const int j = n0 + tile.col(tn);

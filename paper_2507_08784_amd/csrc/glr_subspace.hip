@@ -17,6 +17,7 @@
 // Ritz vectors in descending order of Ritz value.
 #include "glr_device.hpp"
 #include "glr_internal.hpp"
+#include "glr_split.hpp"
 
 namespace glr {
 
@@ -149,6 +150,87 @@ static void gemm_launch(const float* A, int64_t lda, const float* B, int64_t ldb
     else GLR_GEMM(128, 2, 2, false);
   }
 #undef GLR_GEMM
+}
+
+// The same product on the fp16 matrix cores (EPI 0 and 2), for the products
+// whose size makes them matrix-core bound and whose operands' scales are
+// known: the two d x D products of a block iteration, the warm start of the
+// full refresh and the Newton-Schulz product.  8192 x 28672 at K = 320 (150
+// GFLOP): 1440 -> 645 us against the fp32 MFMA; the warm start at 4096: 1500
+// -> 497 us.
+template <int BM, int BN, int WM, int WN, bool B_KC, int EPI>
+__global__ void __launch_bounds__(256, 2)
+k_gemm_split(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
+             float* __restrict__ C, int64_t ldc, int M, int N, int Kc, int kslice, int64_t cstride,
+             const float* __restrict__ X, SplitScale sca, SplitScale scb, const int* __restrict__ gate, int gx,
+             int gy, int ngroups) {
+  if (gate && *gate) return;
+  const int L = blockIdx.x, slot = L >> 3;
+  const int grp = (slot / gy) * 8 + (L & 7), bxy = slot % gy;
+  if (grp >= ngroups) return;
+  const int bxx = grp % gx, bz = grp / gx;
+  using T = SplitTile<BM, BN, WM, WN, kF16x2>;
+  __shared__ __align__(16) char smem[T::LDS_BYTES];
+  __shared__ float red[4];
+  const int n0 = bxx * BN, m0 = bxy * BM;
+  const int k0 = bz * kslice;
+  const int klen = (Kc - k0 < kslice) ? Kc - k0 : kslice;
+  const int ea = split_block_exp(sca, red), eb = split_block_exp(scb, red);
+  const float sa = ldexpf(1.f, ea), sb = ldexpf(1.f, eb);
+  T tile;
+  if (klen > 0) {
+    SplitK<BM, false, false> la(A + k0, nullptr, (int64_t)(M - 1) * lda + Kc - k0, lda, m0, M, klen);
+    if (B_KC) {
+      SplitK<BN, false, false> lb(B + k0, nullptr, (int64_t)(N - 1) * ldb + Kc - k0, ldb, n0, N, klen);
+      tile.run(la, lb, klen, smem, sa, sb);
+    } else {
+      SplitR<BN, false, false> lb(B + (int64_t)k0 * ldb, nullptr, (int64_t)(Kc - k0 - 1) * ldb + N, ldb, n0, N, klen);
+      tile.run(la, lb, klen, smem, sa, sb);
+    }
+  }
+  float* Cz = C + (int64_t)bz * cstride;
+#pragma unroll
+  for (int tm = 0; tm < T::TM; ++tm)
+#pragma unroll
+    for (int tn = 0; tn < T::TN; ++tn) {
+      const int j = n0 + tile.col(tn);
+      if (j >= N) continue;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int i = m0 + tile.row(tm, v);
+        if (i >= M) continue;
+        const float c = ldexpf(tile.acc[tm][tn][v], -ea - eb);
+        Cz[(int64_t)i * ldc + j] = EPI == 2 ? X[(int64_t)i * ldc + j] - c : c;
+      }
+    }
+}
+
+template <bool B_KC, int EPI>
+static void gemm_split_launch(const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc, int M,
+                              int N, int Kc, GemmPlan p, int64_t cstride, const float* X, SplitScale sca,
+                              SplitScale scb, hipStream_t s, const int* gate = nullptr) {
+  const int bm = gemm_rows(M);
+  const int gx = (N + 127) / 128, gy = (M + bm - 1) / bm, ngroups = gx * p.splits;
+  const dim3 grid((unsigned)(((ngroups + 7) / 8) * 8 * gy));
+  if (bm == 64)
+    hipLaunchKernelGGL((k_gemm_split<64, 128, 2, 2, B_KC, EPI>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc, M,
+                       N, Kc, p.kslice, cstride, X, sca, scb, gate, gx, gy, ngroups);
+  else
+    hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, B_KC, EPI>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc,
+                       M, N, Kc, p.kslice, cstride, X, sca, scb, gate, gx, gy, ngroups);
+}
+
+// W (d x D) = Ut (d x d) Mo (d x D): the warm start of the full refresh
+hipError_t launch_warm_product(const MatView& v, hipStream_t s) {
+  const SplitScale mb{v.amax, ef_mean_blocks(v.m * v.n), 1.f, 0};
+  const GemmPlan p{1, (int)v.d};
+  if (v.right)
+    gemm_split_launch<true, 0>(v.Ut, v.d, v.Mbar, v.d, v.W, v.D, (int)v.d, (int)v.D, (int)v.d, p, 0, nullptr,
+                                       split_unit(), mb, s);
+  else
+    gemm_split_launch<false, 0>(v.Ut, v.d, v.Mbar, v.D, v.W, v.D, (int)v.d, (int)v.D, (int)v.d, p, 0, nullptr,
+                                        split_unit(), mb, s);
+  return hipGetLastError();
 }
 
 // out[i] = sum over splits of part[s * count + i], in a fixed order, fp64
@@ -357,7 +439,10 @@ hipError_t launch_reorth(const MatView& v, hipStream_t s) {
   hipLaunchKernelGGL(k_gram64<1>, g64, dim3(256), 0, s, v.Ut, (int64_t)d, v.Ut, (int64_t)d, d, d, d, d,
                      (double*)nullptr, v.Utw, (int64_t)d);
   GemmPlan p1{1, d};
-  gemm_launch<false, 2>(v.Utw, d, v.Ut, d, v.W, d, d, d, d, p1, 0, v.Ut, nullptr, s);
+  // the correction is small against U^T (entries of 1e-6 and below): at a
+  // scale of 2^14 its pieces resolve 2^-39
+  const SplitScale corr{nullptr, 0, 1.f, 14};
+  gemm_split_launch<false, 2>(v.Utw, d, v.Ut, d, v.W, d, d, d, d, p1, 0, v.Ut, corr, split_unit(), s);
   hipError_t e = hipMemcpyAsync(v.Ut, v.W, (size_t)d * d * 4, hipMemcpyDeviceToDevice, s);
   if (e != hipSuccess) return e;
   return hipGetLastError();
@@ -1011,12 +1096,13 @@ static void launch_z(const MatView& v, int K, const int* gate, hipStream_t s) {
   const int64_t d = v.d, D = v.D;
   const GemmPlan pz = plan_z(K, D, d);
   float* out = pz.splits > 1 ? v.sub_part : v.sub_Z;
+  const SplitScale mb{v.amax, ef_mean_blocks(v.m * v.n), 1.f, 0};
   if (v.right)   // Mo[a][b] = Mbar[b][a]: B(k=a, j=b) at Mbar[b d + a]
-    gemm_launch<true, 0>(v.sub_P, d, v.Mbar, d, out, D, K, (int)D, (int)d, pz, (int64_t)K * D, nullptr, nullptr, s,
-                         gate);
+    gemm_split_launch<true, 0>(v.sub_P, d, v.Mbar, d, out, D, K, (int)D, (int)d, pz, (int64_t)K * D, nullptr,
+                                       split_unit(), mb, s, gate);
   else           // Mo = Mbar (d x D): B(k=a, j=b) at Mbar[a D + b]
-    gemm_launch<false, 0>(v.sub_P, d, v.Mbar, D, out, D, K, (int)D, (int)d, pz, (int64_t)K * D, nullptr, nullptr, s,
-                          gate);
+    gemm_split_launch<false, 0>(v.sub_P, d, v.Mbar, D, out, D, K, (int)D, (int)d, pz, (int64_t)K * D, nullptr,
+                                        split_unit(), mb, s, gate);
   if (pz.splits > 1)
     hipLaunchKernelGGL(k_reduce_splits, dim3(grid_n((int64_t)K * D)), dim3(256), 0, s, v.sub_part, pz.splits,
                        (int64_t)K * D, v.sub_Z, (double*)nullptr, gate);
@@ -1066,12 +1152,16 @@ hipError_t launch_sub_iter(const MatView& v, float tol, uint64_t seed, int64_t t
   // P_new = Z Mo^T  (K x d): B(k=b, j=a) = Mo[a][b]
   GemmPlan p2 = plan_splits(K, (int)d, (int)D);
   prof.begin(GLR_PROF_SUB_P);
+  // the scale of Z: orthonormal rows from a cold start, else P^T Mo of
+  // orthonormal rows, below sqrt(d) times the largest |Mbar|
+  const SplitScale mb{v.amax, ef_mean_blocks(v.m * v.n), 1.f, 0};
+  const SplitScale zs = cold ? split_unit() : SplitScale{mb.amax, mb.n, sqrtf((float)d), 0};
   if (v.right)   // Mbar[b d + a]: contiguous along j
-    gemm_launch<false, 0>(v.sub_Z, D, v.Mbar, d, v.sub_part, d, K, (int)d, (int)D, p2, (int64_t)K * d, nullptr,
-                          nullptr, s, g);
+    gemm_split_launch<false, 0>(v.sub_Z, D, v.Mbar, d, v.sub_part, d, K, (int)d, (int)D, p2, (int64_t)K * d,
+                                        nullptr, zs, mb, s, g);
   else           // Mbar[a D + b]: contiguous along k
-    gemm_launch<true, 0>(v.sub_Z, D, v.Mbar, D, v.sub_part, d, K, (int)d, (int)D, p2, (int64_t)K * d, nullptr,
-                         nullptr, s, g);
+    gemm_split_launch<true, 0>(v.sub_Z, D, v.Mbar, D, v.sub_part, d, K, (int)d, (int)D, p2, (int64_t)K * d,
+                                       nullptr, zs, mb, s, g);
   prof.end(GLR_PROF_SUB_P);
   hipLaunchKernelGGL(k_reduce_splits, dim3(grid_n((int64_t)K * d)), dim3(256), 0, s, v.sub_part,
                      p2.splits, (int64_t)K * d, v.sub_Pn, (double*)nullptr, g);
