@@ -532,37 +532,11 @@ struct MfmaTile {
     }
   }
 
-  // the same product with both operands rounded to bf16 (to nearest even) as
-  // they leave LDS, fp32 accumulation: two bf16 MFMAs of depth 16 per slice
-  template <bool SWA, bool SWB>
-  __device__ __forceinline__ void compute_bf16(const float* As, const float* Bs) {
-    const int kh = lane >> 5, l32 = lane & 31;
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      // rows 16 ks + 8 kh .. + 7 share one swizzle
-      const int ca = SWA ? (l32 ^ lds_swz(16 * ks + 8 * kh)) : l32;
-      const int cb = SWB ? (l32 ^ lds_swz(16 * ks + 8 * kh)) : l32;
-      bf16x8 a[TM], b[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) a[i][e] = (__bf16)As[(16 * ks + 8 * kh + e) * PA + wm * WTM + i * 32 + ca];
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) b[j][e] = (__bf16)Bs[(16 * ks + 8 * kh + e) * PB + wn * WTN + j * 32 + cb];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma32_bf16(a[i], b[j], acc[i][j]);
-    }
-  }
-
-  // acc += A B over K (BF16: with both operands rounded to bf16).  With `dacc`,
+  // acc += A B over K.  With `dacc`,
   // the fp32 accumulators are added into fp64 ones after every 16 BK slices
   // and cleared, so that rounding grows with that length only (dacc holds the
   // result then; acc is zero).
-  template <bool BF16 = false, class LA, class LB>
+  template <class LA, class LB>
   __device__ void run(LA& la, LB& lb, int K, float* smem, double (*dacc)[TN][16] = nullptr) {
     float* As = smem;
     float* Bs = smem + SA;
@@ -579,8 +553,7 @@ struct MfmaTile {
         la.fetch((kb + 1) * BK);
         lb.fetch((kb + 1) * BK);
       }
-      if constexpr (BF16) compute_bf16<LA::kSwz, LB::kSwz>(As, Bs);
-      else compute<LA::kSwz, LB::kSwz>(As, Bs);
+      compute<LA::kSwz, LB::kSwz>(As, Bs);
       if (dacc && ((kb & 15) == 15 || !more)) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)

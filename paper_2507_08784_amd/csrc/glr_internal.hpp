@@ -116,6 +116,7 @@ struct MatView {
   float* X;      const void* G;
   // workspace
   float* Mbar;   float* Q;     float* Qpart; float* lam_part;
+  void* Qf; int* Qe; void* Pf;   // packed pieces of Q^(i), their exponents, pieces of P
   float* amax;     // largest |Mbar| of each block of the worker mean (ef_mean_blocks of them)
   float* W;      float* Utw;   double* Apk;  double* Apk2; float* Vrot;   double* V64;   int* skip;
   double* gpart;   // split-contraction partials of the Gram (or null)
@@ -177,8 +178,17 @@ inline int proj_kslice(int64_t d, int64_t D, int r, int N) {
   return (int)(((d + sp - 1) / sp + 31) / 32 * 32);
 }
 
-// above this rank the residuals come first from a wider-tile kernel
-constexpr int kResidWideRank = 128;
+// Up to this rank the residual pass takes P and Q^(i) as packed fp16 pieces
+// (P's fragments fit its registers); above it fp32 operands through LDS.
+constexpr int kPackRank = 256;
+// 16-deep MFMA steps rank r is padded to: a power of two
+__host__ __device__ inline int pack_steps(int r) {
+  int k = 1;
+  while (16 * k < r) k *= 2;
+  return k;
+}
+// largest rank of a grouped selection step
+constexpr int kGroupMaxRank = 128;
 
 struct OptParams {
   int opt;                   // 0 MSGD, 1 Adam, 2 plain step X -= lr Ghat (GaLore: Ghat = P Rhat)
@@ -194,7 +204,8 @@ hipError_t launch_sel_scores(const MatView& v, bool approx, bool bf16, uint64_t 
 hipError_t launch_topr(const MatView& v, hipStream_t s);
 hipError_t launch_iota_J(const MatView& v, hipStream_t s);
 hipError_t launch_proj(const MatView& v, hipStream_t s);
-hipError_t launch_rbar(const MatView& v, hipStream_t s);
+// Rbar, and Q^(i): as fp32, or packed with P for the split residual pass
+hipError_t launch_rbar(const MatView& v, bool packed, hipStream_t s);
 hipError_t launch_resid_opt(const MatView& v, const OptParams& o, hipStream_t s);
 hipError_t launch_full_refresh(const MatView& v, const OptParams& o, hipStream_t s);
 // Algorithm 5 (GaLore Adam in the r x D subspace): S1, S2 <- the moments of

@@ -35,7 +35,7 @@ inline uint64_t align_up(uint64_t x) { return (x + kAlign - 1) / kAlign * kAlign
 thread_local std::string g_create_error;
 
 struct WsLayout {
-  uint64_t off_Mbar, off_Q, off_Qpart, off_lam, off_amax, off_W, off_Utw, off_gram, off_gram2, off_V, off_V64, off_gpart, off_skip,
+  uint64_t off_Mbar, off_Q, off_Qpart, off_Qf, off_Qe, off_Pf, off_lam, off_amax, off_W, off_Utw, off_gram, off_gram2, off_V, off_V64, off_gpart, off_skip,
       off_ctl, off_sigw, off_perm;
   uint64_t off_sP, off_sPn, off_sZ, off_sZt, off_sR, off_spart, off_sS, off_sL, off_sDinv, off_sLi,
       off_sT, off_sLinv, off_sC, off_ssums, off_sctl, off_sbad;
@@ -169,17 +169,31 @@ uint64_t state_bytes_of(const glr_config* c) {
   return o;
 }
 
+// whether the residual pass takes packed operands: error feedback on and a
+// rank it holds P of in registers (GaLore Adam keeps no error buffers)
+bool error_feedback(const glr_config* c) { return !(c->flags & GLR_NO_EF) && c->opt != GLR_GALORE_ADAM; }
+bool packed_resid(const glr_config* c, const Dims& x) { return x.r <= kPackRank && error_feedback(c); }
+
 WsLayout ws_layout(const glr_config* c, int first, int last) {
   uint64_t mx_mn = 0, mx_Q = 0, mx_Qp = 0, mx_lam = 0, mx_dD = 0, mx_dd = 0, mx_gram = 0, mx_groups = 0, mx_vbuf = 0, mx_d = 0;
+  uint64_t p_Q = 0, p_Qe = 0, p_P = 0;
   uint64_t s_Kd = 0, s_KD = 0, s_part = 0, s_KK = 0, s_Kp2 = 0, s_nt = 0, s_sums = 0, s_Kp = 0;
   uint64_t r_gram = 0, r_groups = 0, r_vbuf = 0, r_gpart = 0, mx_gpart = 0;
   auto mx = [](uint64_t& a, uint64_t b) { if (b > a) a = b; };
   for (int i = first; i < last; ++i) {
     const Dims x = dims_of(c, i);
     mx(mx_mn, (uint64_t)(x.m * x.n));
-    mx(mx_Q, (uint64_t)c->num_workers * (uint64_t)x.r * (uint64_t)x.D);
     const int ps = proj_splits(x.d, x.D, x.r, c->num_workers);
-    if (ps > 1) mx(mx_Qp, (uint64_t)ps * c->num_workers * (uint64_t)x.r * (uint64_t)x.D);
+    mx(mx_Qp, (uint64_t)ps * c->num_workers * (uint64_t)x.r * (uint64_t)x.D);
+    if (packed_resid(c, x)) {
+      // two 16-bit pieces a value, padded to whole 32 x 16 fragments
+      const uint64_t k16 = 16 * (uint64_t)pack_steps(x.r), D32 = (uint64_t)(x.D + 31) / 32 * 32;
+      mx(p_Q, c->num_workers * D32 * k16 * 4);
+      mx(p_Qe, c->num_workers * D32 * 4);
+      mx(p_P, (uint64_t)(x.d + 31) / 32 * 32 * k16 * 4);
+    } else {
+      mx(mx_Q, (uint64_t)c->num_workers * (uint64_t)x.r * (uint64_t)x.D);
+    }
     mx(mx_lam, (uint64_t)((x.D + 127) / 128) * (uint64_t)x.d);
     mx(mx_d, (uint64_t)x.d);
     if (use_subspace(c->tau, x.r, x.d)) {
@@ -219,6 +233,9 @@ WsLayout ws_layout(const glr_config* c, int first, int last) {
   w.off_Mbar = take(mx_mn * 4);
   w.off_Q = take(mx_Q * 4);
   w.off_Qpart = take(mx_Qp * 4);
+  w.off_Qf = take(p_Q);
+  w.off_Qe = take(p_Qe);
+  w.off_Pf = take(p_P);
   w.off_lam = take(mx_lam * 4);
   w.off_amax = take((uint64_t)ef_mean_blocks((int64_t)mx_mn) * 4);
   w.off_W = take(mx_dD * 4);
@@ -423,6 +440,9 @@ MatView view_of(glr_handle* h, int mat, float* X, const void* G, int lane) {
   v.Qpart = (float*)(w + WL.off_Qpart);
   v.lam_part = (float*)(w + WL.off_lam);
   v.amax = (float*)(w + WL.off_amax);
+  v.Qf = w + WL.off_Qf;
+  v.Qe = (int*)(w + WL.off_Qe);
+  v.Pf = w + WL.off_Pf;
   v.W = (float*)(w + WL.off_W);
   v.Utw = (float*)(w + WL.off_Utw);
   v.Apk = (double*)(w + WL.off_gram);
@@ -689,7 +709,7 @@ glr_status step_tail(glr_handle* h, const MatView& v, bool refresh, hipStream_t 
   }
   {
     ProfScope p(h, s, GLR_PROF_RBAR);
-    GLR_HIP(h, launch_rbar(v, s));
+    GLR_HIP(h, launch_rbar(v, h->ef && v.r <= kPackRank, s));
   }
   if (galore) GLR_HIP(h, launch_galore_adam(v, op, refresh, s));
   if (refresh && c.refresh == GLR_REFRESH_FULL) {
@@ -922,7 +942,7 @@ bool group_allowed(const glr_handle* h) {
   const glr_mat_layout& L0 = h->lay[0];
   for (int i = 0; i < c.num_mats; ++i) {
     const glr_mat_layout& L = h->lay[(size_t)i];
-    if (L.d > kJointMaxDim || L.r >= L.d || L.r > kResidWideRank || L.r != L0.r || L.right != L0.right)
+    if (L.d > kJointMaxDim || L.r >= L.d || L.r > kGroupMaxRank || L.r != L0.r || L.right != L0.right)
       return false;
   }
   return true;

@@ -417,13 +417,12 @@ static hipError_t launch_proj_st(const MatView& v, hipStream_t s) {
   const ST* E = static_cast<const ST*>(v.E);
   const int splits = proj_splits(v.d, v.D, r, v.N);
   const int64_t kslice = proj_kslice(v.d, v.D, r, v.N);
-  float* const out = splits > 1 ? v.Qpart : v.Q;
   const bool vec = proj_vec(v, sizeof(ST));
   dim3 grid;
   grid.z = (unsigned)(v.N * splits);
 #define GLR_PROJ1(BM, BN, WM, WN, FL, R, VE)                                                      \
   hipLaunchKernelGGL((k_proj<BM, BN, WM, WN, R, FL, ST, VE>), gr, dim3(kThreads), 0, s, G, E, v.Ut, \
-                     v.J, out, v.d, v.D, r, v.N, (int)kslice, gx, gy, ntiles)
+                     v.J, v.Qpart, v.d, v.D, r, v.N, (int)kslice, gx, gy, ntiles)
 #define GLR_PROJ(BM, BN, WM, WN, FL)                                                              \
   do {                                                                                            \
     const int gx = (int)((v.D + BN - 1) / BN), gy = (r + BM - 1) / BM;                            \
@@ -468,12 +467,8 @@ __device__ __forceinline__ void proj_reduce_at(const float* __restrict__ part, i
     double rsum = 0.0;
     for (int w = 0; w < N; ++w) {
       double q = 0.0;
-      if (splits > 1) {
-        for (int z = 0; z < splits; ++z) q += (double)part[((int64_t)z * N + w) * rD + i];
-        Q[(int64_t)w * rD + i] = (float)q;
-      } else {
-        q = (double)Q[(int64_t)w * rD + i];
-      }
+      for (int z = 0; z < splits; ++z) q += (double)part[((int64_t)z * N + w) * rD + i];
+      Q[(int64_t)w * rD + i] = (float)q;
       rsum += q;
     }
     Rbar[i] = (float)(rsum / (double)N);
@@ -484,171 +479,430 @@ __global__ void k_proj_reduce(const float* __restrict__ part, int splits, int N,
   proj_reduce_at(part, splits, N, rD, Q, Rbar, blockIdx.x, gridDim.x);
 }
 
-hipError_t launch_rbar(const MatView& v, hipStream_t s) {
-  const int64_t rD = (int64_t)v.r * v.D;
+// The same for the split residual pass (resid_packed): Q^(i) and P leave as
+// fp16 pieces in the order in which its MFMAs read them, so that it needs
+// neither LDS nor conversions.  A fragment is 64 lanes x 8 values of k: lane l
+// holds row 32 blk + l % 32 of the operand (a column b of Q, a row a of P) at
+// k = 16 ks + 8 (l / 32) ..+7; the fragment of piece p, step ks, block blk is
+// at ((blk KS + ks) 2 + p) 64 (u32x4), KS the steps r is padded to with zeros.
+// Each column of Q^(i) has a scale of its own (its exponent in Qe): the
+// residual is compared and Adam normalises element by element, so a column far
+// smaller than the rest keeps its relative precision.  |P| <= 1: one scale.
+// Bound by reading the projection's slices, and for small ranks by latency.
+// Up to rank 128 a wave holds all of a column (8 KS values a lane) and takes
+// the 32 columns of one worker's block by itself, and other workgroups of the
+// launch form Rbar from a second read of the slices (pack_waves).  Above, a
+// workgroup of 1024 reads the slices of 32 columns once for all workers, in
+// turn, for both (pack_block): there the second read would cost more (0.94 GB
+// at 8192 x 28672), and the chain of barriers less: per launch 350 us against
+// 65 of pack_waves for the fifty layers at rank 8, 143 against 96 at
+// 11008 x 4096, rank 128.
+constexpr int kPackThreads = 1024;
+constexpr int kPackWaveSteps = 8;   // largest KS of pack_waves
+__device__ __forceinline__ void pack_store(const float (&x)[8], float scale, u32x4* dst) {
+  u32x4 h, l;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    uint32_t p[2];
+    split_pair<kF16x2>(x[2 * e], x[2 * e + 1], scale, p);
+    h[e] = p[0];
+    l[e] = p[1];
+  }
+  dst[0] = h;
+  dst[64] = l;
+}
+// fragment f = blk KS + ks of P, by one wave
+__device__ __forceinline__ void pack_p(int f, int r, int KS, int64_t d, const float* __restrict__ Ut,
+                                       const int* __restrict__ J, u32x4* __restrict__ Pf) {
+  const int blk = f / KS, ks = f % KS, lane = lane_id();
+  if (blk >= (int)((d + 31) / 32)) return;
+  const int a = blk * 32 + (lane & 31);
+  float x[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int k = 16 * ks + 8 * (lane >> 5) + e;
+    x[e] = (k < r && a < d) ? Ut[(int64_t)J[k] * d + a] : 0.f;
+  }
+  pack_store(x, ldexpf(1.f, kUnitExp), Pf + (int64_t)f * 128 + lane);
+}
+// blocks of kThreads: four fragments columns of Q each, then four fragments of
+// P each, then Rbar
+struct PackGrid {
+  int q, p, rbar;
+};
+__host__ __device__ inline PackGrid pack_grid(int64_t d, int64_t D, int N, int r, int KS) {
+  const int64_t q = (D + 31) / 32 * N, p = (d + 31) / 32 * KS, rb = ((int64_t)r * D + kThreads - 1) / kThreads;
+  return {(int)((q + 3) / 4), (int)((p + 3) / 4), (int)rb};
+}
+template <int KS>
+__device__ __forceinline__ void pack_waves(const float* __restrict__ part, int splits, int N, int r, int64_t d,
+                                           int64_t D, const float* __restrict__ Ut, const int* __restrict__ J,
+                                           u32x4* __restrict__ Qf, int* __restrict__ Qe, u32x4* __restrict__ Pf,
+                                           float* __restrict__ Rbar, int bid) {
+  const PackGrid g = pack_grid(d, D, N, r, KS);
+  const int64_t rD = (int64_t)r * D;
+  const int lane = lane_id();
+  if (bid < g.q) {
+    const int item = bid * 4 + wave_id(), nqb = (int)((D + 31) / 32);
+    if (item >= nqb * N) return;
+    const int w = item / nqb, blk = item % nqb;
+    const int64_t b = (int64_t)blk * 32 + (lane & 31);
+    // a run of 16 loads a slice (KC steps at a time: fp64 sums of all of them
+    // would leave two waves per SIMD), the row as the scalar part of the
+    // address; what lies past r is dropped below
+    constexpr int KC = KS < 2 ? KS : 2;
+    const uint32_t off = (uint32_t)((8 * (lane >> 5) * D + (b < D ? b : D - 1)) * 4);
+    float x[KS][8], mx = 0.f;
+#pragma unroll
+    for (int k0 = 0; k0 < KS; k0 += KC) {
+      double s[KC][8];
+#pragma unroll
+      for (int ks = 0; ks < KC; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[ks][e] = 0.0;
+      for (int z = 0; z < splits; ++z) {
+        const BufRsrc pz = buf_rsrc(part + ((int64_t)z * N + w) * rD, (uint32_t)(rD * 4));
+        float t[KC][8];
+#pragma unroll
+        for (int ks = 0; ks < KC; ++ks)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int k = 16 * (k0 + ks) + e < r ? 16 * (k0 + ks) + e : 0;
+            t[ks][e] =
+                __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(pz, (int)off, (int)(uint32_t)(k * D * 4), 0));
+          }
+#pragma unroll
+        for (int ks = 0; ks < KC; ++ks)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) s[ks][e] += (double)t[ks][e];
+      }
+#pragma unroll
+      for (int ks = 0; ks < KC; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          x[k0 + ks][e] = (16 * (k0 + ks) + 8 * (lane >> 5) + e < r && b < D) ? (float)s[ks][e] : 0.f;
+          mx = fmaxf(mx, fabsf(x[k0 + ks][e]));
+        }
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const int e2 = split_exp(mx);
+    if (lane < 32) Qe[(int64_t)item * 32 + lane] = e2;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) pack_store(x[ks], ldexpf(1.f, e2), Qf + ((int64_t)item * KS + ks) * 128 + lane);
+  } else if (bid < g.q + g.p) {
+    pack_p((bid - g.q) * 4 + wave_id(), r, KS, d, Ut, J, Pf);
+  } else {
+    const int64_t i = (int64_t)(bid - g.q - g.p) * kThreads + threadIdx.x;
+    if (i >= rD) return;
+    double rsum = 0.0;
+    for (int w = 0; w < N; ++w) {
+      double q = 0.0;
+      for (int z = 0; z < splits; ++z) q += (double)part[((int64_t)z * N + w) * rD + i];
+      rsum += q;
+    }
+    Rbar[i] = (float)(rsum / (double)N);
+  }
+}
+__device__ __forceinline__ void pack_block(const float* __restrict__ part, int splits, int N, int r, int KS, int64_t d,
+                                        int64_t D, const float* __restrict__ Ut, const int* __restrict__ J,
+                                        u32x4* __restrict__ Qf, int* __restrict__ Qe, u32x4* __restrict__ Pf,
+                                        float* __restrict__ Rbar, int bid, float* dyn) {
+  const int tid = threadIdx.x, nqb = (int)((D + 31) / 32);
+  if (bid >= nqb) {
+    pack_p((bid - nqb) * (kPackThreads / 64) + (tid >> 6), r, KS, d, Ut, J, Pf);
+    return;
+  }
+  constexpr int KG = kPackThreads / 32;            // rows of k side by side
+  constexpr int MAXK = kPackRank / KG;             // rows of k per thread
+  float* tile = dyn;                               // 16 KS x 33
+  float* red = dyn + 16 * KS * 33;                 // (waves) x 32
+  const int c = tid & 31, kg = tid >> 5;
+  const int64_t b = (int64_t)bid * 32 + c, rD = (int64_t)r * D;
+  double rsum[MAXK];
+#pragma unroll
+  for (int q = 0; q < MAXK; ++q) rsum[q] = 0.0;
+  for (int w = 0; w < N; ++w) {
+    float mx = 0.f;
+#pragma unroll
+    for (int q = 0; q < MAXK; ++q) {
+      const int k = kg + q * KG;
+      if (k >= 16 * KS) break;
+      double s = 0.0;
+      if (k < r && b < D)
+        for (int z = 0; z < splits; ++z) s += (double)part[((int64_t)z * N + w) * rD + (int64_t)k * D + b];
+      rsum[q] += s;
+      tile[k * 33 + c] = (float)s;
+      mx = fmaxf(mx, fabsf((float)s));
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    if ((tid & 63) < 32) red[(tid >> 6) * 32 + c] = mx;
+    __syncthreads();
+    mx = 0.f;
+#pragma unroll
+    for (int i = 0; i < kPackThreads / 64; ++i) mx = fmaxf(mx, red[i * 32 + c]);
+    const int e2 = split_exp(mx);
+    if (tid < 32) Qe[((int64_t)w * nqb + bid) * 32 + c] = e2;
+    if (tid < KS * 64) {
+      const int lane = tid & 63, ks = tid >> 6;    // lane & 31 == c
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = tile[(16 * ks + 8 * (lane >> 5) + e) * 33 + c];
+      pack_store(x, ldexpf(1.f, e2), Qf + (((int64_t)w * nqb + bid) * KS + ks) * 128 + lane);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int q = 0; q < MAXK; ++q) {
+    const int k = kg + q * KG;
+    if (k < r && b < D) Rbar[(int64_t)k * D + b] = (float)(rsum[q] / (double)N);
+  }
+}
+static size_t pack_lds(int KS) { return ((size_t)16 * KS * 33 + (size_t)kPackThreads / 64 * 32) * 4; }
+static int pack_blocks(int64_t d, int64_t D, int N, int r) {
+  const int KS = pack_steps(r);
+  if (KS <= kPackWaveSteps) {
+    const PackGrid g = pack_grid(d, D, N, r, KS);
+    return g.q + g.p + g.rbar;
+  }
+  const int64_t frags = (d + 31) / 32 * KS;
+  return (int)((D + 31) / 32 + (frags + kPackThreads / 64 - 1) / (kPackThreads / 64));
+}
+__global__ void __launch_bounds__(kPackThreads)
+k_pack_block(const float* __restrict__ part, int splits, int N, int r, int KS, int64_t d, int64_t D,
+             const float* __restrict__ Ut, const int* __restrict__ J, u32x4* __restrict__ Qf, int* __restrict__ Qe,
+             u32x4* __restrict__ Pf, float* __restrict__ Rbar) {
+  extern __shared__ __align__(16) unsigned char dyn[];
+  pack_block(part, splits, N, r, KS, d, D, Ut, J, Qf, Qe, Pf, Rbar, blockIdx.x, reinterpret_cast<float*>(dyn));
+}
+template <int KS>
+__global__ void __launch_bounds__(kThreads)
+k_pack_waves(const float* __restrict__ part, int splits, int N, int r, int64_t d, int64_t D,
+             const float* __restrict__ Ut, const int* __restrict__ J, u32x4* __restrict__ Qf, int* __restrict__ Qe,
+             u32x4* __restrict__ Pf, float* __restrict__ Rbar) {
+  pack_waves<KS>(part, splits, N, r, d, D, Ut, J, Qf, Qe, Pf, Rbar, blockIdx.x);
+}
+
+hipError_t launch_rbar(const MatView& v, bool packed, hipStream_t s) {
   const int splits = proj_splits(v.d, v.D, v.r, v.N);
+  if (packed) {
+    const int KS = pack_steps(v.r);
+    const dim3 grid((unsigned)pack_blocks(v.d, v.D, v.N, v.r));
+#define GLR_PW(K)                                                                                                  \
+  hipLaunchKernelGGL(k_pack_waves<K>, grid, dim3(kThreads), 0, s, v.Qpart, splits, v.N, v.r, v.d, v.D, v.Ut, v.J, \
+                     (u32x4*)v.Qf, v.Qe, (u32x4*)v.Pf, v.Rbar)
+    switch (KS) {
+      case 1: GLR_PW(1); break;
+      case 2: GLR_PW(2); break;
+      case 4: GLR_PW(4); break;
+      case 8: GLR_PW(8); break;
+      default:
+        hipLaunchKernelGGL(k_pack_block, grid, dim3(kPackThreads), pack_lds(KS), s, v.Qpart, splits, v.N, v.r, KS, v.d,
+                           v.D, v.Ut, v.J, (u32x4*)v.Qf, v.Qe, (u32x4*)v.Pf, v.Rbar);
+    }
+    static_assert(kPackWaveSteps == 8, "one variant per KS");
+#undef GLR_PW
+    return hipGetLastError();
+  }
+  const int64_t rD = (int64_t)v.r * v.D;
   hipLaunchKernelGGL(k_proj_reduce, dim3(grid_for(rD)), dim3(kThreads), 0, s, v.Qpart, splits, v.N, rD, v.Q,
                      v.Rbar);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// S5 + S7 + S8 fused, one pass over a ROWS x 64 tile of the m x n layout:
-//   C^(i) = (P Q^(i)) in the caller's layout (rank-r MFMA product)
+// S5 + S7 + S8 fused, one pass over the m x n layout, up to rank 256:
+//   C^(i) = P Q^(i) in the caller's layout
 //   E^(i) <- (G^(i) - C^(i)) + E^(i)
-//   Ghat  = P Rbar;  Ebar = the mean of the stored E^(i) (summed in
-//   registers as they are written: Mbar - Ghat equals it in real
-//   arithmetic, but when the residual is small against Mbar that difference
-//   keeps only the low bits of two nearly equal fp32 values);
+//   Ghat  = (1/N) sum_i C^(i) (= P Rbar by linearity);
+//   Ebar  = the mean of the stored E^(i) (summed in registers as they are
+//   written: Mbar - Ghat equals it in real arithmetic, but when the residual
+//   is small against Mbar that difference keeps only the low bits of two
+//   nearly equal fp32 values);
 //   optimizer on X with Ghat.
-// MFMA rows are tile rows and lanes are tile columns, so that a load or
-// store of one accumulator register moves two whole 128-byte rows of 32
-// columns: every written line of E, X, the optimizer state and Ebar is
-// covered by one instruction (partial-line writes make the memory side
-// fetch the line first).  P (gathered rows of U^T) and Q^(i) are staged
-// through LDS by the tile engine, 32 rank indices at a time.
+// A wave owns a 32 x 32 tile of the layout for all workers: the pieces of P
+// for its rows (columns when RIGHT) stay in its registers, those of Q^(i) come
+// as fragments straight from the cache (k_pack), and there is no LDS and no
+// barrier, so that the waves of a CU drift apart and the loads of some cover
+// the products of others.  MFMA lanes are tile columns, so that a load or
+// store of one accumulator register moves whole 128-byte rows of 32 columns
+// (partial-line writes make the memory side fetch the line first).  h h goes
+// into one accumulator, h l + l h into another: the sums that the large one
+// rounds are a third as many.
+// Bound by HBM: G and E in, E out, X, the optimizer state and Ebar.  Before
+// (fp32 MFMA on LDS slices, P Rbar as a product of its own): 4096 x 4096,
+// r = 64, N = 8: 496 -> 382 us (5.4 TB/s, the rate of a large copy);
+// 11008 x 4096, r = 128: 1890 -> 1450 us; the same in bf16: 1705 -> 1084 us;
+// 8192 x 28672, r = 256, N = 4: 6.73 -> 5.11 ms.
 // ---------------------------------------------------------------------------
-template <int OPT, bool RIGHT, int ROWS, int RO_COLS, class ST>
-__device__ __forceinline__ void resid_opt_at(const ST* __restrict__ G, ST* __restrict__ E,
-                                             float* __restrict__ Ebar,
-            const float* __restrict__ Mbar, const float* __restrict__ Q, const float* __restrict__ Rbar,
-            const float* __restrict__ Ut,
-            const int* __restrict__ J,
-            float* __restrict__ X, float* __restrict__ S1, float* __restrict__ S2, int64_t m,
-            int64_t n, int64_t d, int64_t D, int r, int N, OptParams op, int bx, int by) {
-  using T = MfmaTile<ROWS, RO_COLS, ROWS / 32, 128 / ROWS>;
-  constexpr int TM = T::TM;
-  static_assert(T::TN == 1, "one tile column per lane");
-  __shared__ __align__(16) float smem[T::LDS_FLOATS];
-  const int c0 = bx * RO_COLS;   // first column of the tile
-  const int r0 = by * ROWS;      // first row of the tile
+template <int OPT, bool RIGHT, int KS, class ST>
+__device__ __forceinline__ void resid_packed_at(const ST* __restrict__ G, ST* __restrict__ E, float* __restrict__ Ebar,
+                                                const u32x4* __restrict__ Qf, const int* __restrict__ Qe,
+                                                const u32x4* __restrict__ Pf, float* __restrict__ X,
+                                                float* __restrict__ S1, float* __restrict__ S2, int64_t m, int64_t n,
+                                                int N, const OptParams& op, int bx, int by) {
+  const int lane = lane_id(), wv = wave_id();
+  const int64_t r0 = (int64_t)by * 64 + (wv >> 1) * 32, c0 = (int64_t)bx * 64 + (wv & 1) * 32;
+  if (r0 >= m || c0 >= n) return;
   const int64_t mn = m * n;
-  // this lane's outputs: column cc, rows r0 + row(tm, v) = rb[tm] + rv(v)
-  // with rv(v) = 8 (v / 4) + v % 4 the same in every lane
-  T geo;
-  const int64_t cc = c0 + geo.col(0);
-  const bool cok = cc < n;
-  // every m x n array is addressed as a buffer (m n 4 < 2^32 bytes): a
-  // uniform descriptor and one 32-bit byte offset per element, shared by all
-  // of them; elements outside the matrix take kBufNone
-  const uint32_t bytes = (uint32_t)(mn * 4);
-  uint32_t ob[TM][16];
+  const int64_t nqb = ((RIGHT ? m : n) + 31) / 32, qblk = (RIGHT ? r0 : c0) / 32, pblk = (RIGHT ? c0 : r0) / 32;
+  u32x4 ph[KS], pl[KS];
 #pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
+  for (int ks = 0; ks < KS; ++ks) {
+    ph[ks] = Pf[(pblk * KS + ks) * 128 + lane];
+    pl[ks] = Pf[(pblk * KS + ks) * 128 + 64 + lane];
+  }
+  // every m x n array is addressed as a buffer (m n 4 < 2^32 bytes): a uniform
+  // descriptor and one 32-bit byte offset per element, shared by all of them;
+  // elements outside the matrix take kBufNone
+  const int64_t cc = c0 + (lane & 31);
+  uint32_t ob[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int64_t row = r0 + mfma32_row(v, lane);
+    ob[v] = (cc < n && row < m) ? (uint32_t)((row * n + cc) * 4) : kBufNone;
+  }
+  float esum[16], gsum[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) esum[v] = gsum[v] = 0.f;
+  for (int w = 0; w < N; ++w) {
+    const BufRsrc Gi = buf_rsrc_s(G + (int64_t)w * mn, mn);
+    const BufRsrc Ei = buf_rsrc_s(E + (int64_t)w * mn, mn);
+    float gv[16], eo[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const int64_t row = r0 + geo.row(tm, v);
-      ob[tm][v] = (cok && row < m) ? (uint32_t)((row * n + cc) * 4) : kBufNone;
+      gv[v] = buf_lde<ST>(Gi, ob[v]);
+      eo[v] = buf_lde<ST>(Ei, ob[v]);
     }
-  // Ebar: the mean of the stored residuals
-  float esum[TM][16];
+    const u32x4* q = Qf + ((int64_t)w * nqb + qblk) * KS * 128 + lane;
+    const int* qe = Qe + ((int64_t)w * nqb + qblk) * 32;
+    f32x16 big, small;
 #pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
+    for (int v = 0; v < 16; ++v) big[v] = small[v] = 0.f;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) esum[tm][v] = 0.f;
-  for (int wk = 0; wk < N; ++wk) {
-    const BufRsrc Gi = buf_rsrc_s(G + (int64_t)wk * mn, mn);
-    const BufRsrc Ei = buf_rsrc_s(E + (int64_t)wk * mn, mn);
-    const float* Qi = Q + (int64_t)wk * r * D;
-    // G^(i) and E^(i) for this lane's elements, in flight during the product
-    float gv[TM][16], eo[TM][16];
-#pragma unroll
-    for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        gv[tm][v] = buf_lde<ST>(Gi, ob[tm][v]);
-        eo[tm][v] = buf_lde<ST>(Ei, ob[tm][v]);
+    for (int ks = 0; ks < KS; ++ks) {
+      const u32x4 qh = q[ks * 128], ql = q[ks * 128 + 64];
+      if (RIGHT) {
+        small = split_mfma<kF16x2>(qh, pl[ks], small);
+        big = split_mfma<kF16x2>(qh, ph[ks], big);
+        small = split_mfma<kF16x2>(ql, ph[ks], small);
+      } else {
+        small = split_mfma<kF16x2>(pl[ks], qh, small);
+        big = split_mfma<kF16x2>(ph[ks], qh, big);
+        small = split_mfma<kF16x2>(ph[ks], ql, small);
       }
-    T tile;
-    if (!RIGHT) {
-      // rows a < d, columns b < D: C[a][b] = sum_k Ut[J[k]][a] Q[k][b]
-      LoadR<ROWS, 32, false, true> la(Ut, nullptr, d, r0, (int)d, r, J);
-      LoadR<RO_COLS, 32, false> lb(Qi, nullptr, D, c0, (int)D, r);
-      tile.run(la, lb, r, smem);
+    }
+    // columns of Q are tile rows (RIGHT) or this lane's column
+    int ex[RIGHT ? 16 : 1];
+    if (RIGHT) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int4 x = *reinterpret_cast<const int4*>(qe + 8 * g + 4 * (lane >> 5));
+        ex[RIGHT ? 4 * g : 0] = x.x; ex[RIGHT ? 4 * g + 1 : 0] = x.y;
+        ex[RIGHT ? 4 * g + 2 : 0] = x.z; ex[RIGHT ? 4 * g + 3 : 0] = x.w;
+      }
     } else {
-      // rows b < D, columns a < d: C[b][a] = sum_k Q[k][b] Ut[J[k]][a]
-      LoadR<ROWS, 32, false> la(Qi, nullptr, D, r0, (int)D, r);
-      LoadR<RO_COLS, 32, false, true> lb(Ut, nullptr, d, c0, (int)d, r, J);
-      tile.run(la, lb, r, smem);
+      ex[0] = qe[lane & 31];
     }
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        // (G - P Q) + E: G and P Q nearly cancel, E is the small part
-        const float e = (gv[tm][v] - tile.acc[tm][0][v]) + eo[tm][v];
-        buf_ste<ST>(Ei, ob[tm][v], e);
-        esum[tm][v] += stored<ST>(e);
-      }
+    for (int v = 0; v < 16; ++v) {
+      const float c = ldexpf(big[v] + small[v], -ex[RIGHT ? v : 0] - kUnitExp);
+      // (G - P Q) + E: G and P Q nearly cancel, E is the small part
+      const float e = (gv[v] - c) + eo[v];
+      buf_ste<ST>(Ei, ob[v], e);
+      esum[v] += stored<ST>(e);
+      gsum[v] += c;
+    }
   }
-
-  // Ghat = P Rbar (the reconstruction of the averaged payload)
-  T tile;
-  if (!RIGHT) {
-    LoadR<ROWS, 32, false, true> la(Ut, nullptr, d, r0, (int)d, r, J);
-    LoadR<RO_COLS, 32, false> lb(Rbar, nullptr, D, c0, (int)D, r);
-    tile.run(la, lb, r, smem);
-  } else {
-    LoadR<ROWS, 32, false> la(Rbar, nullptr, D, r0, (int)D, r);
-    LoadR<RO_COLS, 32, false, true> lb(Ut, nullptr, d, c0, (int)d, r, J);
-    tile.run(la, lb, r, smem);
-  }
+  const uint32_t bytes = (uint32_t)(mn * 4);
   const BufRsrc Xr = buf_rsrc(X, bytes), S1r = buf_rsrc(S1, bytes), Ebr = buf_rsrc(Ebar, bytes);
   const BufRsrc S2r = buf_rsrc(OPT == 1 ? S2 : S1, bytes);
+  const float inv_n = 1.0f / (float)N;
 #pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const uint32_t o = ob[tm][v];
-      const float gh = tile.acc[tm][0][v];
-      float xv = buf_ld(Xr, o);
-      if (OPT == 2) {
-        xv = xv - op.lr * gh;
-      } else {
-        float s1 = buf_ld(S1r, o);
-        if (OPT == 0) {
-          s1 = op.beta1 * s1 + (1.0f - op.beta1) * gh;
-          xv = xv - op.lr * s1;
-        } else {
-          float s2 = buf_ld(S2r, o);
-          s1 = op.beta1 * s1 + (1.0f - op.beta1) * gh;
-          s2 = op.beta2 * s2 + (1.0f - op.beta2) * gh * gh;
-          xv = xv - op.lr * s1 / (sqrtf(s2) + op.eps);
-          buf_st(S2r, o, s2);
-        }
-        buf_st(S1r, o, s1);
-      }
-      const float eb = esum[tm][v] / (float)(N > 0 ? N : 1);
-      buf_st(Ebr, o, op.ef ? eb : 0.0f);
-      buf_st(Xr, o, xv);
+  for (int v = 0; v < 16; ++v) {
+    const uint32_t o = ob[v];
+    const float gh = gsum[v] * inv_n;
+    float xv = buf_ld(Xr, o);
+    float s1 = buf_ld(S1r, o);
+    if (OPT == 0) {
+      s1 = op.beta1 * s1 + (1.0f - op.beta1) * gh;
+      xv = xv - op.lr * s1;
+    } else {
+      float s2 = buf_ld(S2r, o);
+      s1 = op.beta1 * s1 + (1.0f - op.beta1) * gh;
+      s2 = op.beta2 * s2 + (1.0f - op.beta2) * gh * gh;
+      xv = xv - op.lr * s1 / (sqrtf(s2) + op.eps);
+      buf_st(S2r, o, s2);
     }
+    buf_st(S1r, o, s1);
+    buf_st(Ebr, o, esum[v] * inv_n);
+    buf_st(Xr, o, xv);
+  }
 }
-// (the stored residuals' running sum for Ebar takes 32 registers per lane
-// beside the rest, so three waves per SIMD instead of four, without spills)
-template <int OPT, bool RIGHT, int ROWS, int RO_COLS>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
-k_resid_opt(const float* __restrict__ G, float* __restrict__ E, float* __restrict__ Ebar,
-            const float* __restrict__ Mbar, const float* __restrict__ Q, const float* __restrict__ Rbar,
-            const float* __restrict__ Ut,
-            const int* __restrict__ J,
-            float* __restrict__ X, float* __restrict__ S1, float* __restrict__ S2, int64_t m,
-            int64_t n, int64_t d, int64_t D, int r, int N, OptParams op) {
-  resid_opt_at<OPT, RIGHT, ROWS, RO_COLS, float>(G, E, Ebar, Mbar, Q, Rbar, Ut, J, X, S1, S2, m, n, d, D, r, N,
-                                                 op, blockIdx.x, blockIdx.y);
-}
-// the same with bf16 storage
-template <int OPT, bool RIGHT, int ROWS, int RO_COLS>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
-k_resid_opt16(const bf16_t* __restrict__ G, bf16_t* __restrict__ E, float* __restrict__ Ebar,
-              const float* __restrict__ Mbar, const float* __restrict__ Q, const float* __restrict__ Rbar,
-              const float* __restrict__ Ut, const int* __restrict__ J, float* __restrict__ X,
-              float* __restrict__ S1, float* __restrict__ S2, int64_t m, int64_t n, int64_t d, int64_t D, int r,
-              int N, OptParams op) {
-  resid_opt_at<OPT, RIGHT, ROWS, RO_COLS, bf16_t>(G, E, Ebar, Mbar, Q, Rbar, Ut, J, X, S1, S2, m, n, d, D, r, N,
-                                                  op, blockIdx.x, blockIdx.y);
+// registers: 8 KS for P, so two waves per SIMD up to rank 256
+template <int OPT, bool RIGHT, int KS, class ST>
+__global__ void __launch_bounds__(256, KS <= 4 ? 3 : 2)
+k_resid_packed(const ST* __restrict__ G, ST* __restrict__ E, float* __restrict__ Ebar, const u32x4* __restrict__ Qf,
+               const int* __restrict__ Qe, const u32x4* __restrict__ Pf, float* __restrict__ X,
+               float* __restrict__ S1, float* __restrict__ S2, int64_t m, int64_t n, int N, OptParams op) {
+  resid_packed_at<OPT, RIGHT, KS, ST>(G, E, Ebar, Qf, Qe, Pf, X, S1, S2, m, n, N, op, blockIdx.x, blockIdx.y);
 }
 
-// S5 + S7 + S8 above rank 128, the workers side by side: one 64 x 64 output
+// Without error feedback (E^(i) and Ebar stay zero): Ghat = P Rbar and the
+// optimizer, over 64 x 64 tiles of the m x n layout.  OPT 2: the plain step
+// of GaLore, whose Rbar holds its step direction.
+template <int OPT, bool RIGHT>
+__global__ void __launch_bounds__(256)
+k_recon_opt(float* __restrict__ Ebar, const float* __restrict__ Rbar, const float* __restrict__ Ut,
+            const int* __restrict__ J, float* __restrict__ X, float* __restrict__ S1, float* __restrict__ S2,
+            int64_t m, int64_t n, int64_t d, int64_t D, int r, OptParams op) {
+  constexpr int ROWS = 64, COLS = 64;
+  using T = MfmaTile<ROWS, COLS, 2, 2>;
+  static_assert(T::TM == 1 && T::TN == 1, "one block per wave");
+  __shared__ __align__(16) float smem[T::LDS_FLOATS];
+  const int c0 = blockIdx.x * COLS, r0 = blockIdx.y * ROWS;
+  T tile;
+  if (!RIGHT) {
+    // rows a < d, columns b < D: C[a][b] = sum_k Ut[J[k]][a] Rbar[k][b]
+    LoadR<ROWS, 32, false, true> la(Ut, nullptr, d, r0, (int)d, r, J);
+    LoadR<COLS, 32, false> lb(Rbar, nullptr, D, c0, (int)D, r);
+    tile.run(la, lb, r, smem);
+  } else {
+    // rows b < D, columns a < d: C[b][a] = sum_k Rbar[k][b] Ut[J[k]][a]
+    LoadR<ROWS, 32, false> la(Rbar, nullptr, D, r0, (int)D, r);
+    LoadR<COLS, 32, false, true> lb(Ut, nullptr, d, c0, (int)d, r, J);
+    tile.run(la, lb, r, smem);
+  }
+  const uint32_t bytes = (uint32_t)(m * n * 4);
+  const BufRsrc Xr = buf_rsrc(X, bytes), S1r = buf_rsrc(S1, bytes), Ebr = buf_rsrc(Ebar, bytes);
+  const BufRsrc S2r = buf_rsrc(OPT == 1 ? S2 : S1, bytes);
+  const int64_t cc = c0 + tile.col(0);
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int64_t row = r0 + tile.row(0, v);
+    const uint32_t o = (cc < n && row < m) ? (uint32_t)((row * n + cc) * 4) : kBufNone;
+    const float gh = tile.acc[0][0][v];
+    float xv = buf_ld(Xr, o);
+    if (OPT == 2) {
+      xv = xv - op.lr * gh;
+    } else {
+      float s1 = buf_ld(S1r, o);
+      s1 = op.beta1 * s1 + (1.0f - op.beta1) * gh;
+      if (OPT == 0) {
+        xv = xv - op.lr * s1;
+      } else {
+        float s2 = buf_ld(S2r, o);
+        s2 = op.beta2 * s2 + (1.0f - op.beta2) * gh * gh;
+        xv = xv - op.lr * s1 / (sqrtf(s2) + op.eps);
+        buf_st(S2r, o, s2);
+      }
+      buf_st(S1r, o, s1);
+    }
+    buf_st(Ebr, o, 0.0f);
+    buf_st(Xr, o, xv);
+  }
+}
+
+// S5 + S7 + S8 above rank 256, the workers side by side: one 64 x 64 output
 // tile of the m x n layout per workgroup (a 32 x 32 MFMA block per wave).
 // Each k-slice of P (gathered rows of U^T) is staged once and multiplied
 // with the slices of Q^(w) of up to kNW workers into one accumulator per
@@ -825,9 +1079,28 @@ template <class ST>
 static hipError_t launch_resid_opt_st(const MatView& v, const OptParams& o, hipStream_t s) {
   const ST* G = static_cast<const ST*>(v.G);
   ST* E = static_cast<ST*>(v.E);
-  if (v.r > kResidWideRank && o.ef) {
-    // MSGD / Adam with error feedback above rank 128 (GaLore runs without
-    // error feedback): one fused pass with the workers side by side
+  dim3 grid((unsigned)((v.n + 63) / 64), (unsigned)((v.m + 63) / 64));
+  if (v.r <= kPackRank && o.ef) {
+#define GLR_RP(OPT, R, KS)                                                                                   \
+  hipLaunchKernelGGL((k_resid_packed<OPT, R, KS, ST>), grid, dim3(kThreads), 0, s, G, E, v.Ebar,             \
+                     (const u32x4*)v.Qf, v.Qe, (const u32x4*)v.Pf, v.X, v.S1, v.S2, v.m, v.n, v.N, o)
+#define GLR_RP2(OPT, R)                       \
+  switch (pack_steps(v.r)) {                  \
+    case 1: GLR_RP(OPT, R, 1); break;         \
+    case 2: GLR_RP(OPT, R, 2); break;         \
+    case 4: GLR_RP(OPT, R, 4); break;         \
+    case 8: GLR_RP(OPT, R, 8); break;         \
+    default: GLR_RP(OPT, R, 16);              \
+  }
+    if (o.opt == 0)      { if (v.right) { GLR_RP2(0, true) } else { GLR_RP2(0, false) } }
+    else if (o.opt == 1) { if (v.right) { GLR_RP2(1, true) } else { GLR_RP2(1, false) } }
+    else return hipErrorInvalidValue;
+#undef GLR_RP2
+#undef GLR_RP
+    return hipGetLastError();
+  }
+  if (o.ef) {
+    // above rank 256: one fused pass with the workers side by side
     const bool multi = v.N > kNW;
     const unsigned rt = (unsigned)((v.m + kNWTile - 1) / kNWTile), ct = (unsigned)((v.n + kNWTile - 1) / kNWTile);
     const int rows_fast = ct <= 65535u ? 1 : 0;
@@ -854,18 +1127,9 @@ static hipError_t launch_resid_opt_st(const MatView& v, const OptParams& o, hipS
 #undef GLR_RW
     return hipGetLastError();
   }
-  const int nfused = o.ef ? v.N : 0;   // workers whose residual k_resid_opt updates
-  constexpr int rows = 64, cols = 64;
-  dim3 grid((unsigned)((v.n + cols - 1) / cols), (unsigned)((v.m + rows - 1) / rows));
-#define GLR_RO(OPT, R)                                                                                     \
-  do {                                                                                                     \
-    if constexpr (sizeof(ST) == 2)                                                                         \
-      hipLaunchKernelGGL((k_resid_opt16<OPT, R, rows, cols>), grid, dim3(kThreads), 0, s, G, E, v.Ebar,    \
-                         v.Mbar, v.Q, v.Rbar, v.Ut, v.J, v.X, v.S1, v.S2, v.m, v.n, v.d, v.D, v.r, nfused, o); \
-    else                                                                                                   \
-      hipLaunchKernelGGL((k_resid_opt<OPT, R, rows, cols>), grid, dim3(kThreads), 0, s, G, E, v.Ebar,      \
-                         v.Mbar, v.Q, v.Rbar, v.Ut, v.J, v.X, v.S1, v.S2, v.m, v.n, v.d, v.D, v.r, nfused, o); \
-  } while (0)
+#define GLR_RO(OPT, R)                                                                                            \
+  hipLaunchKernelGGL((k_recon_opt<OPT, R>), grid, dim3(kThreads), 0, s, v.Ebar, v.Rbar, v.Ut, v.J, v.X, v.S1, v.S2, \
+                     v.m, v.n, v.d, v.D, v.r, o)
   if (o.opt == 0)      { if (v.right) GLR_RO(0, true); else GLR_RO(0, false); }
   else if (o.opt == 1) { if (v.right) GLR_RO(1, true); else GLR_RO(1, false); }
   else if (sizeof(ST) == 2) return hipErrorInvalidValue;   // GaLore runs on fp32 storage only
@@ -1018,37 +1282,29 @@ k_g_proj(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num
   const int gx = (int)((v.D + BN - 1) / BN), gy = (v.r + BM - 1) / BM;
   const int local = blockIdx.x - first[m], rest = local / gx;
   proj_at<BM, BN, WM, WN, RIGHT, FLUSH, ST>(static_cast<const ST*>(v.G), static_cast<const ST*>(v.E), v.Ut, v.J,
-                                            g.splits > 1 ? v.Qpart : v.Q, v.d, v.D, v.r, v.N, g.kslice, local % gx,
+                                            v.Qpart, v.d, v.D, v.r, v.N, g.kslice, local % gx,
                                             rest % gy, rest / gy);
 }
 
-__global__ void k_g_rbar(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num) {
+template <int KS>
+__global__ void __launch_bounds__(kThreads)
+k_g_pack_waves(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num) {
   const int m = group_find(first, num, blockIdx.x);
   const GroupMat& g = gm[m];
   const MatView& v = g.v;
-  proj_reduce_at(v.Qpart, g.splits, v.N, (int64_t)v.r * v.D, v.Q, v.Rbar, blockIdx.x - first[m],
-                 first[m + 1] - first[m]);
+  pack_waves<KS>(v.Qpart, g.splits, v.N, v.r, v.d, v.D, v.Ut, v.J, (u32x4*)v.Qf, v.Qe, (u32x4*)v.Pf, v.Rbar,
+                 blockIdx.x - first[m]);
 }
 
-template <int OPT, bool RIGHT, class ST>
-__device__ __forceinline__ void g_resid_opt_at(const GroupMat* __restrict__ gm, const int* __restrict__ first,
-                                               int num, const OptParams& op) {
+template <int OPT, bool RIGHT, int KS, class ST>
+__global__ void __launch_bounds__(256, KS <= 4 ? 3 : 2)
+k_g_resid(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num, OptParams op) {
   const int m = group_find(first, num, blockIdx.x);
   const MatView& v = gm[m].v;
   const int local = blockIdx.x - first[m], gx = (int)((v.n + 63) / 64);
-  resid_opt_at<OPT, RIGHT, 64, 64, ST>(static_cast<const ST*>(v.G), static_cast<ST*>(v.E), v.Ebar, v.Mbar, v.Q,
-                                       v.Rbar, v.Ut, v.J, v.X, v.S1, v.S2, v.m, v.n, v.d, v.D, v.r, v.N, op,
-                                       local % gx, local / gx);
-}
-template <int OPT, bool RIGHT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
-k_g_resid_opt(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num, OptParams op) {
-  g_resid_opt_at<OPT, RIGHT, float>(gm, first, num, op);
-}
-template <int OPT, bool RIGHT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
-k_g_resid_opt16(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num, OptParams op) {
-  g_resid_opt_at<OPT, RIGHT, bf16_t>(gm, first, num, op);
+  resid_packed_at<OPT, RIGHT, KS, ST>(static_cast<const ST*>(v.G), static_cast<ST*>(v.E), v.Ebar, (const u32x4*)v.Qf,
+                                      v.Qe, (const u32x4*)v.Pf, v.X, v.S1, v.S2, v.m, v.n, v.N, op, local % gx,
+                                      local / gx);
 }
 
 void group_fill(GroupMat& g, int (&blocks)[kGrpKinds]) {
@@ -1064,7 +1320,7 @@ void group_fill(GroupMat& g, int (&blocks)[kGrpKinds]) {
   GLR_PROJ_TIERS(GLR_PROJ_BLOCKS);
 #undef GLR_PROJ_BLOCKS
   blocks[kGrpProj] = proj;
-  blocks[kGrpRbar] = grid_for((int64_t)r * v.D);
+  blocks[kGrpRbar] = pack_blocks(v.d, v.D, v.N, r);
   blocks[kGrpResid] = (int)(((v.n + 63) / 64) * ((v.m + 63) / 64));
 }
 
@@ -1109,18 +1365,27 @@ static hipError_t launch_group_select_st(const GroupPlan& gp, bool check_finite,
   } while (0)
   GLR_PROJ_TIERS(GLR_GPROJ);
 #undef GLR_GPROJ
-  hipLaunchKernelGGL(k_g_rbar, grid(kGrpRbar), dim3(kThreads), 0, s, gp.gm, table(kGrpRbar), num);
-#define GLR_GRO(OPT, R)                                                                                     \
-  do {                                                                                                      \
-    if constexpr (sizeof(ST) == 2)                                                                          \
-      hipLaunchKernelGGL((k_g_resid_opt16<OPT, R>), grid(kGrpResid), dim3(kThreads), 0, s, gp.gm,           \
-                         table(kGrpResid), num, o);                                                         \
-    else                                                                                                    \
-      hipLaunchKernelGGL((k_g_resid_opt<OPT, R>), grid(kGrpResid), dim3(kThreads), 0, s, gp.gm,             \
-                         table(kGrpResid), num, o);                                                         \
-  } while (0)
-  if (o.opt == 0) { if (right) GLR_GRO(0, true); else GLR_GRO(0, false); }
-  else            { if (right) GLR_GRO(1, true); else GLR_GRO(1, false); }
+  switch (pack_steps(r)) {
+    case 1: hipLaunchKernelGGL(k_g_pack_waves<1>, grid(kGrpRbar), dim3(kThreads), 0, s, gp.gm, table(kGrpRbar), num); break;
+    case 2: hipLaunchKernelGGL(k_g_pack_waves<2>, grid(kGrpRbar), dim3(kThreads), 0, s, gp.gm, table(kGrpRbar), num); break;
+    case 4: hipLaunchKernelGGL(k_g_pack_waves<4>, grid(kGrpRbar), dim3(kThreads), 0, s, gp.gm, table(kGrpRbar), num); break;
+    default: hipLaunchKernelGGL(k_g_pack_waves<8>, grid(kGrpRbar), dim3(kThreads), 0, s, gp.gm, table(kGrpRbar), num);
+  }
+  static_assert(kGroupMaxRank <= 16 * kPackWaveSteps, "a variant for every rank");
+#define GLR_GRO1(OPT, R, KS)                                                                             \
+  hipLaunchKernelGGL((k_g_resid<OPT, R, KS, ST>), grid(kGrpResid), dim3(kThreads), 0, s, gp.gm, table(kGrpResid), \
+                     num, o)
+#define GLR_GRO(OPT, R)                    \
+  switch (pack_steps(r)) {                 \
+    case 1: GLR_GRO1(OPT, R, 1); break;    \
+    case 2: GLR_GRO1(OPT, R, 2); break;    \
+    case 4: GLR_GRO1(OPT, R, 4); break;    \
+    default: GLR_GRO1(OPT, R, 8);          \
+  }
+  static_assert(kGroupMaxRank <= 128, "the grouped residual's largest variant");
+  if (o.opt == 0) { if (right) { GLR_GRO(0, true) } else { GLR_GRO(0, false) } }
+  else            { if (right) { GLR_GRO(1, true) } else { GLR_GRO(1, false) } }
+#undef GLR_GRO1
 #undef GLR_GRO
   return hipGetLastError();
 }
