@@ -46,9 +46,9 @@
  * run in shared launches on `stream` itself, with one convergence read per
  * sweep for all matrices; each matrix still computes exactly what it computes
  * alone.  GLR_JAC_JOINT=0, read by glr_create, turns this off.  Likewise a
- * selection step of several matrices that all have d <= 2048, the same side
- * (m > n or not) and the same rank r < d, r <= 128, launches each of its
- * kernels once for all matrices on `stream`, after uploading that step's table
+ * selection step of several matrices that all have d <= 2048 and the same rank
+ * r < d, r <= 128, launches each of its kernels once for all matrices of a
+ * side (m > n or not) on `stream` or one of the handle's streams, after uploading that step's table
  * of matrix views from pinned host memory the handle owns; GLR_GROUPED=0 turns
  * this off.
  * While profiling is enabled the matrices run in order on `stream`.  The

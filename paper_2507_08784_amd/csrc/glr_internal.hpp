@@ -187,6 +187,8 @@ __host__ __device__ inline int pack_steps(int r) {
   while (16 * k < r) k *= 2;
   return k;
 }
+// bytes of a packed value of rank r: three bf16 pieces for one step, else two of fp16
+inline int pack_bytes(int r) { return pack_steps(r) == 1 ? 6 : 4; }
 // largest rank of a grouped selection step
 constexpr int kGroupMaxRank = 128;
 
@@ -201,7 +203,7 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_eye(float* Ut, int64_t d, hipStream_t s);
 hipError_t launch_ef_mean(const MatView& v, bool check_finite, hipStream_t s);
 hipError_t launch_sel_scores(const MatView& v, bool approx, bool bf16, uint64_t seed, int64_t t, hipStream_t s);
-hipError_t launch_topr(const MatView& v, hipStream_t s);
+hipError_t launch_topr(const MatView& v, bool approx, hipStream_t s);
 hipError_t launch_iota_J(const MatView& v, hipStream_t s);
 hipError_t launch_proj(const MatView& v, hipStream_t s);
 // Rbar, and Q^(i): as fp32, or packed with P for the split residual pass
@@ -219,7 +221,7 @@ struct GroupMat {
   int splits, kslice;
 };
 // the kernels of a grouped selection step, each one launch over all matrices
-enum { kGrpEfMean = 0, kGrpSelScores, kGrpSelFinish, kGrpProj, kGrpRbar, kGrpResid, kGrpKinds };
+enum { kGrpEfMean = 0, kGrpSelScores, kGrpProj, kGrpRbar, kGrpResid, kGrpKinds };
 struct GroupPlan {
   const GroupMat* gm = nullptr;   // num entries
   const int* first = nullptr;     // kGrpKinds tables of num + 1 first blocks
@@ -227,15 +229,13 @@ struct GroupPlan {
   bool right = false;             // every matrix of the group has the same side, rank and kernel variants
   bool st16 = false;              // storage type of G and E (the handle's)
   int r = 0;
-  size_t topr_lds = 0;            // the largest matrix's top-r sort keys
   int total[kGrpKinds] = {};
 };
 // the slicing of one matrix's projection and its block count in every grouped launch
 void group_fill(GroupMat& g, int (&blocks)[kGrpKinds]);
-size_t topr_lds_bytes(int64_t d);
 // one selection step of every matrix of the plan: M-bar, the Approx-Top-r (or
 // exact) scores and their top r, the projection and its mean, the residual
-// and the optimizer update, seven launches in all (part 1: M-bar only; part
+// and the optimizer update, six launches in all (part 1: M-bar only; part
 // 2: the launches after it; 0: all)
 hipError_t launch_group_select(const GroupPlan& gp, bool check_finite, bool approx, bool bf16, uint64_t seed,
                                int64_t t, const OptParams& o, int part, hipStream_t s);

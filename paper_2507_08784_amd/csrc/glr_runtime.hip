@@ -186,11 +186,11 @@ WsLayout ws_layout(const glr_config* c, int first, int last) {
     const int ps = proj_splits(x.d, x.D, x.r, c->num_workers);
     mx(mx_Qp, (uint64_t)ps * c->num_workers * (uint64_t)x.r * (uint64_t)x.D);
     if (packed_resid(c, x)) {
-      // two 16-bit pieces a value, padded to whole 32 x 16 fragments
+      // 16-bit pieces, padded to whole 32 x 16 fragments
       const uint64_t k16 = 16 * (uint64_t)pack_steps(x.r), D32 = (uint64_t)(x.D + 31) / 32 * 32;
-      mx(p_Q, c->num_workers * D32 * k16 * 4);
+      mx(p_Q, c->num_workers * D32 * k16 * pack_bytes(x.r));
       mx(p_Qe, c->num_workers * D32 * 4);
-      mx(p_P, (uint64_t)(x.d + 31) / 32 * 32 * k16 * 4);
+      mx(p_P, (uint64_t)(x.d + 31) / 32 * 32 * k16 * pack_bytes(x.r));
     } else {
       mx(mx_Q, (uint64_t)c->num_workers * (uint64_t)x.r * (uint64_t)x.D);
     }
@@ -231,13 +231,18 @@ WsLayout ws_layout(const glr_config* c, int first, int last) {
     return at;
   };
   w.off_Mbar = take(mx_mn * 4);
+  w.off_lam = take(mx_lam * 4);
+  w.off_amax = take((uint64_t)ef_mean_blocks((int64_t)mx_mn) * 4);
+  // the projection's outputs share their place with the scratch of the
+  // refresh, which is done with it before the projection starts
+  const uint64_t shared = o;
   w.off_Q = take(mx_Q * 4);
   w.off_Qpart = take(mx_Qp * 4);
   w.off_Qf = take(p_Q);
   w.off_Qe = take(p_Qe);
   w.off_Pf = take(p_P);
-  w.off_lam = take(mx_lam * 4);
-  w.off_amax = take((uint64_t)ef_mean_blocks((int64_t)mx_mn) * 4);
+  const uint64_t proj_end = o;
+  o = shared;
   w.off_W = take(mx_dD * 4);
   w.off_Utw = take(mx_dd * 4);
   w.off_gram = take(mx_gram * 8);
@@ -275,7 +280,7 @@ WsLayout ws_layout(const glr_config* c, int first, int last) {
   w.off_rctl = take(sizeof(JacCtl));
   w.off_rsigw = take(s_Kd ? 2 * kMaxSubK * 4 : 4);
   w.off_rperm = take(s_Kd ? 2 * kMaxSubK * 4 : 4);
-  w.bytes = o;
+  w.bytes = o > proj_end ? o : proj_end;
   return w;
 }
 
@@ -370,6 +375,7 @@ struct glr_handle {
   JointPlan jp;
   bool grouped = false;                // selection steps launch each kernel once for all matrices
   std::vector<int> gfirst;
+  std::vector<int> gorder;             // matrix of each entry of the grouped tables: left-sided ones first
   GroupPlan gp[kMaxLanes];             // the parts of a grouped selection step (gparts of them)
   int gparts = 0;
   hipEvent_t gev_mean[kMaxLanes] = {}; // end of each part's M-bar
@@ -738,7 +744,7 @@ glr_status step_one(glr_handle* h, int mat, float* X, const void* G, int64_t t, 
                                    s));
     }
     ProfScope p(h, s, GLR_PROF_TOPR);
-    GLR_HIP(h, launch_topr(v, s));
+    GLR_HIP(h, launch_topr(v, c.select != GLR_SELECT_EXACT, s));
   }
   return step_tail(h, v, refresh, s);
 }
@@ -904,7 +910,8 @@ glr_status step_grouped(glr_handle* h, float* const* X, const void* const* G, in
   GroupMat* g = h->gring + (size_t)slot * num;
   int blocks[kGrpKinds];
   for (int i = 0; i < num; ++i) {
-    g[i].v = view_of(h, i, X[i], G[i], 0);
+    const int l = h->gorder[(size_t)i];
+    g[i].v = view_of(h, l, X[l], G[l], 0);
     group_fill(g[i], blocks);
   }
   GLR_HIP(h, hipMemcpyAsync((void*)h->gp[0].gm, g, (size_t)num * sizeof(GroupMat), hipMemcpyHostToDevice, s));
@@ -921,19 +928,21 @@ glr_status step_grouped(glr_handle* h, float* const* X, const void* const* G, in
   // (M-bar, projection, residual) and the MFMA-bound (scores) kinds, so the
   // staggered parts overlap the two
   for (int k = 0; k < h->gparts; ++k) {
-    hipStream_t ks = k == 0 ? s : h->lane_s[k];
-    if (k > 0) GLR_HIP(h, hipStreamWaitEvent(ks, h->gev_mean[k - 1], 0));
+    const bool own = k > 0 && h->lanes > 1;   // on a stream of its own
+    hipStream_t ks = own ? h->lane_s[k] : s;
+    if (own) GLR_HIP(h, hipStreamWaitEvent(ks, h->gev_mean[k - 1], 0));
     GLR_HIP(h, launch_group_select(h->gp[k], fin, approx, b16, c.seed, t, op, 1, ks));
     if (k + 1 < h->gparts) GLR_HIP(h, hipEventRecord(h->gev_mean[k], ks));
     GLR_HIP(h, launch_group_select(h->gp[k], fin, approx, b16, c.seed, t, op, 2, ks));
-    if (k > 0) GLR_HIP(h, hipEventRecord(h->ev_join[k], ks));
+    if (own) GLR_HIP(h, hipEventRecord(h->ev_join[k], ks));
   }
-  for (int k = 1; k < h->gparts; ++k) GLR_HIP(h, hipStreamWaitEvent(s, h->ev_join[k], 0));
+  for (int k = 1; k < h->gparts && h->lanes > 1; ++k) GLR_HIP(h, hipStreamWaitEvent(s, h->ev_join[k], 0));
   return GLR_OK;
 }
 
-// selection steps are grouped when every matrix has d <= 2048, a rank below d
-// and at most 128, and the same side (so the same kernel variants)
+// selection steps are grouped when every matrix has d <= 2048 and the same
+// rank, below d and at most 128 (so the same kernel variants but for the side:
+// the matrices of either side are parts of their own)
 bool group_allowed(const glr_handle* h) {
   const glr_config& c = h->cfg;
   if (c.num_mats < 2 || c.tau == 1 || h->static_ws || h->lazy || !h->ef || c.opt == GLR_GALORE_ADAM) return false;
@@ -942,8 +951,7 @@ bool group_allowed(const glr_handle* h) {
   const glr_mat_layout& L0 = h->lay[0];
   for (int i = 0; i < c.num_mats; ++i) {
     const glr_mat_layout& L = h->lay[(size_t)i];
-    if (L.d > kJointMaxDim || L.r >= L.d || L.r > kGroupMaxRank || L.r != L0.r || L.right != L0.right)
-      return false;
+    if (L.d > kJointMaxDim || L.r >= L.d || L.r > kGroupMaxRank || L.r != L0.r) return false;
   }
   return true;
 }
@@ -951,15 +959,24 @@ bool group_allowed(const glr_handle* h) {
 // block tables of the grouped launches, the pinned ring and its events
 hipError_t group_setup(glr_handle* h, hipStream_t s) {
   const int num = h->cfg.num_mats;
-  // parts of about equal bytes, one per lane stream (two unless
-  // GLR_GROUP_PARTS asks otherwise; at most one part per two matrices)
-  int parts = std::min(h->lanes, 2);
-  if (const char* e = getenv("GLR_GROUP_PARTS")) parts = std::min(h->lanes, std::max(1, atoi(e)));
-  if (const char* e = getenv("GLR_GROUP_SPLIT"))
-    if (atoi(e) == 0) parts = 1;
-  parts = std::max(1, std::min(parts, num / 2));
+  // the matrices of one side together (a launch has one side)
+  h->gorder.clear();
+  for (int side = 0; side < 2; ++side)
+    for (int i = 0; i < num; ++i)
+      if (h->lay[(size_t)i].right == side) h->gorder.push_back(i);
+  const int nleft = (int)std::count_if(h->lay.begin(), h->lay.end(), [](const glr_mat_layout& L) { return !L.right; });
   std::vector<int> cut(1, 0);
-  {
+  if (nleft > 0 && nleft < num) {
+    cut.push_back(nleft);   // both sides: a part each
+    cut.push_back(num);
+  } else {
+    // parts of about equal bytes, one per lane stream (two unless
+    // GLR_GROUP_PARTS asks otherwise; at most one part per two matrices)
+    int parts = std::min(h->lanes, 2);
+    if (const char* e = getenv("GLR_GROUP_PARTS")) parts = std::min(h->lanes, std::max(1, atoi(e)));
+    if (const char* e = getenv("GLR_GROUP_SPLIT"))
+      if (atoi(e) == 0) parts = 1;
+    parts = std::max(1, std::min(parts, num / 2));
     double tot = 0.0, acc = 0.0;
     for (int i = 0; i < num; ++i) tot += (double)h->lay[(size_t)i].m * (double)h->lay[(size_t)i].n;
     for (int i = 0; i < num && (int)cut.size() < parts; ++i) {
@@ -971,14 +988,12 @@ hipError_t group_setup(glr_handle* h, hipStream_t s) {
     cut.push_back(num);
   }
   std::vector<int> blocks((size_t)num * kGrpKinds);
-  size_t topr_lds = 0;
   for (int i = 0; i < num; ++i) {
     GroupMat g;
-    g.v = view_of(h, i, nullptr, nullptr, 0);
+    g.v = view_of(h, h->gorder[(size_t)i], nullptr, nullptr, 0);
     int b[kGrpKinds];
     group_fill(g, b);
     for (int k = 0; k < kGrpKinds; ++k) blocks[(size_t)i * kGrpKinds + k] = b[k];
-    topr_lds = std::max(topr_lds, topr_lds_bytes(g.v.d));
   }
   const GroupMat* gm = (const GroupMat*)(h->work + h->ws.off_gmats);
   const int* first = (const int*)(h->work + h->ws.off_gfirst);
@@ -987,10 +1002,9 @@ hipError_t group_setup(glr_handle* h, hipStream_t s) {
   auto plan = [&](GroupPlan& gp, int a, int b) -> hipError_t {
     const int n = b - a;
     gp.num = n;
-    gp.right = h->lay[0].right != 0;
+    gp.right = h->lay[(size_t)h->gorder[(size_t)a]].right != 0;
     gp.r = h->lay[0].r;
     gp.st16 = (h->cfg.flags & GLR_STORE_BF16) != 0;
-    gp.topr_lds = topr_lds;
     gp.gm = gm + a;
     gp.first = first + h->gfirst.size();
     for (int k = 0; k < kGrpKinds; ++k) {

@@ -198,20 +198,6 @@ k_sel_scores(const float* __restrict__ Mbar, const float* __restrict__ Ut, int64
   sel_scores_at<RIGHT, APPROX, BF16>(Mbar, Ut, d, D, part, mat, tstep, key0, key1, amax, blockIdx.x, blockIdx.y);
 }
 
-// lambdabar / scores from the tile partials, summed in a fixed order
-__device__ __forceinline__ void sel_finish_at(const float* __restrict__ part, int ntiles, int64_t d, int approx,
-                                              float* __restrict__ score, int64_t bx) {
-  int64_t j = bx * (int64_t)blockDim.x + threadIdx.x;
-  if (j >= d) return;
-  float s = 0.f;
-  for (int t = 0; t < ntiles; ++t) s += part[(int64_t)t * d + j];
-  score[j] = approx ? s * s : s;
-}
-__global__ void k_sel_finish(const float* __restrict__ part, int ntiles, int64_t d, int approx,
-                             float* __restrict__ score) {
-  sel_finish_at(part, ntiles, d, approx, score, blockIdx.x);
-}
-
 hipError_t launch_sel_scores(const MatView& v, bool approx, bool bf16, uint64_t seed, int64_t t, hipStream_t s) {
   if (bf16 && !approx) return hipErrorInvalidValue;
   dim3 grid((unsigned)((v.d + SEL_BN - 1) / SEL_BN), (unsigned)((v.D + SEL_BM - 1) / SEL_BM));
@@ -230,89 +216,160 @@ hipError_t launch_sel_scores(const MatView& v, bool approx, bool bf16, uint64_t 
     else GLR_SEL(false, false, false);
   }
 #undef GLR_SEL
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_sel_finish, dim3(grid_for(v.d)), dim3(kThreads), 0, s, v.lam_part,
-                     (int)grid.y, v.d, approx ? 1 : 0, v.score);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// argtop_r: descending score, ties to the smaller index; J ascending.
-// One block of 1024 threads; n_pad (power of two) 64-bit keys in LDS.
+// Scores and argtop_r: the tile partials of each column folded in order, then
+// the r largest (descending score, ties to the smaller index; J ascending) by
+// one workgroup of 1024.  It looks for the r-th largest of the
+// order-preserving 32-bit keys by three passes over a histogram in LDS (11, 11
+// and 10 bits; the keys, at most eight a thread, stay in registers), then
+// places the winners by counting.  Bound by latency: 60 us before (a bitonic
+// sort in LDS) + 9 (the fold) at d = 4096, 20 + 4 now; 8.5 + 4.3 before,
+// 7.6 now at d = 128.  The selecting workgroup folds the
+// partials itself up to kToprFold of them (128 KB: what one CU reads in about
+// the time a launch takes); more are folded by a launch over the chip.  (Fold
+// and selection in one launch, the workgroup that ends last selecting: its
+// device-wide fence writes the dirty lines of the L2 back, 31 us at 4096.)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void topr_at(const float* __restrict__ score, int d, int r, int n_pad,
-                                        int* __restrict__ J, unsigned char* dyn) {
-  uint64_t* keys = reinterpret_cast<uint64_t*>(dyn);
-  for (int i = threadIdx.x; i < n_pad; i += blockDim.x) {
+constexpr int kToprThreads = 1024;
+constexpr int64_t kToprFold = 32768;
+constexpr int kToprBins = 2048;
+struct ToprLds {
+  uint32_t hist[kToprBins];
+  uint32_t wave[kToprThreads / 64];
+  uint32_t pick[2];                                 // the bin found, keys above it
+  uint32_t slab[8][kToprThreads / 64];
+};
+// the folded score of column j
+__device__ __forceinline__ float fold_score(const float* __restrict__ part, int ntiles, int d, int approx, int j) {
+  // 32 loads in flight: the partials come from the other XCDs' L2
+  constexpr int B = 32;
+  float s = 0.f;
+  for (int t0 = 0; t0 < ntiles; t0 += B) {
+    float x[B];
+#pragma unroll
+    for (int i = 0; i < B; ++i) x[i] = part[(int64_t)(t0 + i < ntiles ? t0 + i : t0) * d + j];
+#pragma unroll
+    for (int i = 0; i < B; ++i)
+      if (t0 + i < ntiles) s += x[i];
+  }
+  return approx ? s * s : s;
+}
+// folds `part` into `score` when `own`, else reads it
+__device__ __forceinline__ void topr_at(const float* __restrict__ part, int ntiles, bool own, int approx, int d,
+                                        float* __restrict__ score, int r, int* __restrict__ J) {
+  __shared__ ToprLds L;
+  constexpr int MAXQ = 8;                           // d <= 8192
+  const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
+  uint32_t key[MAXQ];
+  const int nq = (d + kToprThreads - 1) / kToprThreads;
+#pragma unroll
+  for (int q = 0; q < MAXQ; ++q) {
+    const int i = tid + q * kToprThreads;
+    key[q] = 0u;
     if (i < d) {
-      const uint32_t hi = ~float_order(score[i]);   // descending score
-      keys[i] = ((uint64_t)hi << 32) | (uint32_t)i; // ties: smaller index first
-    } else {
-      keys[i] = ~0ull;
+      float s;
+      if (own) {
+        s = fold_score(part, ntiles, d, approx, i);
+        score[i] = s;
+      } else {
+        s = score[i];
+      }
+      key[q] = float_order(s);
     }
   }
-  __syncthreads();
-  bitonic_sort(keys, n_pad);
-  // winners' indices to registers, then reuse the buffer for flags and a scan
-  constexpr int MAXW = 8;   // r <= d <= 8192 = 8 * 1024
-  int win[MAXW];
+  uint32_t prefix = 0, want = (uint32_t)r;          // the r-th largest has these upper bits; `want`-th among them
+  int shift = 32;
 #pragma unroll
-  for (int q = 0; q < MAXW; ++q) {
-    const int k = threadIdx.x + q * (int)blockDim.x;
-    win[q] = k < r ? (int)(keys[k] & 0xFFFFFFFFu) : -1;
+  for (int pass = 0; pass < 3; ++pass) {
+    const int bits = pass < 2 ? 11 : 10;
+    const uint32_t mask = pass == 0 ? 0u : ~0u << shift;
+    shift -= bits;
+    L.hist[tid] = 0;
+    L.hist[tid + kToprThreads] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < MAXQ; ++q)
+      if (tid + q * kToprThreads < d && (key[q] & mask) == prefix)
+        atomicAdd(&L.hist[(key[q] >> shift) & ((1u << bits) - 1u)], 1u);
+    __syncthreads();
+    // thread t holds bins b = 2047 - 2 t and b - 1: an inclusive scan from the top
+    const uint32_t h0 = L.hist[kToprBins - 1 - 2 * tid], h1 = L.hist[kToprBins - 2 - 2 * tid];
+    uint32_t sum = h0 + h1;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t x = __shfl_up(sum, o, 64);
+      if (lane >= o) sum += x;
+    }
+    if (lane == 63) L.wave[w] = sum;
+    __syncthreads();
+    uint32_t before = 0;
+    for (int i = 0; i < w; ++i) before += L.wave[i];
+    const uint32_t upto = before + sum, above = upto - h0 - h1;
+    if (above < want && want <= upto) {
+      const bool first = want <= above + h0;
+      L.pick[0] = (uint32_t)(first ? kToprBins - 1 - 2 * tid : kToprBins - 2 - 2 * tid);
+      L.pick[1] = first ? above : above + h0;
+    }
+    __syncthreads();
+    prefix |= L.pick[0] << shift;
+    want -= L.pick[1];
+    __syncthreads();
+  }
+  // every key above `prefix` and the first `want` equal to it, by index
+  uint64_t gt[MAXQ], eq[MAXQ];
+#pragma unroll
+  for (int q = 0; q < MAXQ; ++q) {
+    const bool in = tid + q * kToprThreads < d;
+    gt[q] = __ballot(in && key[q] > prefix);
+    eq[q] = __ballot(in && key[q] == prefix);
+    if (lane == 0 && q < nq) L.slab[q][w] = (uint32_t)__popcll(gt[q]) | ((uint32_t)__popcll(eq[q]) << 16);
   }
   __syncthreads();
-  int* sel = reinterpret_cast<int*>(dyn);
-  int* scan = sel + n_pad;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) sel[i] = 0;
-  __syncthreads();
+  uint32_t ngt = 0, neq = 0;                        // before this wave's first key, in index order
+  for (int q = 0; q < nq; ++q) {
+    for (int i = 0; i < kToprThreads / 64; ++i) {
+      if (i == w) {
+        const uint64_t lower = (1ull << lane) - 1ull;
+        uint64_t g = 0, e = 0;
+        uint32_t k = 0;
 #pragma unroll
-  for (int q = 0; q < MAXW; ++q)
-    if (win[q] >= 0) sel[win[q]] = 1;
-  __syncthreads();
-  const int per = (d + blockDim.x - 1) / blockDim.x;
-  const int lo = threadIdx.x * per;
-  int cnt = 0;
-  for (int i = lo; i < lo + per && i < d; ++i) cnt += sel[i];
-  scan[threadIdx.x] = cnt;
-  __syncthreads();
-  for (int off = 1; off < (int)blockDim.x; off <<= 1) {
-    const int x = (threadIdx.x >= (unsigned)off) ? scan[threadIdx.x - off] : 0;
-    __syncthreads();
-    scan[threadIdx.x] += x;
-    __syncthreads();
+        for (int c = 0; c < MAXQ; ++c)
+          if (c == q) { g = gt[c]; e = eq[c]; k = key[c]; }
+        const uint32_t mg = ngt + (uint32_t)__popcll(g & lower), me = neq + (uint32_t)__popcll(e & lower);
+        const int idx = tid + q * kToprThreads;
+        if (idx < d && (k > prefix || (k == prefix && me < want))) J[mg + (me < want ? me : want)] = idx;
+      }
+      const uint32_t s = L.slab[q][i];
+      ngt += s & 0xFFFFu;
+      neq += s >> 16;
+    }
   }
-  int pos = scan[threadIdx.x] - cnt;
-  for (int i = lo; i < lo + per && i < d; ++i)
-    if (sel[i]) J[pos++] = i;
 }
-__global__ void __launch_bounds__(1024)
-k_topr(const float* __restrict__ score, int d, int r, int n_pad, int* __restrict__ J) {
-  extern __shared__ __align__(16) unsigned char dyn[];
-  topr_at(score, d, r, n_pad, J, dyn);
+__global__ void __launch_bounds__(kToprThreads)
+k_topr(const float* __restrict__ part, int ntiles, int own, int approx, int d, float* __restrict__ score, int r,
+       int* __restrict__ J) {
+  topr_at(part, ntiles, own != 0, approx, d, score, r, J);
+}
+__global__ void k_fold_scores(const float* __restrict__ part, int ntiles, int approx, int d, float* __restrict__ score) {
+  const int j = blockIdx.x * (int)blockDim.x + threadIdx.x;
+  if (j < d) score[j] = fold_score(part, ntiles, d, approx, j);
 }
 
 __global__ void k_iota(int* J, int r) {
   for (int i = threadIdx.x; i < r; i += blockDim.x) J[i] = i;
 }
 
-static int next_pow2(int64_t x) {
-  int p = 1;
-  while (p < x) p <<= 1;
-  return p;
-}
-
-size_t topr_lds_bytes(int64_t d) {
-  const int n_pad = next_pow2(d < 2 ? 2 : d);
-  size_t lds = (size_t)n_pad * 8;
-  if (lds < (size_t)(n_pad + 1024) * 4) lds = (size_t)(n_pad + 1024) * 4;
-  return lds;
-}
-
-hipError_t launch_topr(const MatView& v, hipStream_t s) {
-  const int n_pad = next_pow2(v.d < 2 ? 2 : v.d);
-  hipLaunchKernelGGL(k_topr, dim3(1), dim3(1024), topr_lds_bytes(v.d), s, v.score, (int)v.d, v.r, n_pad, v.J);
+hipError_t launch_topr(const MatView& v, bool approx, hipStream_t s) {
+  const int ntiles = (int)((v.D + SEL_BM - 1) / SEL_BM);
+  const bool own = v.d * ntiles <= kToprFold;
+  if (!own)
+    hipLaunchKernelGGL(k_fold_scores, dim3((unsigned)((v.d + 63) / 64)), dim3(64), 0, s, v.lam_part, ntiles,
+                       approx ? 1 : 0, (int)v.d, v.score);
+  hipLaunchKernelGGL(k_topr, dim3(1), dim3(kToprThreads), 0, s, v.lam_part, ntiles, own ? 1 : 0, approx ? 1 : 0,
+                     (int)v.d, v.score, v.r, v.J);
   return hipGetLastError();
 }
 
@@ -499,19 +556,24 @@ __global__ void k_proj_reduce(const float* __restrict__ part, int splits, int N,
 // 11008 x 4096, rank 128.
 constexpr int kPackThreads = 1024;
 constexpr int kPackWaveSteps = 8;   // largest KS of pack_waves
+constexpr SplitFmt pack_fmt(int KS) { return KS == 1 ? kBf16x3 : kF16x2; }
+// one lane's part of every piece of a fragment
+template <SplitFmt F>
 __device__ __forceinline__ void pack_store(const float (&x)[8], float scale, u32x4* dst) {
-  u32x4 h, l;
+  constexpr int PC = split_pieces(F);
+  u32x4 f[PC];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    uint32_t p[2];
-    split_pair<kF16x2>(x[2 * e], x[2 * e + 1], scale, p);
-    h[e] = p[0];
-    l[e] = p[1];
+    uint32_t p[PC];
+    split_pair<F>(x[2 * e], x[2 * e + 1], scale, p);
+#pragma unroll
+    for (int i = 0; i < PC; ++i) f[i][e] = p[i];
   }
-  dst[0] = h;
-  dst[64] = l;
+#pragma unroll
+  for (int i = 0; i < PC; ++i) dst[64 * i] = f[i];
 }
 // fragment f = blk KS + ks of P, by one wave
+template <SplitFmt F>
 __device__ __forceinline__ void pack_p(int f, int r, int KS, int64_t d, const float* __restrict__ Ut,
                                        const int* __restrict__ J, u32x4* __restrict__ Pf) {
   const int blk = f / KS, ks = f % KS, lane = lane_id();
@@ -523,7 +585,7 @@ __device__ __forceinline__ void pack_p(int f, int r, int KS, int64_t d, const fl
     const int k = 16 * ks + 8 * (lane >> 5) + e;
     x[e] = (k < r && a < d) ? Ut[(int64_t)J[k] * d + a] : 0.f;
   }
-  pack_store(x, ldexpf(1.f, kUnitExp), Pf + (int64_t)f * 128 + lane);
+  pack_store<F>(x, ldexpf(1.f, kUnitExp), Pf + (int64_t)f * (64 * split_pieces(F)) + lane);
 }
 // blocks of kThreads: four fragments columns of Q each, then four fragments of
 // P each, then Rbar
@@ -588,9 +650,12 @@ __device__ __forceinline__ void pack_waves(const float* __restrict__ part, int s
     const int e2 = split_exp(mx);
     if (lane < 32) Qe[(int64_t)item * 32 + lane] = e2;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) pack_store(x[ks], ldexpf(1.f, e2), Qf + ((int64_t)item * KS + ks) * 128 + lane);
+    for (int ks = 0; ks < KS; ++ks)
+      if (KS > 1 || r > 8 || lane < 32)
+        pack_store<pack_fmt(KS)>(x[ks], ldexpf(1.f, e2),
+                                 Qf + ((int64_t)item * KS + ks) * (64 * split_pieces(pack_fmt(KS))) + lane);
   } else if (bid < g.q + g.p) {
-    pack_p((bid - g.q) * 4 + wave_id(), r, KS, d, Ut, J, Pf);
+    pack_p<pack_fmt(KS)>((bid - g.q) * 4 + wave_id(), r, KS, d, Ut, J, Pf);
   } else {
     const int64_t i = (int64_t)(bid - g.q - g.p) * kThreads + threadIdx.x;
     if (i >= rD) return;
@@ -609,7 +674,7 @@ __device__ __forceinline__ void pack_block(const float* __restrict__ part, int s
                                         float* __restrict__ Rbar, int bid, float* dyn) {
   const int tid = threadIdx.x, nqb = (int)((D + 31) / 32);
   if (bid >= nqb) {
-    pack_p((bid - nqb) * (kPackThreads / 64) + (tid >> 6), r, KS, d, Ut, J, Pf);
+    pack_p<kF16x2>((bid - nqb) * (kPackThreads / 64) + (tid >> 6), r, KS, d, Ut, J, Pf);
     return;
   }
   constexpr int KG = kPackThreads / 32;            // rows of k side by side
@@ -647,7 +712,7 @@ __device__ __forceinline__ void pack_block(const float* __restrict__ part, int s
       float x[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = tile[(16 * ks + 8 * (lane >> 5) + e) * 33 + c];
-      pack_store(x, ldexpf(1.f, e2), Qf + (((int64_t)w * nqb + bid) * KS + ks) * 128 + lane);
+      pack_store<kF16x2>(x, ldexpf(1.f, e2), Qf + (((int64_t)w * nqb + bid) * KS + ks) * 128 + lane);
     }
     __syncthreads();
   }
@@ -725,9 +790,9 @@ hipError_t launch_rbar(const MatView& v, bool packed, hipStream_t s) {
 // barrier, so that the waves of a CU drift apart and the loads of some cover
 // the products of others.  MFMA lanes are tile columns, so that a load or
 // store of one accumulator register moves whole 128-byte rows of 32 columns
-// (partial-line writes make the memory side fetch the line first).  h h goes
-// into one accumulator, h l + l h into another: the sums that the large one
-// rounds are a third as many.
+// (partial-line writes make the memory side fetch the line first).  The
+// product of the first pieces goes into one accumulator, the others into
+// another: the sums that the large one rounds are a third as many.
 // Bound by HBM: G and E in, E out, X, the optimizer state and Ebar.  Before
 // (fp32 MFMA on LDS slices, P Rbar as a product of its own): 4096 x 4096,
 // r = 64, N = 8: 496 -> 382 us (5.4 TB/s, the rate of a large copy);
@@ -739,18 +804,19 @@ __device__ __forceinline__ void resid_packed_at(const ST* __restrict__ G, ST* __
                                                 const u32x4* __restrict__ Qf, const int* __restrict__ Qe,
                                                 const u32x4* __restrict__ Pf, float* __restrict__ X,
                                                 float* __restrict__ S1, float* __restrict__ S2, int64_t m, int64_t n,
-                                                int N, const OptParams& op, int bx, int by) {
-  const int lane = lane_id(), wv = wave_id();
+                                                int r, int N, const OptParams& op, int bx, int by) {
+  const int lane = lane_id(), wv = wave_id(), live = r <= 8 ? 32 : 64;
   const int64_t r0 = (int64_t)by * 64 + (wv >> 1) * 32, c0 = (int64_t)bx * 64 + (wv & 1) * 32;
   if (r0 >= m || c0 >= n) return;
   const int64_t mn = m * n;
   const int64_t nqb = ((RIGHT ? m : n) + 31) / 32, qblk = (RIGHT ? r0 : c0) / 32, pblk = (RIGHT ? c0 : r0) / 32;
-  u32x4 ph[KS], pl[KS];
+  constexpr SplitFmt F = pack_fmt(KS);
+  constexpr int PC = split_pieces(F);
+  u32x4 pp[KS][PC];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    ph[ks] = Pf[(pblk * KS + ks) * 128 + lane];
-    pl[ks] = Pf[(pblk * KS + ks) * 128 + 64 + lane];
-  }
+  for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+    for (int i = 0; i < PC; ++i) pp[ks][i] = Pf[((pblk * KS + ks) * PC + i) * 64 + lane];
   // every m x n array is addressed as a buffer (m n 4 < 2^32 bytes): a uniform
   // descriptor and one 32-bit byte offset per element, shared by all of them;
   // elements outside the matrix take kBufNone
@@ -773,23 +839,34 @@ __device__ __forceinline__ void resid_packed_at(const ST* __restrict__ G, ST* __
       gv[v] = buf_lde<ST>(Gi, ob[v]);
       eo[v] = buf_lde<ST>(Ei, ob[v]);
     }
-    const u32x4* q = Qf + ((int64_t)w * nqb + qblk) * KS * 128 + lane;
+    const u32x4* q = Qf + ((int64_t)w * nqb + qblk) * (KS * PC * 64) + lane;
     const int* qe = Qe + ((int64_t)w * nqb + qblk) * 32;
     f32x16 big, small;
 #pragma unroll
     for (int v = 0; v < 16; ++v) big[v] = small[v] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const u32x4 qh = q[ks * 128], ql = q[ks * 128 + 64];
-      if (RIGHT) {
-        small = split_mfma<kF16x2>(qh, pl[ks], small);
-        big = split_mfma<kF16x2>(qh, ph[ks], big);
-        small = split_mfma<kF16x2>(ql, ph[ks], small);
+      u32x4 qq[PC];
+      if constexpr (KS == 1) {
+        // rank 8 or less: the upper lanes hold zeros and load nothing
+#pragma unroll
+        for (int i = 0; i < PC; ++i) qq[i] = u32x4{0u, 0u, 0u, 0u};
+        if (lane < live) {
+#pragma unroll
+          for (int i = 0; i < PC; ++i) qq[i] = q[i * 64];
+        }
       } else {
-        small = split_mfma<kF16x2>(pl[ks], qh, small);
-        big = split_mfma<kF16x2>(ph[ks], qh, big);
-        small = split_mfma<kF16x2>(ph[ks], ql, small);
+#pragma unroll
+        for (int i = 0; i < PC; ++i) qq[i] = q[(ks * PC + i) * 64];
       }
+      // piece i of P times piece s - i of Q, the smallest products first
+#pragma unroll
+      for (int s = PC - 1; s >= 0; --s)
+#pragma unroll
+        for (int i = 0; i <= s; ++i) {
+          f32x16& c = s == 0 ? big : small;
+          c = RIGHT ? split_mfma<F>(qq[s - i], pp[ks][i], c) : split_mfma<F>(pp[ks][i], qq[s - i], c);
+        }
     }
     // columns of Q are tile rows (RIGHT) or this lane's column
     int ex[RIGHT ? 16 : 1];
@@ -805,7 +882,8 @@ __device__ __forceinline__ void resid_packed_at(const ST* __restrict__ G, ST* __
     }
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const float c = ldexpf(big[v] + small[v], -ex[RIGHT ? v : 0] - kUnitExp);
+      const float s = big[v] + small[v];
+      const float c = F == kF16x2 ? ldexpf(s, -ex[RIGHT ? v : 0] - kUnitExp) : s;
       // (G - P Q) + E: G and P Q nearly cancel, E is the small part
       const float e = (gv[v] - c) + eo[v];
       buf_ste<ST>(Ei, ob[v], e);
@@ -843,8 +921,8 @@ template <int OPT, bool RIGHT, int KS, class ST>
 __global__ void __launch_bounds__(256, KS <= 4 ? 3 : 2)
 k_resid_packed(const ST* __restrict__ G, ST* __restrict__ E, float* __restrict__ Ebar, const u32x4* __restrict__ Qf,
                const int* __restrict__ Qe, const u32x4* __restrict__ Pf, float* __restrict__ X,
-               float* __restrict__ S1, float* __restrict__ S2, int64_t m, int64_t n, int N, OptParams op) {
-  resid_packed_at<OPT, RIGHT, KS, ST>(G, E, Ebar, Qf, Qe, Pf, X, S1, S2, m, n, N, op, blockIdx.x, blockIdx.y);
+               float* __restrict__ S1, float* __restrict__ S2, int64_t m, int64_t n, int r, int N, OptParams op) {
+  resid_packed_at<OPT, RIGHT, KS, ST>(G, E, Ebar, Qf, Qe, Pf, X, S1, S2, m, n, r, N, op, blockIdx.x, blockIdx.y);
 }
 
 // Without error feedback (E^(i) and Ebar stay zero): Ghat = P Rbar and the
@@ -1083,7 +1161,7 @@ static hipError_t launch_resid_opt_st(const MatView& v, const OptParams& o, hipS
   if (v.r <= kPackRank && o.ef) {
 #define GLR_RP(OPT, R, KS)                                                                                   \
   hipLaunchKernelGGL((k_resid_packed<OPT, R, KS, ST>), grid, dim3(kThreads), 0, s, G, E, v.Ebar,             \
-                     (const u32x4*)v.Qf, v.Qe, (const u32x4*)v.Pf, v.X, v.S1, v.S2, v.m, v.n, v.N, o)
+                     (const u32x4*)v.Qf, v.Qe, (const u32x4*)v.Pf, v.X, v.S1, v.S2, v.m, v.n, v.r, v.N, o)
 #define GLR_RP2(OPT, R)                       \
   switch (pack_steps(v.r)) {                  \
     case 1: GLR_RP(OPT, R, 1); break;         \
@@ -1229,12 +1307,6 @@ __device__ __forceinline__ int group_find(const int* __restrict__ first, int num
   return lo;
 }
 
-__device__ __forceinline__ int dev_next_pow2(int64_t x) {
-  int p = 1;
-  while (p < x) p <<= 1;
-  return p;
-}
-
 // projection tiles of rank r: BM x BN, WM x WN waves, fp64 flush of the slices
 #define GLR_PROJ_TIERS(X)                                   \
   if (r <= 32) X(32, 128, 1, 4, true);                      \
@@ -1261,16 +1333,11 @@ k_g_sel_scores(const GroupMat* __restrict__ gm, const int* __restrict__ first, i
                                      v.amax, local % gx, local / gx);
 }
 
-__global__ void k_g_sel_finish(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num, int approx) {
-  const int m = group_find(first, num, blockIdx.x);
-  const MatView& v = gm[m].v;
-  sel_finish_at(v.lam_part, (int)((v.D + SEL_BM - 1) / SEL_BM), v.d, approx, v.score, blockIdx.x - first[m]);
-}
-
-__global__ void __launch_bounds__(1024) k_g_topr(const GroupMat* __restrict__ gm) {
-  extern __shared__ __align__(16) unsigned char dyn[];
+// (many matrices: each one's workgroup folds its own partials, whatever their count)
+__global__ void __launch_bounds__(kToprThreads)
+k_g_topr(const GroupMat* __restrict__ gm, int approx) {
   const MatView& v = gm[blockIdx.x].v;
-  topr_at(v.score, (int)v.d, v.r, dev_next_pow2(v.d < 2 ? 2 : v.d), v.J, dyn);
+  topr_at(v.lam_part, (int)((v.D + SEL_BM - 1) / SEL_BM), true, approx, (int)v.d, v.score, v.r, v.J);
 }
 
 template <int BM, int BN, int WM, int WN, bool RIGHT, bool FLUSH, class ST>
@@ -1303,7 +1370,7 @@ k_g_resid(const GroupMat* __restrict__ gm, const int* __restrict__ first, int nu
   const MatView& v = gm[m].v;
   const int local = blockIdx.x - first[m], gx = (int)((v.n + 63) / 64);
   resid_packed_at<OPT, RIGHT, KS, ST>(static_cast<const ST*>(v.G), static_cast<ST*>(v.E), v.Ebar, (const u32x4*)v.Qf,
-                                      v.Qe, (const u32x4*)v.Pf, v.X, v.S1, v.S2, v.m, v.n, v.N, op, local % gx,
+                                      v.Qe, (const u32x4*)v.Pf, v.X, v.S1, v.S2, v.m, v.n, v.r, v.N, op, local % gx,
                                       local / gx);
 }
 
@@ -1314,7 +1381,6 @@ void group_fill(GroupMat& g, int (&blocks)[kGrpKinds]) {
   g.kslice = proj_kslice(v.d, v.D, r, v.N);
   blocks[kGrpEfMean] = ef_mean_blocks(v.m * v.n);
   blocks[kGrpSelScores] = (int)(((v.d + SEL_BN - 1) / SEL_BN) * ((v.D + SEL_BM - 1) / SEL_BM));
-  blocks[kGrpSelFinish] = grid_for(v.d);
   int proj = 0;
 #define GLR_PROJ_BLOCKS(BM, BN, WM, WN, FL) proj = (int)(((v.D + BN - 1) / BN) * ((r + BM - 1) / BM) * v.N * g.splits)
   GLR_PROJ_TIERS(GLR_PROJ_BLOCKS);
@@ -1351,9 +1417,7 @@ static hipError_t launch_group_select_st(const GroupPlan& gp, bool check_finite,
     else GLR_GSEL(false, false, false);
   }
 #undef GLR_GSEL
-  hipLaunchKernelGGL(k_g_sel_finish, grid(kGrpSelFinish), dim3(kThreads), 0, s, gp.gm, table(kGrpSelFinish), num,
-                     approx ? 1 : 0);
-  hipLaunchKernelGGL(k_g_topr, dim3((unsigned)num), dim3(1024), gp.topr_lds, s, gp.gm);
+  hipLaunchKernelGGL(k_g_topr, dim3((unsigned)num), dim3(kToprThreads), 0, s, gp.gm, approx ? 1 : 0);
 #define GLR_GPROJ(BM, BN, WM, WN, FL)                                                                       \
   do {                                                                                                      \
     if (right)                                                                                              \

@@ -87,3 +87,52 @@ def test_residual_against_fp64(gpu_lib, rank, shape, workers, store):
     assert np.all(np.abs(E - (Mo - C)) <= 4e-6 * col + (2.0 ** -8 if store == "bf16" else 2.0 ** -22) * np.abs(Mo - C))
     assert np.all(np.abs(-oriented(X) - C.mean(0)) <= 4e-6 * col.max(0))
     assert np.all(np.abs(oriented(comp.Ebar(0)) - E.mean(0)) <= 1e-6 * np.abs(E).max(0) + 1e-37)
+
+
+# one and several keys a thread, the fold inside and outside the selecting
+# workgroup, ties (equal scores go to the smaller index) and extremes
+@pytest.mark.parametrize("d,D", [(2, 3), (127, 300), (1023, 1100), (1025, 1500), (2050, 2100), (1030, 9000)])
+@pytest.mark.parametrize("rank", [1, 7, 400])
+def test_top_r_order(gpu_lib, d, D, rank):
+    if rank >= d:
+        pytest.skip("every direction kept")
+    rng = np.random.default_rng([d, rank])
+    # U = I and one entry per row of M: the exact scores are these squares, with
+    # ties (all above (2^-39 max |M|)^2, what one scale for the matrix resolves)
+    vals = rng.choice([0.0, 1e-6, 0.5, 1.0, 2.0, 3.0], size=d).astype(np.float32)
+    G = np.zeros((1, d, D), np.float32)
+    G[0, np.arange(d), rng.integers(0, D, d)] = vals
+    comp = gpu_lib.GreedyLore([(d, D)], 1, rank, 1000, select="exact")
+    comp.resume(1)
+    comp.step([torch.zeros(d, D, device="cuda")], [torch.from_numpy(G).cuda()], 1)
+    comp.check_status()
+    score = comp.score(0).cpu().numpy()
+    assert np.allclose(score, vals.astype(np.float64) ** 2, rtol=1e-6, atol=1e-30)
+    want = np.sort(np.argsort(-score, kind="stable")[:rank])
+    assert np.array_equal(comp.J(0).cpu().numpy(), want)
+
+
+# a set with both sides: one grouped part per side, bitwise the per-matrix launches
+@pytest.mark.parametrize("rank,opt", [(5, "msgd"), (12, "adam"), (40, "adam")])
+def test_grouped_selection_with_both_sides(gpu_lib, monkeypatch, rank, opt):
+    shapes = [(90, 200), (200, 90), (64, 64), (333, 130), (70, 71)]
+    rng = np.random.default_rng(rank)
+    G = [[torch.from_numpy(rng.standard_normal((3, m, n)).astype(np.float32)).cuda() for m, n in shapes]
+         for _ in range(3)]
+    runs = []
+    for grouped in ("0", None):
+        if grouped is None:
+            monkeypatch.delenv("GLR_GROUPED", raising=False)
+        else:
+            monkeypatch.setenv("GLR_GROUPED", grouped)
+        comp = gpu_lib.GreedyLore(shapes, 3, rank, 1000, opt=opt)
+        comp.resume(1)
+        X = [torch.zeros(m, n, device="cuda") for m, n in shapes]
+        for t in range(3):
+            comp.step(X, G[t], t + 1)
+        comp.check_status()
+        runs.append((comp, X))
+    (c1, x1), (c2, x2) = runs
+    for l in range(len(shapes)):
+        assert torch.equal(x1[l], x2[l]) and torch.equal(c1.E(l), c2.E(l)) and torch.equal(c1.J(l), c2.J(l))
+        assert torch.equal(c1.score(l), c2.score(l)) and torch.equal(c1.Rbar(l), c2.Rbar(l))
