@@ -227,8 +227,10 @@ template <int NG>
 struct JacShape {
   static constexpr int NR = NG * kJB;        // rows of a group
   static constexpr int NP = NR / 2;          // rotations per step
-  static constexpr int NT = NG == 4 ? 512 : 256;   // solve threads
+  static constexpr int NT = NG == 4 ? 1024 : 512;  // solve threads
   static constexpr int NW = NT / 64;
+  static constexpr int NOFF = NP * (NP - 1) / 2;   // off-diagonal 2 x 2 blocks of G
+  static constexpr int GW = (NOFF + 63) / 64;      // waves that own them: 0 .. GW - 1
   static constexpr int CROSS = (NG == 2 ? 1 : 3) * kJB;   // steps between blocks
 };
 
@@ -424,7 +426,7 @@ template <int NG>
 struct SolveLds {
   static constexpr int NR = JacShape<NG>::NR, NP = NR / 2, NPK = NR * (NR + 2);
   // past the matrix: a place for the stores of lanes without a block
-  static constexpr int NDUM = 4 * (JacShape<NG>::NT - NP * (NP - 1) / 2 + 64);
+  static constexpr int NDUM = 4 * (64 * JacShape<NG>::GW - JacShape<NG>::NOFF + 64);
   double Gp[2][NPK + NDUM];
   double V[NR][NR + 1];              // row coordinates
   double2 rot[2][64];                // (c, s) of the rotations of two consecutive steps (lanes
@@ -439,70 +441,32 @@ union JacLds {
 };
 
 // One cyclic sweep over the rotations of the group, on G in slot
-// coordinates (see JacTab), V <- V J in row coordinates.  Work items: the
-// NP (NP + 1) / 2 upper 2 x 2 blocks of G and the NR / 2 x NP 2 x 2 blocks
-// of V (rows 2 i, 2 i + 1; columns of rotation j), spread over 256 threads
-// (a few per thread: four waves keep the per-step scalar work of the loop
-// small).  One barrier per step: the items that produce the entry G[p'][q']
-// of a next-step rotation (all in wave 0) also form its new diagonal entries
-// from the old diagonal blocks of its two source rotations and compute it.
+// coordinates (see JacTab), V <- V J in row coordinates.  A step is one
+// barrier, and what bounds it is the longest chain of LDS round trips and
+// dependent fp64 instructions of a wave, so the waves have roles: wave 0 owns
+// the 2 x 2 blocks that hold the next step's rotations (with the diagonal
+// blocks of their sources, from which it forms them) and as many others as it
+// has lanes, waves 1 .. GW - 1 the other off-diagonal blocks, and waves of
+// their own the 2 x 2 blocks of V (rows 2 i, 2 i + 1; columns of rotation j),
+// which need the current rotations only.  Every wave issues all its LDS loads
+// of a step before the arithmetic and the stores (the next step's copy of G;
+// own entries of V).  With the three jobs of a step one after another in every
+// wave (256 and 512 threads) a full sweep of 32 rows took 25 us and one of 64
+// rows 60; with roles 21 and 54.
 template <int NG, bool CROSS>
 __device__ __forceinline__ void sweep_group(SolveLds<NG>& L, int max_inner) {
   using SH = JacShape<NG>;
   using TB = JacTab<NG, CROSS>;
-  constexpr int NR = SH::NR, NT = SH::NT, NP = NR / 2, NOFF = NP * (NP - 1) / 2, STEPS = TB::STEPS;
+  constexpr int NR = SH::NR, NP = NR / 2, NOFF = SH::NOFF, GW = SH::GW, STEPS = TB::STEPS;
   constexpr int NPK = SolveLds<NG>::NPK;
-  constexpr int VB = (NR / 2) * NP / NT;            // V items per thread
-  static_assert(NOFF <= NT && VB * NT == (NR / 2) * NP, "one G item, whole V items per thread");
+  constexpr int VW = NG == 4 ? 8 : 4;                // waves of V
+  constexpr int VB = (NR / 2) * NP / (64 * VW);      // V items per thread
+  static_assert(VB * 64 * VW == (NR / 2) * NP, "whole V items per thread");
+  static_assert(NP <= 64 && (NG == 4 ? GW + VW : 7) <= SH::NW, "a wave for every role");
   const TB& tab = jac_tab<NG, CROSS>();
-  const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
-  // this thread's off-diagonal 2 x 2 block (a, b), a < b, of G: the LDS
-  // offsets of its two rows now and of its four entries at the next step
-  // (threads without a block read block 0 and store into the dummy slots)
-  const bool has = tid < NOFF;
-  const uint32_t be = tab.blk[has ? tid : 0];
-  const int ua = be & 0xFF, ub = be >> 8;
-  const int rd0 = gat<NR>(2 * ua, 2 * ub), rd1 = gat<NR>(2 * ua + 1, 2 * ub);
-  auto dest4 = [&](const uint8_t* sg, int (&wo)[4]) {
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int y = 0; y < 2; ++y) {
-        const int Pn = sg[2 * ua + x], Qn = sg[2 * ub + y];
-        wo[2 * x + y] = has ? gat<NR>(min(Pn, Qn), max(Pn, Qn)) : NPK + 4 * (tid - NOFF) + 2 * x + y;
-      }
-  };
-  int wr[4];
-  dest4(tab.sig[0], wr);
-  // wave 0: lane j < NP forms rotation j of the next step from entry (2 X +
-  // sx, 2 Y + sy) of its block and the diagonal blocks of X and Y, and
-  // stores the new diagonal block of one of them (dsel); the other lanes
-  // repeat lane 0's work into the dummy slots
-  const int oj = lane < NP ? lane : 0;
-  int ox = 0, osx = 0, oy = 0, osy = 0;
-  next_source<NP>(CROSS, oj, ox, osx, oy, osy);
-  const int osel = ox == ua ? 2 * osx + osy : 2 * osy + osx;
-  const int odx = gat<NR>(2 * ox, 2 * ox), ody = gat<NR>(2 * oy, 2 * oy);
-  const int dsel = tab.dsel[oj], dp = dsel == 0 ? ox : oy;
-  const bool ownr = w == 0 && lane < NP;
-  auto dest3 = [&](const uint8_t* sg, int (&wo)[3]) {
-    const int Pn = sg[2 * dp], Qn = sg[2 * dp + 1];
-    wo[0] = ownr ? gat<NR>(Pn, Pn) : NPK + 4 * (NT - NOFF + lane);
-    wo[1] = ownr ? gat<NR>(min(Pn, Qn), max(Pn, Qn)) : NPK + 4 * (NT - NOFF + lane) + 1;
-    wo[2] = ownr ? gat<NR>(Qn, Qn) : NPK + 4 * (NT - NOFF + lane) + 2;
-  };
-  int wd[3];
-  dest3(tab.sig[0], wd);
-  const int vb = tid % NP, vr0 = 2 * (tid / NP);
-  // J^T B J of a diagonal 2 x 2 block (g00, g01, g11) by its own rotation
-  auto diag_update = [](double g00, double g01, double g11, double c, double sn, double& n00, double& n01,
-                        double& n11) {
-    const double t00 = g00 * c - g01 * sn, t01 = g00 * sn + g01 * c;
-    const double t10 = g01 * c - g11 * sn, t11 = g01 * sn + g11 * c;
-    n00 = c * t00 - sn * t10;
-    n01 = c * t01 - sn * t11;
-    n11 = sn * t01 + c * t11;
-  };
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(wave_id());
+  // (NG = 2: waves 2, 3, 5, 6, off the SIMD of wave 0)
+  const int vw = NG == 4 ? w - GW : (w == 2 || w == 3 ? w - 2 : w == 5 || w == 6 ? w - 3 : -1);
   // the rotations of a step from its copy of G (slots 2j, 2j + 1): step 0
   // and the steps after a change of pairing
   auto rotations_from_g = [&](int buf) {
@@ -514,88 +478,174 @@ __device__ __forceinline__ void sweep_group(SolveLds<NG>& L, int max_inner) {
       L.rot[buf][lane] = double2{c, sn};
     }
   };
+  auto change_at = [](int st) { return NG == 4 && CROSS && (st & (kJB - 1)) == kJB - 1; };
+  // the end of a step, the same barriers in every wave
+  auto end_step = [&](bool more, bool change, int pnxt) {
+    __syncthreads();
+    if (more && change) {
+      rotations_from_g(pnxt);
+      __syncthreads();
+    }
+  };
   rotations_from_g(0);
   __syncthreads();
-  const uint16_t* pq16 = reinterpret_cast<const uint16_t*>(L.pq);
-  for (int inner = 0; inner < max_inner; ++inner) {
-    for (int st = 0; st < STEPS; ++st) {
-      const int pcur = (inner * STEPS + st) & 1, pnxt = pcur ^ 1;
-      const bool more = st + 1 < STEPS || inner + 1 < max_inner;
-      const bool change = NG == 4 && CROSS && (st & (kJB - 1)) == kJB - 1;
-      const double* Gc = L.Gp[pcur];
-      double* Gn = L.Gp[pnxt];
-      const double2* rc = L.rot[pcur];
-      // every load of the step first (the stores go to the other copy of G
-      // and to this thread's own entries of V), then the arithmetic, then the
-      // stores: one LDS round trip per step
-      const double2 ra = rc[ua], rb = rc[ub];
-      const double2 g0 = *reinterpret_cast<const double2*>(Gc + rd0);
-      const double2 g1 = *reinterpret_cast<const double2*>(Gc + rd1);
-      double dx0 = 0.0, dx1 = 0.0, dx2 = 0.0, dy0 = 0.0, dy1 = 0.0, dy2 = 0.0;
-      if (w == 0) {
-        dx0 = Gc[odx]; dx1 = Gc[odx + 1]; dx2 = Gc[odx + NR + 3];
-        dy0 = Gc[ody]; dy1 = Gc[ody + 1]; dy2 = Gc[ody + NR + 3];
-      }
-      const uint32_t e = pq16[st * NP + vb];
-      const int pv = e & 0xFF, qv = e >> 8;
-      const double2 rv = rc[vb];
-      double vv[VB][4];
+  if (w < GW) {
+    // this thread's off-diagonal 2 x 2 block (a, b), a < b, of G: the LDS
+    // offsets of its two rows now and of its four entries at the next step
+    // (threads without a block read block 0 and store into the dummy slots)
+    const int item = w * 64 + lane;
+    const bool has = item < NOFF;
+    const uint32_t be = tab.blk[has ? item : 0];
+    const int ua = be & 0xFF, ub = be >> 8;
+    const int rd0 = gat<NR>(2 * ua, 2 * ub), rd1 = gat<NR>(2 * ua + 1, 2 * ub);
+    auto dest4 = [&](const uint8_t* sg, int (&wo)[4]) {
 #pragma unroll
-      for (int k = 0; k < VB; ++k) {
-        const int vr = vr0 + k * (2 * NT / NP);
-        vv[k][0] = L.V[vr][pv]; vv[k][1] = L.V[vr][qv];
-        vv[k][2] = L.V[vr + 1][pv]; vv[k][3] = L.V[vr + 1][qv];
-      }
-      if (change) {
-        const uint8_t* sg = tab.sig[1 + (st >> 4)];
-        dest4(sg, wr);
-        dest3(sg, wd);
-      }
-      // off-diagonal block: G <- J_a^T G J_b
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+          const int Pn = sg[2 * ua + x], Qn = sg[2 * ub + y];
+          wo[2 * x + y] = has ? gat<NR>(min(Pn, Qn), max(Pn, Qn)) : NPK + 4 * (item - NOFF) + 2 * x + y;
+        }
+    };
+    int wr[4];
+    dest4(tab.sig[0], wr);
+    // J_a^T G J_b of an off-diagonal block
+    auto off_update = [](double2 g0, double2 g1, double2 ra, double2 rb, double (&n)[4]) {
       const double ca = ra.x, sa = ra.y, cb = rb.x, sb = rb.y;
       const double t00 = g0.x * cb - g0.y * sb, t01 = g0.x * sb + g0.y * cb;
       const double t10 = g1.x * cb - g1.y * sb, t11 = g1.x * sb + g1.y * cb;
-      const double n00 = ca * t00 - sa * t10, n01 = ca * t01 - sa * t11;
-      const double n10 = sa * t00 + ca * t10, n11 = sa * t01 + ca * t11;
-      if (w == 0) {
-        const double2 rx = ox == ua ? ra : rb, ry = ox == ua ? rb : ra;
-        double x00, x01, x11, y00, y01, y11;
-        diag_update(dx0, dx1, dx2, rx.x, rx.y, x00, x01, x11);
-        diag_update(dy0, dy1, dy2, ry.x, ry.y, y00, y01, y11);
-        if (more && !change) {
-          const double gpq = osel == 0 ? n00 : (osel == 1 ? n01 : (osel == 2 ? n10 : n11));
-          double c, sn;
-          jac_rotation(osx == 0 ? x00 : x11, osy == 0 ? y00 : y11, gpq, c, sn);
-          L.rot[pnxt][lane] = double2{c, sn};
+      n[0] = ca * t00 - sa * t10;
+      n[1] = ca * t01 - sa * t11;
+      n[2] = sa * t00 + ca * t10;
+      n[3] = sa * t01 + ca * t11;
+    };
+    if (w == 0) {
+      // lane j < NP forms rotation j of the next step from entry (2 X + sx,
+      // 2 Y + sy) of its block and the diagonal blocks of X and Y, and stores
+      // the new diagonal block of one of them (dsel); the other lanes repeat
+      // lane 0's work into the dummy slots
+      const int oj = lane < NP ? lane : 0;
+      int ox = 0, osx = 0, oy = 0, osy = 0;
+      next_source<NP>(CROSS, oj, ox, osx, oy, osy);
+      const uint32_t bo = tab.blk[oj];
+      const int oa = bo & 0xFF;                      // ua in the lanes below NP
+      const int osel = ox == oa ? 2 * osx + osy : 2 * osy + osx;
+      const int odx = gat<NR>(2 * ox, 2 * ox), ody = gat<NR>(2 * oy, 2 * oy);
+      const int dsel = tab.dsel[oj], dp = dsel == 0 ? ox : oy;
+      const bool ownr = lane < NP;
+      constexpr int DUM = NPK + 4 * (64 * GW - NOFF);
+      auto dest3 = [&](const uint8_t* sg, int (&wo)[3]) {
+        const int Pn = sg[2 * dp], Qn = sg[2 * dp + 1];
+        wo[0] = ownr ? gat<NR>(Pn, Pn) : DUM + 4 * lane;
+        wo[1] = ownr ? gat<NR>(min(Pn, Qn), max(Pn, Qn)) : DUM + 4 * lane + 1;
+        wo[2] = ownr ? gat<NR>(Qn, Qn) : DUM + 4 * lane + 2;
+      };
+      int wd[3];
+      dest3(tab.sig[0], wd);
+      // J^T B J of a diagonal 2 x 2 block (g00, g01, g11) by its own rotation
+      auto diag_update = [](double g00, double g01, double g11, double c, double sn, double& n00, double& n01,
+                            double& n11) {
+        const double t00 = g00 * c - g01 * sn, t01 = g00 * sn + g01 * c;
+        const double t10 = g01 * c - g11 * sn, t11 = g01 * sn + g11 * c;
+        n00 = c * t00 - sn * t10;
+        n01 = c * t01 - sn * t11;
+        n11 = sn * t01 + c * t11;
+      };
+      for (int inner = 0; inner < max_inner; ++inner)
+        for (int st = 0; st < STEPS; ++st) {
+          const int pcur = (inner * STEPS + st) & 1, pnxt = pcur ^ 1;
+          const bool more = st + 1 < STEPS || inner + 1 < max_inner, change = change_at(st);
+          const double* Gc = L.Gp[pcur];
+          double* Gn = L.Gp[pnxt];
+          const double2* rc = L.rot[pcur];
+          const double2 ra = rc[ua], rb = rc[ub], rx = rc[ox], ry = rc[oy];
+          const double2 g0 = *reinterpret_cast<const double2*>(Gc + rd0);
+          const double2 g1 = *reinterpret_cast<const double2*>(Gc + rd1);
+          const double2 dx = *reinterpret_cast<const double2*>(Gc + odx);
+          const double2 dy = *reinterpret_cast<const double2*>(Gc + ody);
+          const double dx2 = Gc[odx + NR + 3], dy2 = Gc[ody + NR + 3];
+          if (change) {
+            const uint8_t* sg = tab.sig[1 + (st >> 4)];
+            dest4(sg, wr);
+            dest3(sg, wd);
+          }
+          double n[4];
+          off_update(g0, g1, ra, rb, n);
+          double x00, x01, x11, y00, y01, y11;
+          diag_update(dx.x, dx.y, dx2, rx.x, rx.y, x00, x01, x11);
+          diag_update(dy.x, dy.y, dy2, ry.x, ry.y, y00, y01, y11);
+          if (more && !change) {
+            const double gpq = osel == 0 ? n[0] : (osel == 1 ? n[1] : (osel == 2 ? n[2] : n[3]));
+            double c, sn;
+            jac_rotation(osx == 0 ? x00 : x11, osy == 0 ? y00 : y11, gpq, c, sn);
+            L.rot[pnxt][lane] = double2{c, sn};
+          }
+          Gn[wd[0]] = dsel == 0 ? x00 : y00;
+          Gn[wd[1]] = dsel == 0 ? x01 : y01;
+          Gn[wd[2]] = dsel == 0 ? x11 : y11;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) Gn[wr[e]] = n[e];
+          end_step(more, change, pnxt);
+          if (more && change) {
+            dest4(tab.sig[0], wr);
+            dest3(tab.sig[0], wd);
+          }
         }
-        Gn[wd[0]] = dsel == 0 ? x00 : y00;
-        Gn[wd[1]] = dsel == 0 ? x01 : y01;
-        Gn[wd[2]] = dsel == 0 ? x11 : y11;
-      }
-      Gn[wr[0]] = n00;
-      Gn[wr[1]] = n01;
-      Gn[wr[2]] = n10;
-      Gn[wr[3]] = n11;
-      {
-        // V <- V J on rows (row coordinates): columns p, q of rotation vb
+    } else {
+      for (int inner = 0; inner < max_inner; ++inner)
+        for (int st = 0; st < STEPS; ++st) {
+          const int pcur = (inner * STEPS + st) & 1, pnxt = pcur ^ 1;
+          const bool more = st + 1 < STEPS || inner + 1 < max_inner, change = change_at(st);
+          const double* Gc = L.Gp[pcur];
+          double* Gn = L.Gp[pnxt];
+          const double2* rc = L.rot[pcur];
+          const double2 ra = rc[ua], rb = rc[ub];
+          const double2 g0 = *reinterpret_cast<const double2*>(Gc + rd0);
+          const double2 g1 = *reinterpret_cast<const double2*>(Gc + rd1);
+          if (change) dest4(tab.sig[1 + (st >> 4)], wr);
+          double n[4];
+          off_update(g0, g1, ra, rb, n);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) Gn[wr[e]] = n[e];
+          end_step(more, change, pnxt);
+          if (more && change) dest4(tab.sig[0], wr);
+        }
+    }
+  } else if (vw >= 0) {
+    // V <- V J on rows (row coordinates): columns p, q of rotation vb; the
+    // table entry of the next step is read a step ahead
+    const int vt = vw * 64 + lane, vb = vt % NP, vr0 = 2 * (vt / NP);
+    const uint16_t* pq16 = reinterpret_cast<const uint16_t*>(L.pq);
+    uint32_t e = pq16[vb];
+    for (int inner = 0; inner < max_inner; ++inner)
+      for (int st = 0; st < STEPS; ++st) {
+        const int pcur = (inner * STEPS + st) & 1;
+        const bool more = st + 1 < STEPS || inner + 1 < max_inner;
+        const int pv = e & 0xFF, qv = e >> 8;
+        const double2 rv = L.rot[pcur][vb];
+        double vv[VB][4];
+#pragma unroll
+        for (int k = 0; k < VB; ++k) {
+          const int vr = vr0 + k * (2 * 64 * VW / NP);
+          vv[k][0] = L.V[vr][pv]; vv[k][1] = L.V[vr][qv];
+          vv[k][2] = L.V[vr + 1][pv]; vv[k][3] = L.V[vr + 1][qv];
+        }
+        e = pq16[(st + 1 < STEPS ? st + 1 : 0) * NP + vb];
         const double cv = rv.x, sv = rv.y;
 #pragma unroll
         for (int k = 0; k < VB; ++k) {
-          const int vr = vr0 + k * (2 * NT / NP);
+          const int vr = vr0 + k * (2 * 64 * VW / NP);
           L.V[vr][pv] = vv[k][0] * cv - vv[k][1] * sv;
           L.V[vr][qv] = vv[k][0] * sv + vv[k][1] * cv;
           L.V[vr + 1][pv] = vv[k][2] * cv - vv[k][3] * sv;
           L.V[vr + 1][qv] = vv[k][2] * sv + vv[k][3] * cv;
         }
+        end_step(more, change_at(st), pcur ^ 1);
       }
-      __syncthreads();
-      if (more && change) {
-        rotations_from_g(pnxt);
-        __syncthreads();
-        dest4(tab.sig[0], wr);
-        dest3(tab.sig[0], wd);
-      }
-    }
+  } else {
+    for (int inner = 0; inner < max_inner; ++inner)
+      for (int st = 0; st < STEPS; ++st)
+        end_step(st + 1 < STEPS || inner + 1 < max_inner, change_at(st), ((inner * STEPS + st) & 1) ^ 1);
   }
 }
 
