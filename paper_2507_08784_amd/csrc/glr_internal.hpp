@@ -266,6 +266,8 @@ hipError_t launch_joint_solve(const JointPlan& jp, int par, int round, float tol
 hipError_t launch_joint_solve_apply(const JointPlan& jp, int par, int round, float tol, int max_inner,
                                     double floor_rel2, hipStream_t s);
 hipError_t launch_joint_update(const JointPlan& jp, int par, int round, hipStream_t s);
+hipError_t launch_joint_tail(const JointPlan& jp, int par, int n, float tol, int max_inner, double floor_rel2,
+                             hipStream_t s);
 hipError_t launch_joint_check(const JointPlan& jp, float tol, hipStream_t s);
 
 // Jacobi on the fp64 Gram of the rows of W
@@ -289,6 +291,12 @@ hipError_t launch_jac_sort(const MatView& v, hipStream_t s);
 hipError_t launch_jac_solve(const MatView& v, int round, float tol, int max_inner, double floor_rel2,
                             hipStream_t s);
 hipError_t launch_jac_check(const MatView& v, float tol, hipStream_t s);
+// up to n trailing sweeps in one launch, the result in the same buffers (d up
+// to kTailMaxDim and pairs of blocks: jac_has_tail)
+constexpr int kTailMaxDim = 640;
+bool jac_has_tail(int64_t d);
+hipError_t launch_jac_tail(const MatView& v, int n, bool sort, float tol, int max_inner, double floor_rel2,
+                           hipStream_t s);
 hipError_t launch_jac_finish(const MatView& v, int max_sweeps, hipStream_t s);
 hipError_t launch_reorth(const MatView& v, hipStream_t s);
 hipError_t launch_warm_product(const MatView& v, hipStream_t s);

@@ -172,6 +172,18 @@ hipError_t launch_jac_init(const MatView& v, bool warm, hipStream_t s) {
 // one round: solve (one block per pair), update (one block per two pairs),
 // apply (column chunks of every pair's rows of U^T)
 // ---------------------------------------------------------------------------
+// Words that the same kernel may have written (the trailing sweeps run all of
+// a sweep in one workgroup): read past the scalar cache.
+__device__ __forceinline__ int ld_fresh(const int* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t ld_fresh(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t ld_fresh(const uint64_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // entry (x, y) of the 32 x 32 block of A whose rows are the blocks (bx0, bx1)
 // and columns (by0, by1); zero for padding blocks
 __device__ __forceinline__ double pk_get(const double* __restrict__ Apk, int nb, int bx, int by, int lx,
@@ -666,7 +678,7 @@ __device__ __forceinline__ void solve_group(const double* __restrict__ Apk, JacC
   double* red = L.red;
   double* redw = L.redw;
   constexpr int NE = NR * NR / NT;
-  const double rm_prev = __longlong_as_double((long long)ctl->rowmax2_bits);
+  const double rm_prev = __longlong_as_double((long long)ld_fresh(&ctl->rowmax2_bits));
   // the group's diagonal NR x NR block of A; element k of this thread is
   // (x, y) = (tid / NR + k (NT / NR), tid % NR)
   double g[NE];
@@ -780,7 +792,7 @@ __device__ __forceinline__ void apply_chunk(float* __restrict__ Utw, int64_t d, 
                                             int grp, int chunk, int width,
                                             float (*Va)[JacShape<NG>::NR + 1]) {
   constexpr int NR = JacShape<NG>::NR;
-  if (skip[grp]) return;
+  if (ld_fresh(skip + grp)) return;
   int blk[NG];
   group_blocks<NG>(round, grp, seats, blk);
   if (group_empty<NG>(blk, nb)) return;
@@ -858,12 +870,13 @@ __device__ __forceinline__ void update_pair(double* __restrict__ Apk, const doub
     ++g;
   }
   const int h = g + rem;
-  const bool sg = skip[g] != 0, sh = skip[h] != 0;
+  const bool sg = ld_fresh(skip + g) != 0, sh = ld_fresh(skip + h) != 0;
   if (sg && sh) return;
   int bg[NG], bh[NG];
   group_blocks<NG>(round, g, seats, bg);
   group_blocks<NG>(round, h, seats, bh);
-  const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
+  // (a larger workgroup repeats the work of its first 256 threads)
+  const int tid = threadIdx.x & 255, lane = lane_id(), w = wave_id() & 3;
   const int er = tid / kJB, ec = tid % kJB;
   const int R0 = (w >> 1) * (NR / 2), C0 = (w & 1) * (NR / 2), li = lane & 15, lk = lane >> 4;
   double sv[NG * NG];
@@ -1152,9 +1165,10 @@ constexpr int kPermBlocks = 8;
 // the kPermBlocks stored blocks from `bid * kPermBlocks` of B = A with rows and
 // columns reordered by perm
 __device__ __forceinline__ void pk_permute_blocks(const double* __restrict__ A, double* __restrict__ B,
-                                                  const int* __restrict__ perm, int64_t d, int nb, int64_t bid) {
+                                                  const int* perm, int64_t d, int nb, int64_t bid) {
   const int64_t nblk = (int64_t)nb * (nb + 1) / 2;
-  const int r = threadIdx.x / kJB, c = threadIdx.x % kJB;
+  const int tid = threadIdx.x & (kJB * kJB - 1);   // (a larger workgroup: 256 threads for each bid)
+  const int r = tid / kJB, c = tid % kJB;
   const int64_t first = bid * kPermBlocks;
   // (a, b) of the first block, then walk along the packed order
   int64_t blk = first;
@@ -1176,7 +1190,7 @@ __device__ __forceinline__ void pk_permute_blocks(const double* __restrict__ A, 
   }
 #pragma unroll
   for (int q = 0; q < kPermBlocks; ++q)
-    if (first + q < nblk) B[(first + q) * (kJB * kJB) + threadIdx.x] = x[q];
+    if (first + q < nblk) B[(first + q) * (kJB * kJB) + tid] = x[q];
 }
 __global__ void __launch_bounds__(256)
 k_pk_permute(const double* __restrict__ A, double* __restrict__ B, const int* __restrict__ perm, int64_t d,
@@ -1221,6 +1235,105 @@ hipError_t launch_jac_finish(const MatView& v, int max_sweeps, hipStream_t s) {
   return hipGetLastError();
 }
 
+
+// ---------------------------------------------------------------------------
+// Trailing sweeps: up to n more sweeps (until convergence) by one workgroup
+// per matrix in one launch, each sweep the launches of an enqueued sweep one
+// after another, so the same bits.  Every refresh enqueues the sweeps its
+// matrix has been seen to need and one more; what it may need beyond them is
+// left to this launch, which nearly always finds the matrix converged and
+// returns.  Enqueued as sweeps of their own, each of them cost its 3 + 2
+// rounds empty launches: about 45 us at d = 128 (of a 1.5 ms refresh, eight of
+// them) and 350 us for the fifty layers at d <= 512 (of 21.6 ms, nine).  The
+// price is a slow sweep when one is needed: some 50 us of every round's
+// groups one by one, so only up to kTailMaxDim.
+// The sorts swap Apk <-> Apk2 and Utw <-> W; an odd count of sweeps is copied
+// back, so the result is where it was.
+// ---------------------------------------------------------------------------
+struct TailDims {
+  int nb, seats, groups, rounds;
+};
+__device__ __forceinline__ void jac_tail(const MatView& v, const TailDims& J, int n, bool sort, float tol,
+                                         int max_inner, double floor_rel2, JacLds<2>& lds) {
+  constexpr int NG = 2, NT = JacShape<NG>::NT, NR = JacShape<NG>::NR;
+  const int tid = threadIdx.x, d = (int)v.d;
+  double* A = v.Apk;
+  double* A2 = v.Apk2;
+  float* U = v.Utw;
+  float* U2 = v.W;
+  bool swapped = false;
+  for (int sw = 0; sw < n; ++sw) {
+    if (ld_fresh(&v.ctl->converged)) break;
+    if (sort) {
+      for (int j = tid; j < d; j += NT) diag_sqrt_at(A, d, J.nb, v.sigma_w, j);
+      __syncthreads();
+      int n_pad = 2;
+      while (n_pad < d) n_pad <<= 1;
+      sort_desc_block(v.sigma_w, d, n_pad, v.perm, reinterpret_cast<uint64_t*>(&lds));
+      __syncthreads();
+      const int64_t nblk = (int64_t)J.nb * (J.nb + 1) / 2;
+      for (int64_t b = tid >> 8; b < (nblk + kPermBlocks - 1) / kPermBlocks; b += NT / 256)
+        pk_permute_blocks(A, A2, v.perm, d, J.nb, b);
+      for (int k = 0; k < d; ++k) {
+        const int64_t p = ld_fresh(v.perm + k);
+        for (int a = tid; a < d; a += NT) U2[(int64_t)k * d + a] = U[p * d + a];
+      }
+      double* ta = A; A = A2; A2 = ta;
+      float* tu = U; U = U2; U2 = tu;
+      swapped = !swapped;
+      __syncthreads();
+    }
+    const int64_t vb = (int64_t)J.groups * NR * NR;
+    for (int rd = 0; rd < J.rounds; ++rd) {
+      const int64_t p = rd & 1;
+      float* V = v.Vrot + p * vb;
+      double* V64 = v.V64 + p * vb;
+      int* skip = v.skip + p * J.groups;
+      for (int g = 0; g < J.groups; ++g) {
+        solve_group<NG>(A, v.ctl, rd, J.seats, J.nb, tol, max_inner, floor_rel2, V, V64, skip, g, lds.s);
+        __syncthreads();
+      }
+      for (int b = 0; b < J.groups * (J.groups + 1) / 2; ++b) {
+        update_pair<NG>(A, V64, skip, rd, J.seats, J.nb, J.groups, b, reinterpret_cast<double (*)[NR + 1]>(&lds));
+        __syncthreads();
+      }
+      for (int g = 0; g < J.groups; ++g) {
+        apply_chunk<NG>(U, d, V, skip, rd, J.seats, J.nb, g, 0, (d + 1023) / 1024 * 1024, lds.Va);
+        __syncthreads();
+      }
+    }
+    if (tid == 0) {
+      const uint32_t mx = ld_fresh(&v.ctl->sweep_max_bits);
+      const uint32_t done = ld_fresh(&v.ctl->sweeps);
+      if (done < (uint32_t)kHistory) v.ctl->history[done] = mx;
+      __hip_atomic_store(&v.ctl->sweeps, done + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&v.ctl->sweep_max_bits, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__uint_as_float(mx) <= tol)
+        __hip_atomic_store(&v.ctl->converged, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+  }
+  if (swapped) {
+    const int64_t na = pk_doubles(J.nb);
+    for (int64_t i = tid; i < na; i += NT) A2[i] = A[i];
+    for (int64_t i = tid; i < (int64_t)d * d; i += NT) U2[i] = U[i];
+  }
+}
+static_assert(kTailMaxDim <= 1024, "one chunk of U^T rows, sort keys within the solve's LDS");
+__global__ void __launch_bounds__(JacShape<2>::NT)
+k_jac_tail(MatView v, TailDims J, int n, int sort, float tol, int max_inner, double floor_rel2) {
+  if (v.ctl->converged) return;
+  __shared__ JacLds<2> lds;
+  jac_tail(v, J, n, sort != 0, tol, max_inner, floor_rel2, lds);
+}
+bool jac_has_tail(int64_t d) { return d <= kTailMaxDim && jac_group_blocks(d) == 2; }
+hipError_t launch_jac_tail(const MatView& v, int n, bool sort, float tol, int max_inner, double floor_rel2,
+                           hipStream_t s) {
+  const TailDims J{jac_blocks(v.d), jac_seats(v.d), jac_groups(v.d), jac_rounds(v.d)};
+  hipLaunchKernelGGL(k_jac_tail, dim3(1), dim3(JacShape<2>::NT), 0, s, v, J, n, sort ? 1 : 0, tol, max_inner,
+                     floor_rel2);
+  return hipGetLastError();
+}
 
 // ---------------------------------------------------------------------------
 // Joint refresh: the sweeps of several matrices (one group size NG) in the
@@ -1324,6 +1437,15 @@ k_joint_update(const JointMat* __restrict__ jm, const int* __restrict__ first, i
                   blockIdx.x - first[m], S);
 }
 
+__global__ void __launch_bounds__(JacShape<2>::NT)
+k_joint_tail(const JointMat* __restrict__ jm, int par, int n, float tol, int max_inner, double floor_rel2) {
+  const JointMat& J = jm[blockIdx.x];
+  const MatView& v = J.v[par];
+  if (v.ctl->converged) return;
+  __shared__ JacLds<2> lds;
+  jac_tail(v, {J.nb, J.seats, J.groups, J.rounds}, n, true, tol, max_inner, floor_rel2, lds);
+}
+
 // the sweep's check of every matrix, and its converged flag for the host
 __global__ void k_joint_check(const JointMat* __restrict__ jm, float tol, int* __restrict__ flags) {
   JacCtl* ctl = jm[blockIdx.x].v[0].ctl;
@@ -1398,6 +1520,13 @@ hipError_t launch_joint_update(const JointPlan& jp, int par, int round, hipStrea
   const dim3 grid((unsigned)jp.total[kJointUpdate]);
   if (jp.ng == 4) hipLaunchKernelGGL(k_joint_update<4>, grid, dim3(256), 0, s, jp.jm, f, jp.num, par, round);
   else hipLaunchKernelGGL(k_joint_update<2>, grid, dim3(256), 0, s, jp.jm, f, jp.num, par, round);
+  return hipGetLastError();
+}
+
+hipError_t launch_joint_tail(const JointPlan& jp, int par, int n, float tol, int max_inner, double floor_rel2,
+                             hipStream_t s) {
+  hipLaunchKernelGGL(k_joint_tail, dim3((unsigned)jp.num), dim3(JacShape<2>::NT), 0, s, jp.jm, par, n, tol, max_inner,
+                     floor_rel2);
   return hipGetLastError();
 }
 

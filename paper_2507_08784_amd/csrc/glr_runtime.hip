@@ -360,7 +360,7 @@ struct glr_handle {
   // after convergence return at once) and never waits for the device.  The
   // sweeps each matrix's last refresh needed come back through pinned host
   // memory, read only once the copy's event has completed.
-  std::vector<int> known_sweeps;       // most sweeps a converged refresh took (-1: none yet)
+  std::vector<int> known_sweeps;       // most sweeps a converged refresh took (-1: none yet, -2: the last one missed)
   std::vector<int> known_conv;         // its converged flag
   std::vector<int> info_pending;       // a read-back is in flight
   int64_t repaired_total = 0;          // status reads that found replaced (dependent) rows
@@ -564,27 +564,32 @@ hipError_t prof_collect(glr_handle* h) {
     if (e_ != hipSuccess) return hip_fail(h, e_, #call); \
   } while (0)
 
-// Sweeps to enqueue for a refresh of `mat`: every allowed sweep until a
+// Sweeps to enqueue for a refresh of `mat`, with Jacobi dimension jd.  Where
+// trailing sweeps can follow in one launch (jac_has_tail) the largest count
+// read back so far and one more (kFirstSweeps before any): the trailing launch
+// covers every allowed sweep beyond them.  Else every allowed sweep until a
 // refresh of this matrix has been read back converged, then the largest count
 // read back so far plus a margin of half of it (at least four): a warm
 // refresh can need more sweeps than the cold one before it (7 then 10 have
 // been seen on the gradients of a small network).  A refresh that runs out of
 // its budget reports GLR_ERR_NOT_CONVERGED like one that runs out of
 // max_sweeps, and the next refresh gets every allowed sweep again.
-int sweep_budget(glr_handle* h, int mat) {
+constexpr int kFirstSweeps = 16;
+int sweep_budget(glr_handle* h, int mat, int64_t jd) {
   const int mx = h->cfg.max_sweeps;
-  if (!h->info_host) return mx;   // no read-back buffer (glr_create_static)
+  const bool tail = jac_has_tail(jd);
+  if (!h->info_host) return tail ? std::min(mx, kFirstSweeps) : mx;   // no read-back buffer (glr_create_static)
   if (h->info_pending[(size_t)mat] && hipEventQuery(h->info_ev[(size_t)mat]) == hipSuccess) {
     h->info_pending[(size_t)mat] = 0;
     const int seen = h->info_host[2 * mat], conv = h->info_host[2 * mat + 1];
     h->known_conv[(size_t)mat] = conv;
     // a miss forgets the record: the next refresh takes max_sweeps
-    h->known_sweeps[(size_t)mat] = conv ? std::max(h->known_sweeps[(size_t)mat], seen) : -1;
+    h->known_sweeps[(size_t)mat] = conv ? std::max(h->known_sweeps[(size_t)mat], seen) : -2;
   }
   const int k = h->known_sweeps[(size_t)mat];
+  if (k == -1) return tail ? std::min(mx, kFirstSweeps) : mx;
   if (k < 0 || !h->known_conv[(size_t)mat]) return mx;
-  const int b = k + std::max(4, k / 2);
-  return b < mx ? b : mx;
+  return std::min(mx, tail ? k + 1 : k + std::max(4, k / 2));
 }
 
 // after a refresh's finish: its sweep count and converged flag to the host
@@ -647,7 +652,7 @@ glr_status refresh_svd(glr_handle* h, const MatView& v0, int64_t t, hipStream_t 
   glr_status st = svd_begin(h, v, t, s);
   if (st != GLR_OK) return st;
   const int rounds = jac_rounds(v.d);
-  const int budget = sweep_budget(h, v.mat);
+  const int budget = sweep_budget(h, v.mat, v.d);
   for (int sw = 0; sw < budget; ++sw) {
     if (h->jac_sort == 1 || (h->jac_sort == 2 && sw == 0)) {
       GLR_HIP(h, launch_jac_sort(v, s));
@@ -657,6 +662,8 @@ glr_status refresh_svd(glr_handle* h, const MatView& v0, int64_t t, hipStream_t 
     GLR_HIP(h, jacobi_sweep(h, v, rounds, GLR_PROF_JAC_SOLVE, GLR_PROF_JAC_UPDATE, s));
     GLR_HIP(h, launch_jac_check(v, c.tol, s));
   }
+  if (jac_has_tail(v.d) && budget < c.max_sweeps)
+    GLR_HIP(h, launch_jac_tail(v, c.max_sweeps - budget, h->jac_sort == 1, c.tol, h->jac_inner, h->jac_floor2, s));
   st = svd_end(h, v, s);
   if (st != GLR_OK) return st;
   GLR_HIP(h, read_back_info(h, v.mat, v, s));
@@ -685,11 +692,13 @@ glr_status refresh_subspace(glr_handle* h, const MatView& v, int64_t t, hipStrea
   MatView rr;
   GLR_HIP(h, launch_sub_rr_begin(v, &rr, s));
   const int rounds = jac_rounds(rr.d);
-  const int budget = sweep_budget(h, v.mat);
+  const int budget = sweep_budget(h, v.mat, rr.d);
   for (int sw = 0; sw < budget; ++sw) {
     GLR_HIP(h, jacobi_sweep(h, rr, rounds, GLR_PROF_RR_SOLVE, GLR_PROF_RR_UPDATE, s));
     GLR_HIP(h, launch_jac_check(rr, c.tol, s));
   }
+  if (jac_has_tail(rr.d) && budget < c.max_sweeps)
+    GLR_HIP(h, launch_jac_tail(rr, c.max_sweeps - budget, false, c.tol, h->jac_inner, h->jac_floor2, s));
   ProfScope p(h, s, GLR_PROF_JAC_FINISH);
   GLR_HIP(h, launch_jac_finish(rr, c.max_sweeps, s));
   GLR_HIP(h, launch_sub_rr_end(v, sub_tol, iters, s));
@@ -819,7 +828,10 @@ glr_status step_joint(glr_handle* h, float* const* X, const void* const* G, int6
   // as many sweeps as the matrix with the largest budget needs; a converged
   // matrix's later sweeps only move its data to the other buffer of the pair
   int budget = 1;
-  for (int i = 0; i < num; ++i) budget = std::max(budget, sweep_budget(h, i));
+  bool tail = true;
+  for (int i = 0; i < num; ++i) tail = tail && jac_has_tail(h->lay[(size_t)i].d);
+  for (int i = 0; i < num; ++i)
+    budget = std::max(budget, sweep_budget(h, i, tail ? h->lay[(size_t)i].d : INT64_MAX));
   for (int sw = 0; sw < budget; ++sw) {
     const int par = sw & 1, p = par ^ 1;   // the sort reads parity par and fills the other
     GLR_HIP(h, launch_joint_sort(jp, par, s));
@@ -830,6 +842,8 @@ glr_status step_joint(glr_handle* h, float* const* X, const void* const* G, int6
     }
     GLR_HIP(h, launch_joint_check(jp, c.tol, s));
   }
+  if (tail && budget < c.max_sweeps)
+    GLR_HIP(h, launch_joint_tail(jp, budget & 1, c.max_sweeps - budget, c.tol, h->jac_inner, h->jac_floor2, s));
   return on_lanes(h, s, [&](int i, int lane, hipStream_t ls) -> glr_status {
     const MatView v = view_of(h, i, X[i], G[i], lane);
     const MatView& fin = h->jm[(size_t)i].v[budget & 1];

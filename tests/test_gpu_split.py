@@ -136,3 +136,29 @@ def test_grouped_selection_with_both_sides(gpu_lib, monkeypatch, rank, opt):
     for l in range(len(shapes)):
         assert torch.equal(x1[l], x2[l]) and torch.equal(c1.E(l), c2.E(l)) and torch.equal(c1.J(l), c2.J(l))
         assert torch.equal(c1.score(l), c2.score(l)) and torch.equal(c1.Rbar(l), c2.Rbar(l))
+
+
+# a refresh whose regular sweeps end before it converges is finished by the
+# trailing launch with the bits of regular sweeps: sixteen are enqueued of a
+# first refresh, so a tolerance that takes more than sixteen of them
+@pytest.mark.parametrize("shapes,tau", [([(130, 200)], 3), ([(97, 64), (64, 70), (200, 90)], 3), ([(400, 700)], 1)])
+def test_trailing_sweeps_finish_a_refresh(gpu_lib, monkeypatch, shapes, tau):
+    rng = np.random.default_rng(len(shapes))
+    G = [torch.from_numpy(rng.standard_normal((2, m, n)).astype(np.float32)).cuda() for m, n in shapes]
+    runs = []
+    for sweeps in (16, 17, 22):
+        comp = gpu_lib.GreedyLore(shapes, 2, 20, tau, max_sweeps=sweeps, tol=1e-16)
+        X = [torch.zeros(m, n, device="cuda") for m, n in shapes]
+        comp.step(X, G, 0)
+        torch.cuda.synchronize()
+        runs.append((comp, X, [comp.sweep_history(l) for l in range(len(shapes))]))
+    for (c, x, hist), sweeps in zip(runs, (16, 17, 22)):
+        for l in range(len(shapes)):
+            n, conv, h = hist[l]
+            assert n <= sweeps and (conv or n == sweeps)
+            assert h[:16] == runs[0][2][l][2][:16]
+            assert np.all(np.diff(h[8:]) <= 1e-12)           # stays converged to rounding, sweep after sweep
+            U = c.Ut(l).double()[:20]
+            assert float((U @ U.T - torch.eye(20, device="cuda", dtype=torch.float64)).abs().max()) < 1e-5
+            e = (c.E(l).double() - runs[0][0].E(l).double()).norm() / runs[0][0].E(l).double().norm()
+            assert float(e) < 1e-5
