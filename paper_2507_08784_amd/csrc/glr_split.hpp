@@ -291,23 +291,30 @@ struct SplitR {
 };
 
 // C[BM x BN] = A[BM x K] B[K x BN] (times the scales), 4 waves in a WM x WN
-// grid of TM x TN MFMA blocks each; accumulators laid out as MfmaTile's.  Two
-// copies of the slices in LDS, one barrier a slice: while a slice feeds the
-// MFMAs the next one, already in registers, is split and stored and the one
-// after it is loaded.  FLUSH: the second set of accumulators.
+// grid of TM x TN MFMA blocks each; accumulators laid out as MfmaTile's.
+// NBUF 2: two copies of the slices in LDS, one barrier a slice: while a slice
+// feeds the MFMAs the next one, already in registers, is split and stored and
+// the one after it is loaded; NBUF 1: one copy and two barriers, for tiles
+// whose two copies would leave one workgroup per CU.  A second set of
+// accumulators keeps the sums that are rounded short: kAccFlush adds the
+// products into it and it into the result every kSplitFlush slices, kAccSplit
+// keeps every product but the first pieces' in it (for contractions that the
+// caller slices itself).
 constexpr int kSplitFlush = 8;
-template <int BM, int BN, int WM, int WN, SplitFmt F, bool FLUSH = true>
+enum SplitAcc { kAccOne, kAccFlush, kAccSplit };
+template <int BM, int BN, int WM, int WN, SplitFmt F, SplitAcc ACC, int NBUF = 2>
 struct SplitTile {
   static constexpr int PIECES = split_pieces(F);
   static constexpr int WTM = BM / WM, WTN = BN / WN;
   static constexpr int TM = WTM / 32, TN = WTN / 32;
   static constexpr int SA = PIECES * BM * 64, SB = PIECES * BN * 64;
-  static constexpr int LDS_BYTES = 2 * (SA + SB);
+  static constexpr int LDS_BYTES = NBUF * (SA + SB);
+  static constexpr bool TWO = ACC != kAccOne;
   static_assert(WM * WN == 4, "4 waves");
   static_assert(TM >= 1 && TN >= 1 && WTM % 32 == 0 && WTN % 32 == 0, "32x32 blocks");
 
   f32x16 acc[TM][TN];                                // the result after run()
-  f32x16 part[FLUSH ? TM : 1][FLUSH ? TN : 1];
+  f32x16 part[TWO ? TM : 1][TWO ? TN : 1];
   int wm, wn, lane;
 
   __device__ SplitTile() {
@@ -321,7 +328,7 @@ struct SplitTile {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           acc[i][j][v] = 0.f;
-          if constexpr (FLUSH) part[i][j][v] = 0.f;
+          if constexpr (TWO) part[i][j][v] = 0.f;
         }
   }
   // tile-relative row / column of accumulator element (tm, tn, v)
@@ -352,13 +359,13 @@ struct SplitTile {
           for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-              f32x16& c = FLUSH ? part[FLUSH ? i : 0][FLUSH ? j : 0] : acc[i][j];
+              f32x16& c = (ACC == kAccFlush || (ACC == kAccSplit && s > 0)) ? part[TWO ? i : 0][TWO ? j : 0] : acc[i][j];
               c = split_mfma<F>(a[i][p], b[j][s - p], c);
             }
     }
   }
   __device__ __forceinline__ void flush() {
-    if constexpr (FLUSH) {
+    if constexpr (TWO) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -386,18 +393,32 @@ struct SplitTile {
     }
     __syncthreads();
     for (int kb = 0; kb < nk; ++kb) {
-      char* cur = smem + (kb & 1) * (SA + SB);
-      char* nxt = smem + ((kb & 1) ^ 1) * (SA + SB);
-      if (kb + 1 < nk) {
-        la.template put<F>(nxt, sa);
-        lb.template put<F>(nxt + SA, sb);
+      const bool more = kb + 1 < nk;
+      if constexpr (NBUF == 2) {
+        char* cur = smem + (kb & 1) * (SA + SB);
+        char* nxt = smem + ((kb & 1) ^ 1) * (SA + SB);
+        if (more) {
+          la.template put<F>(nxt, sa);
+          lb.template put<F>(nxt + SA, sb);
+        }
+        if (kb + 2 < nk) {
+          la.fetch((kb + 2) * kSplitBK);
+          lb.fetch((kb + 2) * kSplitBK);
+        }
+        compute(cur, cur + SA);
+      } else {
+        compute(smem, smem + SA);
+        __syncthreads();
+        if (more) {
+          la.template put<F>(smem, sa);
+          lb.template put<F>(smem + SA, sb);
+        }
+        if (kb + 2 < nk) {
+          la.fetch((kb + 2) * kSplitBK);
+          lb.fetch((kb + 2) * kSplitBK);
+        }
       }
-      if (kb + 2 < nk) {
-        la.fetch((kb + 2) * kSplitBK);
-        lb.fetch((kb + 2) * kSplitBK);
-      }
-      compute(cur, cur + SA);
-      if (FLUSH && kb % kSplitFlush == kSplitFlush - 1) flush();
+      if (ACC == kAccFlush && kb % kSplitFlush == kSplitFlush - 1) flush();
       __syncthreads();
     }
     flush();

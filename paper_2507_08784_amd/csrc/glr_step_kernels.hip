@@ -134,7 +134,7 @@ __device__ __forceinline__ void sel_scores_at(const float* __restrict__ Mbar, co
                                               int64_t D, float* __restrict__ part, uint32_t mat, uint32_t tstep,
                                               uint32_t key0, uint32_t key1, const float* __restrict__ amax, int bx,
                                               int by) {
-  using T = SplitTile<SEL_BM, SEL_BN, 2, 2, BF16 ? kBf16 : kF16x2, !BF16>;
+  using T = SplitTile<SEL_BM, SEL_BN, 2, 2, BF16 ? kBf16 : kF16x2, BF16 ? kAccOne : kAccFlush>;
   __shared__ __align__(16) char smem[T::LDS_BYTES];
   __shared__ float red[2][SEL_BN];
   const int m0 = by * SEL_BM;   // rows: b in [0, D)
@@ -458,6 +458,67 @@ k_proj(const ST* __restrict__ G, const ST* __restrict__ E, const float* __restri
   }
   proj_at<BM, BN, WM, WN, RIGHT, FLUSH, ST, VEC>(G, E, Ut, J, Qpart, d, D, r, N, kslice, bx, by, bz);
 }
+// Above rank 64 the projection is bound by the matrix cores: the same product
+// on the bf16 ones (kBf16x3: M^(i) has no scale known in advance, and Q's
+// columns are held to their own size), the 1024-term slices of d added in fp64
+// by the launch that packs Q.  11008 x 4096, r = 128: 1000 -> 757 us (122
+// TFLOP/s of fp32 products), the same with bf16 storage 1030 -> 756 us,
+// 8192 x 28672, r = 256, N = 4: 5.2 -> 3.7 ms, against the fp32 MFMA.
+template <int BM, int WM, int WN, bool RIGHT, class ST>
+struct ProjSplit {
+  static constexpr int BN = 64;
+  using T = SplitTile<BM, BN, WM, WN, kBf16x3, kAccSplit, BM == 256 ? 1 : 2>;
+};
+template <int BM, int WM, int WN, bool RIGHT, class ST>
+__device__ __forceinline__ void proj_split_at(const ST* __restrict__ G, const ST* __restrict__ E,
+                                              const float* __restrict__ Ut, const int* __restrict__ J,
+                                              float* __restrict__ Qpart, int64_t d, int64_t D, int r, int N, int kslice,
+                                              int bx, int by, int bz) {
+  using PS = ProjSplit<BM, WM, WN, RIGHT, ST>;
+  using T = typename PS::T;
+  constexpr int BN = PS::BN;
+  __shared__ __align__(16) char smem[T::LDS_BYTES];
+  const int n0 = bx * BN, m0 = by * BM;   // b, rank index
+  const int w = bz % N, z = bz / N;       // worker, slice of the d contraction
+  const int64_t k0 = (int64_t)z * kslice, dD = d * D;
+  const int klen = (int)(d - k0 < kslice ? d - k0 : kslice);
+  const ST* Gi = G + (int64_t)w * dD;
+  const ST* Ei = E + (int64_t)w * dD;
+  T tile;
+  SplitK<BM, false, true> la(Ut + k0, nullptr, d * d - k0, d, m0, r, klen, J);
+  if (RIGHT) {
+    // M^(i) oriented: Mo[a][b] = M[b][a], M is D x d row-major
+    SplitK<BN, true, false, ST> lb(Gi + k0, Ei + k0, dD - k0, d, n0, (int)D, klen);
+    tile.run(la, lb, klen, smem);
+  } else {
+    SplitR<BN, true, false, ST> lb(Gi + k0 * D, Ei + k0 * D, dD - k0 * D, D, n0, (int)D, klen);
+    tile.run(la, lb, klen, smem);
+  }
+  float* Qz = Qpart + ((int64_t)z * N + w) * r * D;
+#pragma unroll
+  for (int tm = 0; tm < T::TM; ++tm)
+#pragma unroll
+    for (int tn = 0; tn < T::TN; ++tn) {
+      const int b = n0 + tile.col(tn);
+      if (b >= D) continue;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int k = m0 + tile.row(tm, v);
+        if (k < r) Qz[(int64_t)k * D + b] = tile.acc[tm][tn][v];
+      }
+    }
+}
+// rank tiles over the same columns run 8 blocks apart (see k_proj)
+template <int BM, int WM, int WN, bool RIGHT, class ST>
+__global__ void __launch_bounds__(256, 2)
+k_proj_split(const ST* __restrict__ G, const ST* __restrict__ E, const float* __restrict__ Ut,
+             const int* __restrict__ J, float* __restrict__ Qpart, int64_t d, int64_t D, int r, int N, int kslice,
+             int gx, int gy, int ntiles) {
+  const int L = blockIdx.x, xcd = L & 7, slot = L >> 3;
+  const int by = slot % gy, tile = (slot / gy) * 8 + xcd;
+  if (tile >= ntiles) return;
+  proj_split_at<BM, WM, WN, RIGHT, ST>(G, E, Ut, J, Qpart, d, D, r, N, kslice, tile % gx, by, tile / gx);
+}
 // the conditions under which every loader of the projection takes its
 // float4 path: rows of U^T, G and E in whole float4s (d and D multiples of
 // 4, so every slice start and length is one), and the arrays aligned
@@ -504,8 +565,21 @@ static hipError_t launch_proj_st(const MatView& v, hipStream_t s) {
   // slower than the 64 x 64 one with them (fewer, longer blocks).
   if (r <= 32) GLR_PROJ(32, 128, 1, 4, true);
   else if (r <= kProjFlushRank) GLR_PROJ(64, 64, 2, 2, true);
-  else if (r <= kProjWideRank) GLR_PROJ(128, 64, 2, 2, false);
-  else GLR_PROJ(256, 64, 4, 1, false);
+#define GLR_PROJS1(BM, WM, WN, R)                                                                          \
+  hipLaunchKernelGGL((k_proj_split<BM, WM, WN, R, ST>), gr, dim3(kThreads), 0, s, G, E, v.Ut, v.J, v.Qpart, \
+                     v.d, v.D, r, v.N, (int)kslice, gx, gy, ntiles)
+#define GLR_PROJS(BM, WM, WN)                                         \
+  do {                                                                \
+    const int gx = (int)((v.D + 63) / 64), gy = (r + BM - 1) / BM;    \
+    const int ntiles = gx * (int)grid.z;                              \
+    const dim3 gr((unsigned)(((ntiles + 7) / 8) * 8 * gy));           \
+    if (v.right) GLR_PROJS1(BM, WM, WN, true);                        \
+    else GLR_PROJS1(BM, WM, WN, false);                               \
+  } while (0)
+  else if (r <= kProjWideRank) GLR_PROJS(128, 2, 2);
+  else GLR_PROJS(256, 4, 1);
+#undef GLR_PROJS
+#undef GLR_PROJS1
 #undef GLR_PROJ
 #undef GLR_PROJ1
   return hipGetLastError();
@@ -1307,12 +1381,12 @@ __device__ __forceinline__ int group_find(const int* __restrict__ first, int num
   return lo;
 }
 
-// projection tiles of rank r: BM x BN, WM x WN waves, fp64 flush of the slices
+// projection tiles of rank r (at most kGroupMaxRank): BM x BN, WM x WN waves,
+// fp64 flush of the slices (false: the split product)
 #define GLR_PROJ_TIERS(X)                                   \
   if (r <= 32) X(32, 128, 1, 4, true);                      \
   else if (r <= kProjFlushRank) X(64, 64, 2, 2, true);      \
-  else if (r <= kProjWideRank) X(128, 64, 2, 2, false);     \
-  else X(256, 64, 4, 1, false)
+  else X(128, 64, 2, 2, false)
 
 template <class ST>
 __global__ void k_g_ef_mean(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num, int check) {
@@ -1341,16 +1415,19 @@ k_g_topr(const GroupMat* __restrict__ gm, int approx) {
 }
 
 template <int BM, int BN, int WM, int WN, bool RIGHT, bool FLUSH, class ST>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, FLUSH ? 1 : 2)
 k_g_proj(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num) {
   const int m = group_find(first, num, blockIdx.x);
   const GroupMat& g = gm[m];
   const MatView& v = g.v;
   const int gx = (int)((v.D + BN - 1) / BN), gy = (v.r + BM - 1) / BM;
   const int local = blockIdx.x - first[m], rest = local / gx;
-  proj_at<BM, BN, WM, WN, RIGHT, FLUSH, ST>(static_cast<const ST*>(v.G), static_cast<const ST*>(v.E), v.Ut, v.J,
-                                            v.Qpart, v.d, v.D, v.r, v.N, g.kslice, local % gx,
-                                            rest % gy, rest / gy);
+  if constexpr (FLUSH)
+    proj_at<BM, BN, WM, WN, RIGHT, true, ST>(static_cast<const ST*>(v.G), static_cast<const ST*>(v.E), v.Ut, v.J,
+                                             v.Qpart, v.d, v.D, v.r, v.N, g.kslice, local % gx, rest % gy, rest / gy);
+  else
+    proj_split_at<BM, WM, WN, RIGHT, ST>(static_cast<const ST*>(v.G), static_cast<const ST*>(v.E), v.Ut, v.J, v.Qpart,
+                                         v.d, v.D, v.r, v.N, g.kslice, local % gx, rest % gy, rest / gy);
 }
 
 template <int KS>

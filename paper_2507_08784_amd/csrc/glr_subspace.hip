@@ -169,7 +169,7 @@ k_gemm_split(const float* __restrict__ A, int64_t lda, const float* __restrict__
   const int grp = (slot / gy) * 8 + (L & 7), bxy = slot % gy;
   if (grp >= ngroups) return;
   const int bxx = grp % gx, bz = grp / gx;
-  using T = SplitTile<BM, BN, WM, WN, kF16x2>;
+  using T = SplitTile<BM, BN, WM, WN, kF16x2, kAccFlush>;
   __shared__ __align__(16) char smem[T::LDS_BYTES];
   __shared__ float red[4];
   const int n0 = bxx * BN, m0 = bxy * BM;
