@@ -124,14 +124,30 @@ __device__ __forceinline__ BufRsrc split_rsrc(const T* p, int64_t count) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), (short)0, (int)(uint32_t)(count * (int64_t)sizeof(T)),
                                            0x00020000);
 }
-// W consecutive elements (W 2 or 4) at byte offset off: any element
-// alignment; elements past the array read 0
+// whether the elements of a row of the operand at p may be loaded by dwords: a
+// buffer load of dwords takes any dword address, but drops the low two bits of
+// a bf16 element at an odd index
+template <class ST>
+__device__ __forceinline__ bool split_dwords(const ST* p, const ST* p2, int64_t ld) {
+  if constexpr (sizeof(ST) == 4) return true;
+  else return ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(p2) | (uintptr_t)(2 * ld)) & 3) == 0;
+}
+// W consecutive elements (W 2 or 4) at byte offset off; elements past the
+// array read 0.  DWORDS: see split_dwords
 template <class ST, int W>
 struct SplitRaw {
   static constexpr int DW = W * (int)sizeof(ST) / 4;   // dwords
   uint32_t v[DW];
+  template <bool DWORDS = true>
   __device__ __forceinline__ void load(BufRsrc r, uint32_t off) {
-    if constexpr (DW == 4) {
+    if constexpr (!DWORDS && sizeof(ST) == 2) {
+#pragma unroll
+      for (int i = 0; i < DW; ++i) {
+        const uint32_t lo = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)(off + 4 * i), 0, 0);
+        const uint32_t hi = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)(off + 4 * i + 2), 0, 0);
+        v[i] = lo | (hi << 16);
+      }
+    } else if constexpr (DW == 4) {
       const auto x = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
       v[0] = x[0]; v[1] = x[1]; v[2] = x[2]; v[3] = x[3];
     } else if constexpr (DW == 2) {
@@ -161,6 +177,7 @@ struct SplitK {
   static_assert(NV >= 1 && R * 8 % kThreads == 0, "whole items per thread");
   BufRsrc rs, rs2;
   int K, kend;
+  bool dwords;
   uint32_t off[NV];
   SplitRaw<ST, 4> a[NV], b[FUSED ? NV : 1];
   // count: elements of the operand's array from base
@@ -169,6 +186,7 @@ struct SplitK {
       : K(K_), kend(0) {
     rs = split_rsrc(base, count);
     rs2 = FUSED ? split_rsrc(base2, count) : rs;
+    dwords = split_dwords(base, FUSED ? base2 : base, ld);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int idx = threadIdx.x + kThreads * i;
@@ -178,14 +196,19 @@ struct SplitK {
       off[i] = (uint32_t)((int64_t)row * ld + 4 * (idx & 7)) * (uint32_t)sizeof(ST);
     }
   }
-  __device__ __forceinline__ void fetch(int k0) {
-    kend = K - k0;
+  template <bool DWORDS>
+  __device__ __forceinline__ void load(int k0) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const uint32_t o = off[i] + (uint32_t)k0 * (uint32_t)sizeof(ST);
-      a[i].load(rs, o);
-      if constexpr (FUSED) b[i].load(rs2, o);
+      a[i].template load<DWORDS>(rs, o);
+      if constexpr (FUSED) b[i].template load<DWORDS>(rs2, o);
     }
+  }
+  __device__ __forceinline__ void fetch(int k0) {
+    kend = K - k0;
+    if (sizeof(ST) == 4 || dwords) load<true>(k0);
+    else load<false>(k0);
   }
   template <SplitFmt F>
   __device__ __forceinline__ void put(char* s, float scale) const {
@@ -226,6 +249,7 @@ struct SplitR {
   const int* rows;
   uint32_t ldb;
   int K, kend;
+  bool dwords;
   uint32_t col[NV];
   SplitRaw<ST, RW> a[NV][4], b[FUSED ? NV : 1][4];
   static __device__ __forceinline__ int item_r(int idx) { return RW * ((idx / (8 * RL)) * RL + idx % RL); }
@@ -235,6 +259,7 @@ struct SplitR {
       : rows(rows_), K(K_), kend(0) {
     rs = split_rsrc(base, count);
     rs2 = FUSED ? split_rsrc(base2, count) : rs;
+    dwords = split_dwords(base, FUSED ? base2 : base, ld);
     ldb = (uint32_t)(ld * (int64_t)sizeof(ST));
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
@@ -252,13 +277,18 @@ struct SplitR {
         const int k = k0 + 4 * item_q(threadIdx.x + kThreads * i) + j, kc = k < K ? k : K - 1;
         kr[i][j] = GATHER ? rows[kc] : kc;
       }
+    if (sizeof(ST) == 4 || dwords) load<true>(kr);
+    else load<false>(kr);
+  }
+  template <bool DWORDS>
+  __device__ __forceinline__ void load(const int (&kr)[NV][4]) {
 #pragma unroll
     for (int i = 0; i < NV; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const uint32_t o = (uint32_t)kr[i][j] * ldb + col[i];
-        a[i][j].load(rs, o);
-        if constexpr (FUSED) b[i][j].load(rs2, o);
+        a[i][j].template load<DWORDS>(rs, o);
+        if constexpr (FUSED) b[i][j].template load<DWORDS>(rs2, o);
       }
   }
   template <SplitFmt F>

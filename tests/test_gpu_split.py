@@ -56,7 +56,7 @@ def test_scores_against_fp64(gpu_lib, shape, select, scale):
 # and the fp32 pass above rank 256); ragged tiles on both sides; columns of
 # very different size, whose residuals are held to their own column's size
 @pytest.mark.parametrize("rank", [1, 15, 16, 17, 33, 64, 65, 128, 130, 256, 257])
-@pytest.mark.parametrize("shape", [(299, 330), (330, 299)])
+@pytest.mark.parametrize("shape", [(299, 330), (330, 299), (297, 331)])
 @pytest.mark.parametrize("workers,store", [(1, "fp32"), (3, "fp32"), (5, "bf16")])
 def test_residual_against_fp64(gpu_lib, rank, shape, workers, store):
     m, n = shape
