@@ -221,7 +221,8 @@ struct GroupMat {
   int splits, kslice;
 };
 // the kernels of a grouped selection step, each one launch over all matrices
-enum { kGrpEfMean = 0, kGrpSelScores, kGrpProj, kGrpRbar, kGrpResid, kGrpKinds };
+// (the scores with either tile)
+enum { kGrpEfMean = 0, kGrpSel128, kGrpSel64, kGrpProj, kGrpRbar, kGrpResid, kGrpKinds };
 struct GroupPlan {
   const GroupMat* gm = nullptr;   // num entries
   const int* first = nullptr;     // kGrpKinds tables of num + 1 first blocks

@@ -194,7 +194,7 @@ WsLayout ws_layout(const glr_config* c, int first, int last) {
     } else {
       mx(mx_Q, (uint64_t)c->num_workers * (uint64_t)x.r * (uint64_t)x.D);
     }
-    mx(mx_lam, (uint64_t)((x.D + 127) / 128) * (uint64_t)x.d);
+    mx(mx_lam, (uint64_t)((x.D + 63) / 64) * (uint64_t)x.d);
     mx(mx_d, (uint64_t)x.d);
     if (use_subspace(c->tau, x.r, x.d)) {
       const int Ki = sub_block(x.r, x.d);

@@ -127,29 +127,36 @@ hipError_t launch_ef_mean(const MatView& v, bool check_finite, hipStream_t s) {
 // 4096 x 11008: 3430 -> 1378 us, 768 x 768: 85 -> 52 us, against the fp32 MFMA
 // with 16-byte loads; the scores' error against 64 bits 8.1e-7 -> 2.3e-7.
 // ---------------------------------------------------------------------------
-constexpr int SEL_BM = 128, SEL_BN = 128;
+// Tiles of 128 x 128, or of 64 x 64 when the launch has fewer than kSelFew of
+// the large ones, one for each CU: below that part of the chip stays idle while
+// each workgroup works through its d-long contraction and its share of the
+// normals.  1011 x 2053 (136 large tiles): 49 us large, 38 small; 256 x 128
+// (2): 16.5 and 7.9; but the five left-sided matrices of an encoder layer (288)
+// ran 3 % faster in large tiles.  Both fold 32 rows at a time in one order, so
+// the scores do not depend on the choice.
+constexpr int kSelFew = 256;
 
-template <bool RIGHT, bool APPROX, bool BF16>
+template <int BT, bool RIGHT, bool APPROX, bool BF16>
 __device__ __forceinline__ void sel_scores_at(const float* __restrict__ Mbar, const float* __restrict__ Ut, int64_t d,
                                               int64_t D, float* __restrict__ part, uint32_t mat, uint32_t tstep,
                                               uint32_t key0, uint32_t key1, const float* __restrict__ amax, int bx,
                                               int by) {
-  using T = SplitTile<SEL_BM, SEL_BN, 2, 2, BF16 ? kBf16 : kF16x2, BF16 ? kAccOne : kAccFlush>;
+  using T = SplitTile<BT, BT, 2, 2, BF16 ? kBf16 : kF16x2, BF16 ? kAccOne : kAccFlush>;
   __shared__ __align__(16) char smem[T::LDS_BYTES];
-  __shared__ float red[2][SEL_BN];
-  const int m0 = by * SEL_BM;   // rows: b in [0, D)
-  const int n0 = bx * SEL_BN;   // cols: j in [0, d)
+  __shared__ float red[2][BT];
+  const int m0 = by * BT;   // rows: b in [0, D)
+  const int n0 = bx * BT;   // cols: j in [0, d)
   const int em = BF16 ? 0 : split_block_exp({amax, ef_mean_blocks(d * D), 1.f, 0}, red[0]);
   const float sm = ldexpf(1.f, em), su = BF16 ? 1.f : ldexpf(1.f, kUnitExp);
   T tile;
-  SplitK<SEL_BN, false, false> lb(Ut, nullptr, d * d, d, n0, (int)d, (int)d);
+  SplitK<BT, false, false> lb(Ut, nullptr, d * d, d, n0, (int)d, (int)d);
   if (RIGHT) {
     // Mo[a][b] = Mbar[b][a] : A[b][a] contiguous along a
-    SplitK<SEL_BM, false, false> la(Mbar, nullptr, d * D, d, m0, (int)D, (int)d);
+    SplitK<BT, false, false> la(Mbar, nullptr, d * D, d, m0, (int)D, (int)d);
     tile.run(la, lb, (int)d, smem, sm, su);
   } else {
     // Mo[a][b] = Mbar[a][b] : A[b][a] contiguous along b
-    SplitR<SEL_BM, false, false> la(Mbar, nullptr, d * D, D, m0, (int)D, (int)d);
+    SplitR<BT, false, false> la(Mbar, nullptr, d * D, D, m0, (int)D, (int)d);
     tile.run(la, lb, (int)d, smem, sm, su);
   }
   const int lane = lane_id();
@@ -157,10 +164,11 @@ __device__ __forceinline__ void sel_scores_at(const float* __restrict__ Mbar, co
 #pragma unroll
   for (int tn = 0; tn < T::TN; ++tn) {
     const int j = n0 + tile.col(tn);
-    float acc = 0.f;
-    if (j < d) {
+    float total = 0.f;
 #pragma unroll
-      for (int tm = 0; tm < T::TM; ++tm) {
+    for (int tm = 0; tm < T::TM; ++tm) {
+      float acc = 0.f;   // 32 rows of column j
+      if (j < d) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int b0 = m0 + tile.row(tm, 4 * g);   // multiple of 4
@@ -180,32 +188,49 @@ __device__ __forceinline__ void sel_scores_at(const float* __restrict__ Mbar, co
           }
         }
       }
+      acc += __shfl_xor(acc, 32, 64);
+      total = tm == 0 ? acc : total + acc;
     }
-    acc += __shfl_xor(acc, 32, 64);
-    if (lane < 32) red[tile.wm][tile.wn * T::WTN + tn * 32 + lane] = acc;
+    if (lane < 32) red[tile.wm][tile.wn * T::WTN + tn * 32 + lane] = total;
   }
   __syncthreads();
-  if (threadIdx.x < SEL_BN) {
+  // one partial for 64 rows: the two waves' of a small tile, each wave's of a large one
+  if (threadIdx.x < BT) {
     const int j = n0 + threadIdx.x;
-    if (j < d) part[(int64_t)by * d + j] = red[0][threadIdx.x] + red[1][threadIdx.x];
+    if (j < d) {
+      if (BT == 64) {
+        part[(int64_t)by * d + j] = red[0][threadIdx.x] + red[1][threadIdx.x];
+      } else {
+        part[(int64_t)(2 * by) * d + j] = red[0][threadIdx.x];
+        if (m0 + 64 < D) part[(int64_t)(2 * by + 1) * d + j] = red[1][threadIdx.x];
+      }
+    }
   }
 }
-template <bool RIGHT, bool APPROX, bool BF16>
-__global__ void __launch_bounds__(256, 2)
+template <int BT, bool RIGHT, bool APPROX, bool BF16>
+__global__ void __launch_bounds__(256, BT == 64 ? 4 : 2)
 k_sel_scores(const float* __restrict__ Mbar, const float* __restrict__ Ut, int64_t d, int64_t D,
              float* __restrict__ part, uint32_t mat, uint32_t tstep, uint32_t key0, uint32_t key1,
              const float* __restrict__ amax) {
-  sel_scores_at<RIGHT, APPROX, BF16>(Mbar, Ut, d, D, part, mat, tstep, key0, key1, amax, blockIdx.x, blockIdx.y);
+  sel_scores_at<BT, RIGHT, APPROX, BF16>(Mbar, Ut, d, D, part, mat, tstep, key0, key1, amax, blockIdx.x, blockIdx.y);
 }
 
+static int sel_tiles(int64_t d, int64_t D, int bt) { return (int)(((d + bt - 1) / bt) * ((D + bt - 1) / bt)); }
 hipError_t launch_sel_scores(const MatView& v, bool approx, bool bf16, uint64_t seed, int64_t t, hipStream_t s) {
   if (bf16 && !approx) return hipErrorInvalidValue;
-  dim3 grid((unsigned)((v.d + SEL_BN - 1) / SEL_BN), (unsigned)((v.D + SEL_BM - 1) / SEL_BM));
+  const bool few = sel_tiles(v.d, v.D, 128) < kSelFew;
+  const int bt = few ? 64 : 128;
+  dim3 grid((unsigned)((v.d + bt - 1) / bt), (unsigned)((v.D + bt - 1) / bt));
   const uint32_t k0 = (uint32_t)(seed & 0xFFFFFFFFu), k1 = (uint32_t)(seed >> 32);
   const uint32_t tt = (uint32_t)((uint64_t)t & 0xFFFFFFFFu);
-#define GLR_SEL(R, A, B)                                                                         \
-  hipLaunchKernelGGL((k_sel_scores<R, A, B>), grid, dim3(kThreads), 0, s, v.Mbar, v.Ut, v.d, v.D, \
+#define GLR_SEL1(T, R, A, B)                                                                         \
+  hipLaunchKernelGGL((k_sel_scores<T, R, A, B>), grid, dim3(kThreads), 0, s, v.Mbar, v.Ut, v.d, v.D, \
                      v.lam_part, (uint32_t)v.mat, tt, k0, k1, v.amax)
+#define GLR_SEL(R, A, B)                    \
+  do {                                      \
+    if (few) GLR_SEL1(64, R, A, B);         \
+    else GLR_SEL1(128, R, A, B);            \
+  } while (0)
   if (v.right) {
     if (bf16) GLR_SEL(true, true, true);
     else if (approx) GLR_SEL(true, true, false);
@@ -216,6 +241,7 @@ hipError_t launch_sel_scores(const MatView& v, bool approx, bool bf16, uint64_t 
     else GLR_SEL(false, false, false);
   }
 #undef GLR_SEL
+#undef GLR_SEL1
   return hipGetLastError();
 }
 
@@ -363,7 +389,7 @@ __global__ void k_iota(int* J, int r) {
 }
 
 hipError_t launch_topr(const MatView& v, bool approx, hipStream_t s) {
-  const int ntiles = (int)((v.D + SEL_BM - 1) / SEL_BM);
+  const int ntiles = (int)((v.D + 63) / 64);
   const bool own = v.d * ntiles <= kToprFold;
   if (!own)
     hipLaunchKernelGGL(k_fold_scores, dim3((unsigned)((v.d + 63) / 64)), dim3(64), 0, s, v.lam_part, ntiles,
@@ -1396,14 +1422,14 @@ __global__ void k_g_ef_mean(const GroupMat* __restrict__ gm, const int* __restri
              blockIdx.x - first[m], first[m + 1] - first[m]);
 }
 
-template <bool RIGHT, bool APPROX, bool BF16>
-__global__ void __launch_bounds__(256, 2)
+template <int BT, bool RIGHT, bool APPROX, bool BF16>
+__global__ void __launch_bounds__(256, BT == 64 ? 4 : 2)
 k_g_sel_scores(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num, uint32_t tstep,
                uint32_t key0, uint32_t key1) {
   const int m = group_find(first, num, blockIdx.x);
   const MatView& v = gm[m].v;
-  const int local = blockIdx.x - first[m], gx = (int)((v.d + SEL_BN - 1) / SEL_BN);
-  sel_scores_at<RIGHT, APPROX, BF16>(v.Mbar, v.Ut, v.d, v.D, v.lam_part, (uint32_t)v.mat, tstep, key0, key1,
+  const int local = blockIdx.x - first[m], gx = (int)((v.d + BT - 1) / BT);
+  sel_scores_at<BT, RIGHT, APPROX, BF16>(v.Mbar, v.Ut, v.d, v.D, v.lam_part, (uint32_t)v.mat, tstep, key0, key1,
                                      v.amax, local % gx, local / gx);
 }
 
@@ -1411,7 +1437,7 @@ k_g_sel_scores(const GroupMat* __restrict__ gm, const int* __restrict__ first, i
 __global__ void __launch_bounds__(kToprThreads)
 k_g_topr(const GroupMat* __restrict__ gm, int approx) {
   const MatView& v = gm[blockIdx.x].v;
-  topr_at(v.lam_part, (int)((v.D + SEL_BM - 1) / SEL_BM), true, approx, (int)v.d, v.score, v.r, v.J);
+  topr_at(v.lam_part, (int)((v.D + 63) / 64), true, approx, (int)v.d, v.score, v.r, v.J);
 }
 
 template <int BM, int BN, int WM, int WN, bool RIGHT, bool FLUSH, class ST>
@@ -1457,7 +1483,8 @@ void group_fill(GroupMat& g, int (&blocks)[kGrpKinds]) {
   g.splits = proj_splits(v.d, v.D, r, v.N);
   g.kslice = proj_kslice(v.d, v.D, r, v.N);
   blocks[kGrpEfMean] = ef_mean_blocks(v.m * v.n);
-  blocks[kGrpSelScores] = (int)(((v.d + SEL_BN - 1) / SEL_BN) * ((v.D + SEL_BM - 1) / SEL_BM));
+  blocks[kGrpSel128] = sel_tiles(v.d, v.D, 128);
+  blocks[kGrpSel64] = sel_tiles(v.d, v.D, 64);
   int proj = 0;
 #define GLR_PROJ_BLOCKS(BM, BN, WM, WN, FL) proj = (int)(((v.D + BN - 1) / BN) * ((r + BM - 1) / BM) * v.N * g.splits)
   GLR_PROJ_TIERS(GLR_PROJ_BLOCKS);
@@ -1481,9 +1508,14 @@ static hipError_t launch_group_select_st(const GroupPlan& gp, bool check_finite,
   if (part == 1) return hipGetLastError();
   const uint32_t k0 = (uint32_t)(seed & 0xFFFFFFFFu), k1 = (uint32_t)(seed >> 32);
   const uint32_t tt = (uint32_t)((uint64_t)t & 0xFFFFFFFFu);
-#define GLR_GSEL(R, A, B)                                                                                   \
-  hipLaunchKernelGGL((k_g_sel_scores<R, A, B>), grid(kGrpSelScores), dim3(kThreads), 0, s, gp.gm,          \
-                     table(kGrpSelScores), num, tt, k0, k1)
+  const bool few = gp.total[kGrpSel128] < kSelFew;
+#define GLR_GSEL1(T, K, R, A, B) \
+  hipLaunchKernelGGL((k_g_sel_scores<T, R, A, B>), grid(K), dim3(kThreads), 0, s, gp.gm, table(K), num, tt, k0, k1)
+#define GLR_GSEL(R, A, B)                            \
+  do {                                               \
+    if (few) GLR_GSEL1(64, kGrpSel64, R, A, B);      \
+    else GLR_GSEL1(128, kGrpSel128, R, A, B);        \
+  } while (0)
   if (right) {
     if (bf16) GLR_GSEL(true, true, true);
     else if (approx) GLR_GSEL(true, true, false);
@@ -1494,6 +1526,7 @@ static hipError_t launch_group_select_st(const GroupPlan& gp, bool check_finite,
     else GLR_GSEL(false, false, false);
   }
 #undef GLR_GSEL
+#undef GLR_GSEL1
   hipLaunchKernelGGL(k_g_topr, dim3((unsigned)num), dim3(kToprThreads), 0, s, gp.gm, approx ? 1 : 0);
 #define GLR_GPROJ(BM, BN, WM, WN, FL)                                                                       \
   do {                                                                                                      \
