@@ -39,7 +39,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK = 8.0e12           # bytes/s
 FP32_MFMA_PEAK = 157.3e12   # flop/s, dense
 FP64_MFMA_PEAK = 78.6e12
-BF16_MFMA_PEAK = 2.5e15     # dense bf16 (the selection products of the approx_bf16 mode)
+BF16_MFMA_PEAK = 2.5e15     # dense bf16 and fp16 (split fp32 products; the approx_bf16 mode)
 METRIC = "ms/step and effective HBM GB/s for compress+EF+update; % of roofline"
 
 
@@ -119,11 +119,9 @@ def group_work(wl, name, esz=4):
         elif name == "resid_opt":
             # G, E read and E written per worker; Ebar written (the mean of
             # the stored residuals, summed in registers); X and the optimizer
-            # state read and written.  Products: P Q^(i) per worker, and
-            # Ghat = P Rbar as a product of its own up to rank 128 (above it
-            # Ghat is the mean of the workers' products)
-            prods = N if r > 128 else N + 1
-            w = ((3.0 * esz * N + 4 + (24 if adam else 16)) * mn + 4.0 * N * r * D, 2.0 * r * d * D * prods, 0, 0)
+            # state read and written.  Products: P Q^(i) per worker (Ghat is
+            # the mean of the workers' products)
+            w = ((3.0 * esz * N + 4 + (24 if adam else 16)) * mn + 4.0 * N * r * D, 2.0 * r * d * D * N, 0, 0)
         elif name.startswith("jac_") and not sub:
             w = jacobi_work(name[4:], d)
         elif name.startswith("rr_") and sub:
@@ -141,6 +139,23 @@ def group_work(wl, name, esz=4):
     return tuple(x / count for x in tot)
 
 
+def product_peak(wl, name, select):
+    """Dense matrix-core rate a group's fp32 products run against: split into
+    two fp16 pieces (three products) in the scores, the tau = 1 products and
+    the residuals, into three bf16 pieces (six products) in the projection
+    above rank 64 and the residuals up to rank 16, rounded to bf16 in the bf16
+    selection mode, else the fp32 matrix cores."""
+    if name == "select":
+        return BF16_MFMA_PEAK if select == "approx_bf16" else BF16_MFMA_PEAK / 3
+    if name in ("sub_z", "sub_p"):
+        return BF16_MFMA_PEAK / 3
+    if name == "resid_opt" and wl.rank <= 256:
+        return BF16_MFMA_PEAK / (6 if wl.rank <= 16 else 3)
+    if name == "proj" and wl.rank > 64:
+        return BF16_MFMA_PEAK / 6
+    return FP32_MFMA_PEAK
+
+
 def roofline_entry(wl, name, total_ms, launches, select="approx", esz=4):
     work = group_work(wl, name, esz)
     if work is None or launches == 0 or total_ms <= 0:
@@ -148,9 +163,7 @@ def roofline_entry(wl, name, total_ms, launches, select="approx", esz=4):
     avg_s = total_ms / 1e3 / launches
     byts, f32, f64, alu = work
     t_hbm = byts / HBM_PEAK
-    # the approx_bf16 selection runs its products on the bf16 matrix cores
-    f32_peak = BF16_MFMA_PEAK if (name == "select" and select == "approx_bf16") else FP32_MFMA_PEAK
-    t_mfma = f32 / f32_peak + f64 / FP64_MFMA_PEAK
+    t_mfma = f32 / product_peak(wl, name, select) + f64 / FP64_MFMA_PEAK
     t_alu = alu / FP64_ALU_PEAK
     base = {"kernel": name, "avg_us": avg_s * 1e6, "launches": launches,
             "bytes_per_launch": byts, "flops_per_launch": f32 + f64 + alu}
@@ -184,7 +197,7 @@ def source_sha256(name):
     device headers): a traffic figure applies only to the code it was taken on."""
     src = os.path.join(ROOT, "paper_2507_08784_amd", "csrc")
     h = hashlib.sha256()
-    for f in (KERNEL_SOURCES[name], "glr_device.hpp", "glr_internal.hpp"):
+    for f in (KERNEL_SOURCES[name], "glr_device.hpp", "glr_split.hpp", "glr_internal.hpp"):
         with open(os.path.join(src, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

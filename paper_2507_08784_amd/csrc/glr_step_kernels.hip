@@ -410,7 +410,7 @@ hipError_t launch_iota_J(const MatView& v, hipStream_t s) {
 // and E in the storage type ST, widened to fp32 as they load).  VEC: every
 // operand slice loads as whole float4s (proj_vec on the host).
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int WM, int WN, bool RIGHT, bool FLUSH, class ST, bool VEC = false>
+template <int BM, int BN, int WM, int WN, bool RIGHT, class ST, bool VEC = false>
 __device__ __forceinline__ void proj_at(const ST* __restrict__ G, const ST* __restrict__ E,
                                         const float* __restrict__ Ut, const int* __restrict__ J,
                                         float* __restrict__ Qpart, int64_t d, int64_t D, int r, int N, int kslice,
@@ -428,26 +428,21 @@ __device__ __forceinline__ void proj_at(const ST* __restrict__ G, const ST* __re
   const ST* Ei = E + (int64_t)w * dD;
   T tile;
   // fp32 accumulators are added into fp64 ones every 512 terms of the slice
-  // (FLUSH), or the slice itself is at most 512 terms
-  double dacc[FLUSH ? T::TM : 1][FLUSH ? T::TN : 1][16];
-  if (FLUSH) {
+  double dacc[T::TM][T::TN][16];
 #pragma unroll
-    for (int tm = 0; tm < T::TM; ++tm)
+  for (int tm = 0; tm < T::TM; ++tm)
 #pragma unroll
-      for (int tn = 0; tn < T::TN; ++tn)
+    for (int tn = 0; tn < T::TN; ++tn)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) dacc[FLUSH ? tm : 0][FLUSH ? tn : 0][v] = 0.0;
-  }
+      for (int v = 0; v < 16; ++v) dacc[tm][tn][v] = 0.0;
   LoadK<BM, 32, false, true, float, VEC> la(Ut + k0, nullptr, d, m0, r, klen, J);
   if (RIGHT) {
     // M^(i) oriented: Mo[a][b] = M[b][a], M is D x d row-major
     LoadK<BN, 32, true, false, ST, VEC> lb(Gi + k0, Ei + k0, d, n0, (int)D, klen, nullptr);
-    if constexpr (FLUSH) tile.run(la, lb, klen, smem, dacc);
-    else tile.run(la, lb, klen, smem);
+    tile.run(la, lb, klen, smem, dacc);
   } else {
     LoadR<BN, 32, true, false, ST, VEC> lb(Gi + k0 * D, Ei + k0 * D, D, n0, (int)D, klen);
-    if constexpr (FLUSH) tile.run(la, lb, klen, smem, dacc);
-    else tile.run(la, lb, klen, smem);
+    tile.run(la, lb, klen, smem, dacc);
   }
   float* Qz = Qpart + ((int64_t)z * N + w) * r * D;
 #pragma unroll
@@ -459,30 +454,15 @@ __device__ __forceinline__ void proj_at(const ST* __restrict__ G, const ST* __re
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int k = m0 + tile.row(tm, v);
-        if (k < r) Qz[(int64_t)k * D + b] = FLUSH ? (float)dacc[FLUSH ? tm : 0][FLUSH ? tn : 0][v] : tile.acc[tm][tn][v];
+        if (k < r) Qz[(int64_t)k * D + b] = (float)dacc[tm][tn][v];
       }
     }
 }
-// gy > 1 (several rank tiles over the same columns of G and E): a 1-D grid
-// in which the gy rank tiles of a (column tile, worker, slice) triple are 8
-// blocks apart, so they run on the same XCD at the same time and the second
-// read of those columns hits that XCD's L2 (blocks go to the XCDs in turn);
-// gy = 1: the 3-D grid (x column tiles, z worker and slice)
-template <int BM, int BN, int WM, int WN, bool RIGHT, bool FLUSH, class ST, bool VEC>
+template <int BM, int BN, int WM, int WN, bool RIGHT, class ST, bool VEC>
 __global__ void __launch_bounds__(256)
 k_proj(const ST* __restrict__ G, const ST* __restrict__ E, const float* __restrict__ Ut,
-       const int* __restrict__ J, float* __restrict__ Qpart, int64_t d, int64_t D, int r, int N, int kslice,
-       int gx, int gy, int ntiles) {
-  int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
-  if (gy > 1) {
-    const int L = blockIdx.x, xcd = L & 7, slot = L >> 3;
-    by = slot % gy;
-    const int tile = (slot / gy) * 8 + xcd;
-    if (tile >= ntiles) return;
-    bx = tile % gx;
-    bz = tile / gx;
-  }
-  proj_at<BM, BN, WM, WN, RIGHT, FLUSH, ST, VEC>(G, E, Ut, J, Qpart, d, D, r, N, kslice, bx, by, bz);
+       const int* __restrict__ J, float* __restrict__ Qpart, int64_t d, int64_t D, int r, int N, int kslice) {
+  proj_at<BM, BN, WM, WN, RIGHT, ST, VEC>(G, E, Ut, J, Qpart, d, D, r, N, kslice, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 // Above rank 64 the projection is bound by the matrix cores: the same product
 // on the bf16 ones (kBf16x3: M^(i) has no scale known in advance, and Q's
@@ -534,7 +514,10 @@ __device__ __forceinline__ void proj_split_at(const ST* __restrict__ G, const ST
       }
     }
 }
-// rank tiles over the same columns run 8 blocks apart (see k_proj)
+// A 1-D grid in which the gy rank tiles of a (column tile, worker, slice)
+// triple are 8 blocks apart, so they run on the same XCD at the same time and
+// the second read of those columns hits that XCD's L2 (blocks go to the XCDs
+// in turn).
 template <int BM, int WM, int WN, bool RIGHT, class ST>
 __global__ void __launch_bounds__(256, 2)
 k_proj_split(const ST* __restrict__ G, const ST* __restrict__ E, const float* __restrict__ Ut,
@@ -564,24 +547,20 @@ static hipError_t launch_proj_st(const MatView& v, hipStream_t s) {
   const bool vec = proj_vec(v, sizeof(ST));
   dim3 grid;
   grid.z = (unsigned)(v.N * splits);
-#define GLR_PROJ1(BM, BN, WM, WN, FL, R, VE)                                                      \
-  hipLaunchKernelGGL((k_proj<BM, BN, WM, WN, R, FL, ST, VE>), gr, dim3(kThreads), 0, s, G, E, v.Ut, \
-                     v.J, v.Qpart, v.d, v.D, r, v.N, (int)kslice, gx, gy, ntiles)
-#define GLR_PROJ(BM, BN, WM, WN, FL)                                                              \
-  do {                                                                                            \
-    const int gx = (int)((v.D + BN - 1) / BN), gy = (r + BM - 1) / BM;                            \
-    const int ntiles = gx * (int)grid.z;                                                          \
-    dim3 gr = grid;                                                                               \
-    gr.x = (unsigned)gx;                                                                          \
-    gr.y = (unsigned)gy;                                                                          \
-    if (gy > 1) gr = dim3((unsigned)(((ntiles + 7) / 8) * 8 * gy));                               \
-    if (v.right) {                                                                                \
-      if (vec) GLR_PROJ1(BM, BN, WM, WN, FL, true, true);                                         \
-      else GLR_PROJ1(BM, BN, WM, WN, FL, true, false);                                            \
-    } else {                                                                                      \
-      if (vec) GLR_PROJ1(BM, BN, WM, WN, FL, false, true);                                        \
-      else GLR_PROJ1(BM, BN, WM, WN, FL, false, false);                                           \
-    }                                                                                             \
+#define GLR_PROJ1(BM, BN, WM, WN, R, VE)                                                            \
+  hipLaunchKernelGGL((k_proj<BM, BN, WM, WN, R, ST, VE>), grid, dim3(kThreads), 0, s, G, E, v.Ut,   \
+                     v.J, v.Qpart, v.d, v.D, r, v.N, (int)kslice)
+#define GLR_PROJ(BM, BN, WM, WN)                                                                    \
+  do {                                                                                              \
+    grid.x = (unsigned)((v.D + BN - 1) / BN);                                                       \
+    grid.y = (unsigned)((r + BM - 1) / BM);                                                         \
+    if (v.right) {                                                                                  \
+      if (vec) GLR_PROJ1(BM, BN, WM, WN, true, true);                                               \
+      else GLR_PROJ1(BM, BN, WM, WN, true, false);                                                  \
+    } else {                                                                                        \
+      if (vec) GLR_PROJ1(BM, BN, WM, WN, false, true);                                              \
+      else GLR_PROJ1(BM, BN, WM, WN, false, false);                                                 \
+    }                                                                                               \
   } while (0)
   // one rank tile covers all r rows, so G and E are read once.  Up to rank
   // 64 the tile adds its fp32 sums into fp64 every 512 terms; above, the
@@ -589,8 +568,8 @@ static hipError_t launch_proj_st(const MatView& v, hipStream_t s) {
   // fp64 accumulators out of the larger tiles (a 128-row tile holding them
   // spills).  At rank 64 the 64 x 128 tile without the fp64 sums was 10 %
   // slower than the 64 x 64 one with them (fewer, longer blocks).
-  if (r <= 32) GLR_PROJ(32, 128, 1, 4, true);
-  else if (r <= kProjFlushRank) GLR_PROJ(64, 64, 2, 2, true);
+  if (r <= 32) GLR_PROJ(32, 128, 1, 4);
+  else if (r <= kProjFlushRank) GLR_PROJ(64, 64, 2, 2);
 #define GLR_PROJS1(BM, WM, WN, R)                                                                          \
   hipLaunchKernelGGL((k_proj_split<BM, WM, WN, R, ST>), gr, dim3(kThreads), 0, s, G, E, v.Ut, v.J, v.Qpart, \
                      v.d, v.D, r, v.N, (int)kslice, gx, gy, ntiles)
@@ -1323,7 +1302,7 @@ hipError_t launch_resid_opt(const MatView& v, const OptParams& o, hipStream_t s)
 // r x D subspace (S1 = M, S2 = V, row-major r x D, oriented) and restart from
 // zero at every refresh; the step direction Rhat = M / (sqrt(V) + eps)
 // replaces Rbar, so that the reconstruction P Rhat and X -= lr P Rhat follow
-// in k_resid_opt<2>.  Moments in the main text's form (eq-adam).
+// in k_recon_opt<2>.  Moments in the main text's form (eq-adam).
 __global__ void k_galore_adam(float* __restrict__ Rbar, float* __restrict__ S1, float* __restrict__ S2, int64_t n,
                               float beta1, float beta2, float eps, int reset) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -1449,7 +1428,7 @@ k_g_proj(const GroupMat* __restrict__ gm, const int* __restrict__ first, int num
   const int gx = (int)((v.D + BN - 1) / BN), gy = (v.r + BM - 1) / BM;
   const int local = blockIdx.x - first[m], rest = local / gx;
   if constexpr (FLUSH)
-    proj_at<BM, BN, WM, WN, RIGHT, true, ST>(static_cast<const ST*>(v.G), static_cast<const ST*>(v.E), v.Ut, v.J,
+    proj_at<BM, BN, WM, WN, RIGHT, ST>(static_cast<const ST*>(v.G), static_cast<const ST*>(v.E), v.Ut, v.J,
                                              v.Qpart, v.d, v.D, v.r, v.N, g.kslice, local % gx, rest % gy, rest / gy);
   else
     proj_split_at<BM, WM, WN, RIGHT, ST>(static_cast<const ST*>(v.G), static_cast<const ST*>(v.E), v.Ut, v.J, v.Qpart,
