@@ -268,20 +268,23 @@ struct ToprLds {
   uint32_t pick[2];                                 // the bin found, keys above it
   uint32_t slab[8][kToprThreads / 64];
 };
-// the folded score of column j
+// the folded score of column j, in fp64: an fp32 sum of the D / 64 partials
+// (squares, all positive, in the exact scores) was further off than their own
+// rounding (768 x 3072: 9.5e-8 from 64 bits, 2.3e-8 so; D / 128 partials in
+// fp32 7.0e-8)
 __device__ __forceinline__ float fold_score(const float* __restrict__ part, int ntiles, int d, int approx, int j) {
   // 32 loads in flight: the partials come from the other XCDs' L2
   constexpr int B = 32;
-  float s = 0.f;
+  double s = 0.0;
   for (int t0 = 0; t0 < ntiles; t0 += B) {
     float x[B];
 #pragma unroll
     for (int i = 0; i < B; ++i) x[i] = part[(int64_t)(t0 + i < ntiles ? t0 + i : t0) * d + j];
 #pragma unroll
     for (int i = 0; i < B; ++i)
-      if (t0 + i < ntiles) s += x[i];
+      if (t0 + i < ntiles) s += (double)x[i];
   }
-  return approx ? s * s : s;
+  return (float)(approx ? s * s : s);
 }
 // folds `part` into `score` when `own`, else reads it
 __device__ __forceinline__ void topr_at(const float* __restrict__ part, int ntiles, bool own, int approx, int d,

@@ -52,6 +52,24 @@ def test_scores_against_fp64(gpu_lib, shape, select, scale):
     assert np.all(np.abs(got - ref) <= bound)
 
 
+# hundreds of partials a column: their fold adds no error of its own.  A
+# partial of 64 rows is within about 2^-23 of its squares' sum, of either sign,
+# so 313 and 1094 of them leave 7e-9; the rounding of the stored score is 2.5e-8
+# rms.  (Folded in fp32: 2e-7.)
+@pytest.mark.parametrize("d,D", [(256, 20000), (40, 70003)])
+def test_score_fold_over_many_partials(gpu_lib, d, D):
+    rng = np.random.default_rng(D)
+    U = torch.from_numpy(_orthonormal(d, rng).astype(np.float32)).cuda()
+    G = torch.from_numpy(rng.standard_normal((1, d, D)).astype(np.float32)).cuda()
+    comp = gpu_lib.GreedyLore([(d, D)], 1, 2, 1000, select="exact")
+    comp.write_state(0, Ut=U)
+    comp.resume(1)
+    comp.step([torch.zeros(d, D, device="cuda")], [G], 1)
+    comp.check_status()
+    ref = (U.double() @ G[0].double()).square().sum(1)
+    assert float((comp.score(0).double() - ref).norm() / ref.norm()) < 4e-8
+
+
 # ranks around the 16-deep steps and their powers of two (one to sixteen steps,
 # and the fp32 pass above rank 256); ragged tiles on both sides; columns of
 # very different size, whose residuals are held to their own column's size
