@@ -1003,8 +1003,10 @@ template <int OPT, bool RIGHT, int KS, class ST>
 __global__ void __launch_bounds__(256, KS <= 4 ? 3 : 2)
 k_resid_packed(const ST* __restrict__ G, ST* __restrict__ E, float* __restrict__ Ebar, const u32x4* __restrict__ Qf,
                const int* __restrict__ Qe, const u32x4* __restrict__ Pf, float* __restrict__ X,
-               float* __restrict__ S1, float* __restrict__ S2, int64_t m, int64_t n, int r, int N, OptParams op) {
-  resid_packed_at<OPT, RIGHT, KS, ST>(G, E, Ebar, Qf, Qe, Pf, X, S1, S2, m, n, r, N, op, blockIdx.x, blockIdx.y);
+               float* __restrict__ S1, float* __restrict__ S2, int64_t m, int64_t n, int r, int N, OptParams op,
+               int rows_fast) {
+  resid_packed_at<OPT, RIGHT, KS, ST>(G, E, Ebar, Qf, Qe, Pf, X, S1, S2, m, n, r, N, op,
+                                      rows_fast ? blockIdx.y : blockIdx.x, rows_fast ? blockIdx.x : blockIdx.y);
 }
 
 // Without error feedback (E^(i) and Ebar stay zero): Ghat = P Rbar and the
@@ -1239,11 +1241,16 @@ template <class ST>
 static hipError_t launch_resid_opt_st(const MatView& v, const OptParams& o, hipStream_t s) {
   const ST* G = static_cast<const ST*>(v.G);
   ST* E = static_cast<ST*>(v.E);
-  dim3 grid((unsigned)((v.n + 63) / 64), (unsigned)((v.m + 63) / 64));
+  const dim3 grid((unsigned)((v.n + 63) / 64), (unsigned)((v.m + 63) / 64));
   if (v.r <= kPackRank && o.ef) {
+    // row tiles on x when they exceed a grid's y extent (65535: m above
+    // 4194240; the column tiles are few then, m n being below 2^30)
+    const int rows_fast = grid.y > 65535u ? 1 : 0;
+    const dim3 gp = rows_fast ? dim3(grid.y, grid.x) : grid;
 #define GLR_RP(OPT, R, KS)                                                                                   \
-  hipLaunchKernelGGL((k_resid_packed<OPT, R, KS, ST>), grid, dim3(kThreads), 0, s, G, E, v.Ebar,             \
-                     (const u32x4*)v.Qf, v.Qe, (const u32x4*)v.Pf, v.X, v.S1, v.S2, v.m, v.n, v.r, v.N, o)
+  hipLaunchKernelGGL((k_resid_packed<OPT, R, KS, ST>), gp, dim3(kThreads), 0, s, G, E, v.Ebar,               \
+                     (const u32x4*)v.Qf, v.Qe, (const u32x4*)v.Pf, v.X, v.S1, v.S2, v.m, v.n, v.r, v.N, o,   \
+                     rows_fast)
 #define GLR_RP2(OPT, R)                       \
   switch (pack_steps(v.r)) {                  \
     case 1: GLR_RP(OPT, R, 1); break;         \

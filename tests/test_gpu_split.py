@@ -107,6 +107,28 @@ def test_residual_against_fp64(gpu_lib, rank, shape, workers, store):
     assert np.all(np.abs(oriented(comp.Ebar(0)) - E.mean(0)) <= 1e-6 * np.abs(E).max(0) + 1e-37)
 
 
+# more row tiles than a grid's y extent holds (65535): the rows on both sides of
+# that tile, against fp64
+def test_residual_of_more_row_tiles_than_a_grid_extent(gpu_lib):
+    m, n, r = 65535 * 64 + 129, 130, 129
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    U = torch.from_numpy(_orthonormal(n, np.random.default_rng(3)).astype(np.float32)).cuda()
+    G = torch.randn(1, m, n, generator=gen, device="cuda")
+    comp = gpu_lib.GreedyLore([(m, n)], 1, r, 1000, lr=1.0, beta1=0.0, select="exact")
+    comp.write_state(0, Ut=U)
+    comp.resume(1)
+    X = torch.zeros(m, n, device="cuda")
+    comp.step([X], [G], 1)
+    comp.check_status()
+    P = U.double()[comp.J(0).long()]
+    for a in (0, 65535 * 64 - 64, m - 193, m - 64):
+        M = G[0, a:a + 64].double()
+        C = (M @ P.T) @ P
+        col = M.norm(dim=1, keepdim=True)
+        assert bool(((comp.E(0)[0, a:a + 64].double() - (M - C)).abs() <= 4e-6 * col).all())
+        assert bool(((X[a:a + 64].double() + C).abs() <= 4e-6 * col).all())
+
+
 # one and several keys a thread, the fold inside and outside the selecting
 # workgroup, ties (equal scores go to the smaller index) and extremes
 @pytest.mark.parametrize("d,D", [(2, 3), (127, 300), (1023, 1100), (1025, 1500), (2050, 2100), (1030, 9000)])
