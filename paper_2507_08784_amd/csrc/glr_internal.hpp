@@ -116,7 +116,7 @@ struct MatView {
   float* X;      const void* G;
   // workspace
   float* Mbar;   float* Q;     float* Qpart; float* lam_part;
-  void* Qf; int* Qe; void* Pf;   // packed pieces of Q^(i), their exponents, pieces of P
+  void* Qf; int* Qe; void* Pf; int* Pe;   // packed pieces of Q^(i) and of P, and their exponents
   float* amax;     // largest |Mbar| of each block of the worker mean (ef_mean_blocks of them)
   float* W;      float* Utw;   double* Apk;  double* Apk2; float* Vrot;   double* V64;   int* skip;
   double* gpart;   // split-contraction partials of the Gram (or null)

@@ -35,7 +35,7 @@ inline uint64_t align_up(uint64_t x) { return (x + kAlign - 1) / kAlign * kAlign
 thread_local std::string g_create_error;
 
 struct WsLayout {
-  uint64_t off_Mbar, off_Q, off_Qpart, off_Qf, off_Qe, off_Pf, off_lam, off_amax, off_W, off_Utw, off_gram, off_gram2, off_V, off_V64, off_gpart, off_skip,
+  uint64_t off_Mbar, off_Q, off_Qpart, off_Qf, off_Qe, off_Pf, off_Pe, off_lam, off_amax, off_W, off_Utw, off_gram, off_gram2, off_V, off_V64, off_gpart, off_skip,
       off_ctl, off_sigw, off_perm;
   uint64_t off_sP, off_sPn, off_sZ, off_sZt, off_sR, off_spart, off_sS, off_sL, off_sDinv, off_sLi,
       off_sT, off_sLinv, off_sC, off_ssums, off_sctl, off_sbad;
@@ -176,7 +176,7 @@ bool packed_resid(const glr_config* c, const Dims& x) { return x.r <= kPackRank 
 
 WsLayout ws_layout(const glr_config* c, int first, int last) {
   uint64_t mx_mn = 0, mx_Q = 0, mx_Qp = 0, mx_lam = 0, mx_dD = 0, mx_dd = 0, mx_gram = 0, mx_groups = 0, mx_vbuf = 0, mx_d = 0;
-  uint64_t p_Q = 0, p_Qe = 0, p_P = 0;
+  uint64_t p_Q = 0, p_Qe = 0, p_P = 0, p_Pe = 0;
   uint64_t s_Kd = 0, s_KD = 0, s_part = 0, s_KK = 0, s_Kp2 = 0, s_nt = 0, s_sums = 0, s_Kp = 0;
   uint64_t r_gram = 0, r_groups = 0, r_vbuf = 0, r_gpart = 0, mx_gpart = 0;
   auto mx = [](uint64_t& a, uint64_t b) { if (b > a) a = b; };
@@ -191,6 +191,7 @@ WsLayout ws_layout(const glr_config* c, int first, int last) {
       mx(p_Q, c->num_workers * D32 * k16 * pack_bytes(x.r));
       mx(p_Qe, c->num_workers * D32 * 4);
       mx(p_P, (uint64_t)(x.d + 31) / 32 * 32 * k16 * pack_bytes(x.r));
+      mx(p_Pe, (uint64_t)(x.d + 31) / 32 * 33 * 4);   // each row's and a flag a block
     } else {
       mx(mx_Q, (uint64_t)c->num_workers * (uint64_t)x.r * (uint64_t)x.D);
     }
@@ -241,6 +242,7 @@ WsLayout ws_layout(const glr_config* c, int first, int last) {
   w.off_Qf = take(p_Q);
   w.off_Qe = take(p_Qe);
   w.off_Pf = take(p_P);
+  w.off_Pe = take(p_Pe);
   const uint64_t proj_end = o;
   o = shared;
   w.off_W = take(mx_dD * 4);
@@ -449,6 +451,7 @@ MatView view_of(glr_handle* h, int mat, float* X, const void* G, int lane) {
   v.Qf = w + WL.off_Qf;
   v.Qe = (int*)(w + WL.off_Qe);
   v.Pf = w + WL.off_Pf;
+  v.Pe = (int*)(w + WL.off_Pe);
   v.W = (float*)(w + WL.off_W);
   v.Utw = (float*)(w + WL.off_Utw);
   v.Apk = (double*)(w + WL.off_gram);

@@ -6,6 +6,8 @@
 #include "glr_internal.hpp"
 #include "glr_split.hpp"
 
+#include <type_traits>
+
 namespace glr {
 
 // ---------------------------------------------------------------------------
@@ -624,9 +626,10 @@ __global__ void k_proj_reduce(const float* __restrict__ part, int splits, int N,
 // holds row 32 blk + l % 32 of the operand (a column b of Q, a row a of P) at
 // k = 16 ks + 8 (l / 32) ..+7; the fragment of piece p, step ks, block blk is
 // at ((blk KS + ks) 2 + p) 64 (u32x4), KS the steps r is padded to with zeros.
-// Each column of Q^(i) has a scale of its own (its exponent in Qe): the
-// residual is compared and Adam normalises element by element, so a column far
-// smaller than the rest keeps its relative precision.  |P| <= 1: one scale.
+// Each column of Q^(i), and each row of P that needs it (pack_p), has a scale of
+// its own (exponents in Qe and Pe): the residual is compared and Adam normalises element by element, so
+// a column or row far smaller than the rest keeps its relative precision (with
+// one scale for P, rows 1e-4 of the rest were 4.6e-5 off, 1e-6 4.7e-3).
 // Bound by reading the projection's slices, and for small ranks by latency.
 // Up to rank 128 a wave holds all of a column (8 KS values a lane) and takes
 // the 32 columns of one worker's block by itself, and other workgroups of the
@@ -654,36 +657,71 @@ __device__ __forceinline__ void pack_store(const float (&x)[8], float scale, u32
 #pragma unroll
   for (int i = 0; i < PC; ++i) dst[64 * i] = f[i];
 }
-// fragment f = blk KS + ks of P, by one wave
-template <SplitFmt F>
-__device__ __forceinline__ void pack_p(int f, int r, int KS, int64_t d, const float* __restrict__ Ut,
-                                       const int* __restrict__ J, u32x4* __restrict__ Pf) {
-  const int blk = f / KS, ks = f % KS, lane = lane_id();
+// The KS fragments of block blk of P, by one wave, KC steps at a time (two
+// passes when they are not all in registers).  Rows whose largest entry lies in
+// [kUnitLow, kUnitHigh), nearly all of an orthonormal basis, are scaled by
+// 2^kUnitExp (their pieces resolve 2^-24 of it); a row outside, by a power of
+// its own: Pe holds its exponent beyond kUnitExp and, past the rows, whether a
+// block has any.  The residual then corrects that block's products; doing so
+// for every block cost it 12 % at rank 128 (registers of loads in flight).
+constexpr float kUnitLow = 0x1p-7f, kUnitHigh = 0x1p+9f;
+template <SplitFmt F, int KC>
+__device__ __forceinline__ void pack_p(int blk, int r, int KS, int64_t d, const float* __restrict__ Ut,
+                                       const int* __restrict__ J, u32x4* __restrict__ Pf, int* __restrict__ Pe) {
+  const int lane = lane_id();
   if (blk >= (int)((d + 31) / 32)) return;
   const int a = blk * 32 + (lane & 31);
-  float x[8];
+  float x[KC][8];
+  auto load = [&](int k0) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int k = 16 * ks + 8 * (lane >> 5) + e;
-    x[e] = (k < r && a < d) ? Ut[(int64_t)J[k] * d + a] : 0.f;
+    for (int ks = 0; ks < KC; ++ks)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int k = 16 * (k0 + ks) + 8 * (lane >> 5) + e;
+        x[ks][e] = (k < r && a < d) ? Ut[(int64_t)J[k] * d + a] : 0.f;
+      }
+  };
+  float scale = 1.f;
+  load(0);
+  if constexpr (F == kF16x2) {
+    float mx = 0.f;
+    for (int k0 = 0;;) {
+#pragma unroll
+      for (int ks = 0; ks < KC; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(x[ks][e]));
+      if ((k0 += KC) >= KS) break;
+      load(k0);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const int own = mx >= kUnitLow && mx < kUnitHigh ? 0 : mx > 0.f ? split_exp(mx) - kUnitExp : 0;
+    const uint64_t odd = __ballot(own != 0);
+    if (lane < 32) Pe[blk * 32 + lane] = own;
+    if (lane == 0) Pe[(int64_t)((d + 31) / 32) * 32 + blk] = odd != 0;
+    scale = ldexpf(1.f, kUnitExp + own);
   }
-  pack_store<F>(x, ldexpf(1.f, kUnitExp), Pf + (int64_t)f * (64 * split_pieces(F)) + lane);
+  for (int k0 = 0; k0 < KS; k0 += KC) {
+    if (KC < KS) load(k0);
+#pragma unroll
+    for (int ks = 0; ks < KC; ++ks)
+      pack_store<F>(x[ks], scale, Pf + ((int64_t)blk * KS + k0 + ks) * (64 * split_pieces(F)) + lane);
+  }
 }
-// blocks of kThreads: four fragments columns of Q each, then four fragments of
-// P each, then Rbar
+// blocks of kThreads: four fragments columns of Q each, then four blocks of P
+// each, then Rbar
 struct PackGrid {
   int q, p, rbar;
 };
-__host__ __device__ inline PackGrid pack_grid(int64_t d, int64_t D, int N, int r, int KS) {
-  const int64_t q = (D + 31) / 32 * N, p = (d + 31) / 32 * KS, rb = ((int64_t)r * D + kThreads - 1) / kThreads;
+__host__ __device__ inline PackGrid pack_grid(int64_t d, int64_t D, int N, int r) {
+  const int64_t q = (D + 31) / 32 * N, p = (d + 31) / 32, rb = ((int64_t)r * D + kThreads - 1) / kThreads;
   return {(int)((q + 3) / 4), (int)((p + 3) / 4), (int)rb};
 }
 template <int KS>
 __device__ __forceinline__ void pack_waves(const float* __restrict__ part, int splits, int N, int r, int64_t d,
                                            int64_t D, const float* __restrict__ Ut, const int* __restrict__ J,
                                            u32x4* __restrict__ Qf, int* __restrict__ Qe, u32x4* __restrict__ Pf,
-                                           float* __restrict__ Rbar, int bid) {
-  const PackGrid g = pack_grid(d, D, N, r, KS);
+                                           int* __restrict__ Pe, float* __restrict__ Rbar, int bid) {
+  const PackGrid g = pack_grid(d, D, N, r);
   const int64_t rD = (int64_t)r * D;
   const int lane = lane_id();
   if (bid < g.q) {
@@ -737,7 +775,7 @@ __device__ __forceinline__ void pack_waves(const float* __restrict__ part, int s
         pack_store<pack_fmt(KS)>(x[ks], ldexpf(1.f, e2),
                                  Qf + ((int64_t)item * KS + ks) * (64 * split_pieces(pack_fmt(KS))) + lane);
   } else if (bid < g.q + g.p) {
-    pack_p<pack_fmt(KS)>((bid - g.q) * 4 + wave_id(), r, KS, d, Ut, J, Pf);
+    pack_p<pack_fmt(KS), KS>((bid - g.q) * 4 + wave_id(), r, KS, d, Ut, J, Pf, Pe);
   } else {
     const int64_t i = (int64_t)(bid - g.q - g.p) * kThreads + threadIdx.x;
     if (i >= rD) return;
@@ -753,10 +791,10 @@ __device__ __forceinline__ void pack_waves(const float* __restrict__ part, int s
 __device__ __forceinline__ void pack_block(const float* __restrict__ part, int splits, int N, int r, int KS, int64_t d,
                                         int64_t D, const float* __restrict__ Ut, const int* __restrict__ J,
                                         u32x4* __restrict__ Qf, int* __restrict__ Qe, u32x4* __restrict__ Pf,
-                                        float* __restrict__ Rbar, int bid, float* dyn) {
+                                        int* __restrict__ Pe, float* __restrict__ Rbar, int bid, float* dyn) {
   const int tid = threadIdx.x, nqb = (int)((D + 31) / 32);
   if (bid >= nqb) {
-    pack_p<kF16x2>((bid - nqb) * (kPackThreads / 64) + (tid >> 6), r, KS, d, Ut, J, Pf);
+    pack_p<kF16x2, 4>((bid - nqb) * (kPackThreads / 64) + (tid >> 6), r, KS, d, Ut, J, Pf, Pe);
     return;
   }
   constexpr int KG = kPackThreads / 32;            // rows of k side by side
@@ -808,25 +846,25 @@ static size_t pack_lds(int KS) { return ((size_t)16 * KS * 33 + (size_t)kPackThr
 static int pack_blocks(int64_t d, int64_t D, int N, int r) {
   const int KS = pack_steps(r);
   if (KS <= kPackWaveSteps) {
-    const PackGrid g = pack_grid(d, D, N, r, KS);
+    const PackGrid g = pack_grid(d, D, N, r);
     return g.q + g.p + g.rbar;
   }
-  const int64_t frags = (d + 31) / 32 * KS;
-  return (int)((D + 31) / 32 + (frags + kPackThreads / 64 - 1) / (kPackThreads / 64));
+  const int64_t pb = (d + 31) / 32;
+  return (int)((D + 31) / 32 + (pb + kPackThreads / 64 - 1) / (kPackThreads / 64));
 }
 __global__ void __launch_bounds__(kPackThreads)
 k_pack_block(const float* __restrict__ part, int splits, int N, int r, int KS, int64_t d, int64_t D,
              const float* __restrict__ Ut, const int* __restrict__ J, u32x4* __restrict__ Qf, int* __restrict__ Qe,
-             u32x4* __restrict__ Pf, float* __restrict__ Rbar) {
+             u32x4* __restrict__ Pf, int* __restrict__ Pe, float* __restrict__ Rbar) {
   extern __shared__ __align__(16) unsigned char dyn[];
-  pack_block(part, splits, N, r, KS, d, D, Ut, J, Qf, Qe, Pf, Rbar, blockIdx.x, reinterpret_cast<float*>(dyn));
+  pack_block(part, splits, N, r, KS, d, D, Ut, J, Qf, Qe, Pf, Pe, Rbar, blockIdx.x, reinterpret_cast<float*>(dyn));
 }
 template <int KS>
 __global__ void __launch_bounds__(kThreads)
 k_pack_waves(const float* __restrict__ part, int splits, int N, int r, int64_t d, int64_t D,
              const float* __restrict__ Ut, const int* __restrict__ J, u32x4* __restrict__ Qf, int* __restrict__ Qe,
-             u32x4* __restrict__ Pf, float* __restrict__ Rbar) {
-  pack_waves<KS>(part, splits, N, r, d, D, Ut, J, Qf, Qe, Pf, Rbar, blockIdx.x);
+             u32x4* __restrict__ Pf, int* __restrict__ Pe, float* __restrict__ Rbar) {
+  pack_waves<KS>(part, splits, N, r, d, D, Ut, J, Qf, Qe, Pf, Pe, Rbar, blockIdx.x);
 }
 
 hipError_t launch_rbar(const MatView& v, bool packed, hipStream_t s) {
@@ -836,7 +874,7 @@ hipError_t launch_rbar(const MatView& v, bool packed, hipStream_t s) {
     const dim3 grid((unsigned)pack_blocks(v.d, v.D, v.N, v.r));
 #define GLR_PW(K)                                                                                                  \
   hipLaunchKernelGGL(k_pack_waves<K>, grid, dim3(kThreads), 0, s, v.Qpart, splits, v.N, v.r, v.d, v.D, v.Ut, v.J, \
-                     (u32x4*)v.Qf, v.Qe, (u32x4*)v.Pf, v.Rbar)
+                     (u32x4*)v.Qf, v.Qe, (u32x4*)v.Pf, v.Pe, v.Rbar)
     switch (KS) {
       case 1: GLR_PW(1); break;
       case 2: GLR_PW(2); break;
@@ -844,7 +882,7 @@ hipError_t launch_rbar(const MatView& v, bool packed, hipStream_t s) {
       case 8: GLR_PW(8); break;
       default:
         hipLaunchKernelGGL(k_pack_block, grid, dim3(kPackThreads), pack_lds(KS), s, v.Qpart, splits, v.N, v.r, KS, v.d,
-                           v.D, v.Ut, v.J, (u32x4*)v.Qf, v.Qe, (u32x4*)v.Pf, v.Rbar);
+                           v.D, v.Ut, v.J, (u32x4*)v.Qf, v.Qe, (u32x4*)v.Pf, v.Pe, v.Rbar);
     }
     static_assert(kPackWaveSteps == 8, "one variant per KS");
 #undef GLR_PW
@@ -878,13 +916,14 @@ hipError_t launch_rbar(const MatView& v, bool packed, hipStream_t s) {
 // Bound by HBM: G and E in, E out, X, the optimizer state and Ebar.  Before
 // (fp32 MFMA on LDS slices, P Rbar as a product of its own): 4096 x 4096,
 // r = 64, N = 8: 496 -> 382 us (5.4 TB/s, the rate of a large copy);
-// 11008 x 4096, r = 128: 1890 -> 1450 us; the same in bf16: 1705 -> 1084 us;
+// 11008 x 4096, r = 128: 1890 -> 1210 us; the same in bf16: 1705 -> 1072 us;
 // 8192 x 28672, r = 256, N = 4: 6.73 -> 5.11 ms.
 // ---------------------------------------------------------------------------
 template <int OPT, bool RIGHT, int KS, class ST>
 __device__ __forceinline__ void resid_packed_at(const ST* __restrict__ G, ST* __restrict__ E, float* __restrict__ Ebar,
                                                 const u32x4* __restrict__ Qf, const int* __restrict__ Qe,
-                                                const u32x4* __restrict__ Pf, float* __restrict__ X,
+                                                const u32x4* __restrict__ Pf, const int* __restrict__ Pe,
+                                                float* __restrict__ X,
                                                 float* __restrict__ S1, float* __restrict__ S2, int64_t m, int64_t n,
                                                 int r, int N, const OptParams& op, int bx, int by) {
   const int lane = lane_id(), wv = wave_id(), live = r <= 8 ? 32 : 64;
@@ -899,6 +938,7 @@ __device__ __forceinline__ void resid_packed_at(const ST* __restrict__ G, ST* __
   for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
     for (int i = 0; i < PC; ++i) pp[ks][i] = Pf[((pblk * KS + ks) * PC + i) * 64 + lane];
+  const int podd = F == kF16x2 ? __builtin_amdgcn_readfirstlane(Pe[((RIGHT ? n : m) + 31) / 32 * 32 + pblk]) : 0;
   // every m x n array is addressed as a buffer (m n 4 < 2^32 bytes): a uniform
   // descriptor and one 32-bit byte offset per element, shared by all of them;
   // elements outside the matrix take kBufNone
@@ -912,67 +952,88 @@ __device__ __forceinline__ void resid_packed_at(const ST* __restrict__ G, ST* __
   float esum[16], gsum[16];
 #pragma unroll
   for (int v = 0; v < 16; ++v) esum[v] = gsum[v] = 0.f;
-  for (int w = 0; w < N; ++w) {
-    const BufRsrc Gi = buf_rsrc_s(G + (int64_t)w * mn, mn);
-    const BufRsrc Ei = buf_rsrc_s(E + (int64_t)w * mn, mn);
-    float gv[16], eo[16];
+  // (two copies of the loop: the common one keeps its registers and schedule)
+  auto workers = [&](auto odd) {
+    constexpr bool ODD = decltype(odd)::value;
+    for (int w = 0; w < N; ++w) {
+      const BufRsrc Gi = buf_rsrc_s(G + (int64_t)w * mn, mn);
+      const BufRsrc Ei = buf_rsrc_s(E + (int64_t)w * mn, mn);
+      float gv[16], eo[16];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      gv[v] = buf_lde<ST>(Gi, ob[v]);
-      eo[v] = buf_lde<ST>(Ei, ob[v]);
-    }
-    const u32x4* q = Qf + ((int64_t)w * nqb + qblk) * (KS * PC * 64) + lane;
-    const int* qe = Qe + ((int64_t)w * nqb + qblk) * 32;
-    f32x16 big, small;
+      for (int v = 0; v < 16; ++v) {
+        gv[v] = buf_lde<ST>(Gi, ob[v]);
+        eo[v] = buf_lde<ST>(Ei, ob[v]);
+      }
+      const u32x4* q = Qf + ((int64_t)w * nqb + qblk) * (KS * PC * 64) + lane;
+      const int* qe = Qe + ((int64_t)w * nqb + qblk) * 32;
+      f32x16 big, small;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) big[v] = small[v] = 0.f;
+      for (int v = 0; v < 16; ++v) big[v] = small[v] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      u32x4 qq[PC];
-      if constexpr (KS == 1) {
-        // rank 8 or less: the upper lanes hold zeros and load nothing
+      for (int ks = 0; ks < KS; ++ks) {
+        u32x4 qq[PC];
+        if constexpr (KS == 1) {
+          // rank 8 or less: the upper lanes hold zeros and load nothing
 #pragma unroll
-        for (int i = 0; i < PC; ++i) qq[i] = u32x4{0u, 0u, 0u, 0u};
-        if (lane < live) {
+          for (int i = 0; i < PC; ++i) qq[i] = u32x4{0u, 0u, 0u, 0u};
+          if (lane < live) {
 #pragma unroll
-          for (int i = 0; i < PC; ++i) qq[i] = q[i * 64];
+            for (int i = 0; i < PC; ++i) qq[i] = q[i * 64];
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < PC; ++i) qq[i] = q[(ks * PC + i) * 64];
+        }
+        // piece i of P times piece s - i of Q, the smallest products first
+#pragma unroll
+        for (int s = PC - 1; s >= 0; --s)
+#pragma unroll
+          for (int i = 0; i <= s; ++i) {
+            f32x16& c = s == 0 ? big : small;
+            c = RIGHT ? split_mfma<F>(qq[s - i], pp[ks][i], c) : split_mfma<F>(pp[ks][i], qq[s - i], c);
+          }
+      }
+      if constexpr (ODD) {
+        // rows of P that are packed by exponents of their own
+        const int* pe = Pe + pblk * 32;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int4 x = RIGHT ? make_int4(pe[lane & 31], pe[lane & 31], pe[lane & 31], pe[lane & 31])
+                               : *reinterpret_cast<const int4*>(pe + 8 * g + 4 * (lane >> 5));
+          const int xe[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            big[4 * g + e] = ldexpf(big[4 * g + e], -xe[e]);
+            small[4 * g + e] = ldexpf(small[4 * g + e], -xe[e]);
+          }
+        }
+      }
+      // columns of Q are tile rows (RIGHT) or this lane's column
+      int ex[RIGHT ? 16 : 1];
+      if (RIGHT) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int4 x = *reinterpret_cast<const int4*>(qe + 8 * g + 4 * (lane >> 5));
+          ex[RIGHT ? 4 * g : 0] = x.x; ex[RIGHT ? 4 * g + 1 : 0] = x.y;
+          ex[RIGHT ? 4 * g + 2 : 0] = x.z; ex[RIGHT ? 4 * g + 3 : 0] = x.w;
         }
       } else {
-#pragma unroll
-        for (int i = 0; i < PC; ++i) qq[i] = q[(ks * PC + i) * 64];
+        ex[0] = qe[lane & 31];
       }
-      // piece i of P times piece s - i of Q, the smallest products first
 #pragma unroll
-      for (int s = PC - 1; s >= 0; --s)
-#pragma unroll
-        for (int i = 0; i <= s; ++i) {
-          f32x16& c = s == 0 ? big : small;
-          c = RIGHT ? split_mfma<F>(qq[s - i], pp[ks][i], c) : split_mfma<F>(pp[ks][i], qq[s - i], c);
-        }
-    }
-    // columns of Q are tile rows (RIGHT) or this lane's column
-    int ex[RIGHT ? 16 : 1];
-    if (RIGHT) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int4 x = *reinterpret_cast<const int4*>(qe + 8 * g + 4 * (lane >> 5));
-        ex[RIGHT ? 4 * g : 0] = x.x; ex[RIGHT ? 4 * g + 1 : 0] = x.y;
-        ex[RIGHT ? 4 * g + 2 : 0] = x.z; ex[RIGHT ? 4 * g + 3 : 0] = x.w;
+      for (int v = 0; v < 16; ++v) {
+        const float s = big[v] + small[v];
+        const float c = F == kF16x2 ? ldexpf(s, -ex[RIGHT ? v : 0] - kUnitExp) : s;
+        // (G - P Q) + E: G and P Q nearly cancel, E is the small part
+        const float e = (gv[v] - c) + eo[v];
+        buf_ste<ST>(Ei, ob[v], e);
+        esum[v] += stored<ST>(e);
+        gsum[v] += c;
       }
-    } else {
-      ex[0] = qe[lane & 31];
     }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const float s = big[v] + small[v];
-      const float c = F == kF16x2 ? ldexpf(s, -ex[RIGHT ? v : 0] - kUnitExp) : s;
-      // (G - P Q) + E: G and P Q nearly cancel, E is the small part
-      const float e = (gv[v] - c) + eo[v];
-      buf_ste<ST>(Ei, ob[v], e);
-      esum[v] += stored<ST>(e);
-      gsum[v] += c;
-    }
-  }
+  };
+  if (podd) workers(std::true_type{});
+  else workers(std::false_type{});
   const uint32_t bytes = (uint32_t)(mn * 4);
   const BufRsrc Xr = buf_rsrc(X, bytes), S1r = buf_rsrc(S1, bytes), Ebr = buf_rsrc(Ebar, bytes);
   const BufRsrc S2r = buf_rsrc(OPT == 1 ? S2 : S1, bytes);
@@ -1002,10 +1063,11 @@ __device__ __forceinline__ void resid_packed_at(const ST* __restrict__ G, ST* __
 template <int OPT, bool RIGHT, int KS, class ST>
 __global__ void __launch_bounds__(256, KS <= 4 ? 3 : 2)
 k_resid_packed(const ST* __restrict__ G, ST* __restrict__ E, float* __restrict__ Ebar, const u32x4* __restrict__ Qf,
-               const int* __restrict__ Qe, const u32x4* __restrict__ Pf, float* __restrict__ X,
-               float* __restrict__ S1, float* __restrict__ S2, int64_t m, int64_t n, int r, int N, OptParams op,
+               const int* __restrict__ Qe, const u32x4* __restrict__ Pf, const int* __restrict__ Pe,
+               float* __restrict__ X, float* __restrict__ S1, float* __restrict__ S2, int64_t m, int64_t n, int r,
+               int N, OptParams op,
                int rows_fast) {
-  resid_packed_at<OPT, RIGHT, KS, ST>(G, E, Ebar, Qf, Qe, Pf, X, S1, S2, m, n, r, N, op,
+  resid_packed_at<OPT, RIGHT, KS, ST>(G, E, Ebar, Qf, Qe, Pf, Pe, X, S1, S2, m, n, r, N, op,
                                       rows_fast ? blockIdx.y : blockIdx.x, rows_fast ? blockIdx.x : blockIdx.y);
 }
 
@@ -1247,10 +1309,10 @@ static hipError_t launch_resid_opt_st(const MatView& v, const OptParams& o, hipS
     // 4194240; the column tiles are few then, m n being below 2^30)
     const int rows_fast = grid.y > 65535u ? 1 : 0;
     const dim3 gp = rows_fast ? dim3(grid.y, grid.x) : grid;
-#define GLR_RP(OPT, R, KS)                                                                                   \
-  hipLaunchKernelGGL((k_resid_packed<OPT, R, KS, ST>), gp, dim3(kThreads), 0, s, G, E, v.Ebar,               \
-                     (const u32x4*)v.Qf, v.Qe, (const u32x4*)v.Pf, v.X, v.S1, v.S2, v.m, v.n, v.r, v.N, o,   \
-                     rows_fast)
+#define GLR_RP(OPT, R, KS)                                                                                  \
+  hipLaunchKernelGGL((k_resid_packed<OPT, R, KS, ST>), gp, dim3(kThreads), 0, s, G, E, v.Ebar,              \
+                     (const u32x4*)v.Qf, v.Qe, (const u32x4*)v.Pf, v.Pe, v.X, v.S1, v.S2, v.m, v.n, v.r, v.N, \
+                     o, rows_fast)
 #define GLR_RP2(OPT, R)                       \
   switch (pack_steps(v.r)) {                  \
     case 1: GLR_RP(OPT, R, 1); break;         \
@@ -1451,7 +1513,7 @@ k_g_pack_waves(const GroupMat* __restrict__ gm, const int* __restrict__ first, i
   const int m = group_find(first, num, blockIdx.x);
   const GroupMat& g = gm[m];
   const MatView& v = g.v;
-  pack_waves<KS>(v.Qpart, g.splits, v.N, v.r, v.d, v.D, v.Ut, v.J, (u32x4*)v.Qf, v.Qe, (u32x4*)v.Pf, v.Rbar,
+  pack_waves<KS>(v.Qpart, g.splits, v.N, v.r, v.d, v.D, v.Ut, v.J, (u32x4*)v.Qf, v.Qe, (u32x4*)v.Pf, v.Pe, v.Rbar,
                  blockIdx.x - first[m]);
 }
 
@@ -1462,7 +1524,7 @@ k_g_resid(const GroupMat* __restrict__ gm, const int* __restrict__ first, int nu
   const MatView& v = gm[m].v;
   const int local = blockIdx.x - first[m], gx = (int)((v.n + 63) / 64);
   resid_packed_at<OPT, RIGHT, KS, ST>(static_cast<const ST*>(v.G), static_cast<ST*>(v.E), v.Ebar, (const u32x4*)v.Qf,
-                                      v.Qe, (const u32x4*)v.Pf, v.X, v.S1, v.S2, v.m, v.n, v.r, v.N, op, local % gx,
+                                      v.Qe, (const u32x4*)v.Pf, v.Pe, v.X, v.S1, v.S2, v.m, v.n, v.r, v.N, op, local % gx,
                                       local / gx);
 }
 

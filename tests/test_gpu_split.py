@@ -107,6 +107,41 @@ def test_residual_against_fp64(gpu_lib, rank, shape, workers, store):
     assert np.all(np.abs(oriented(comp.Ebar(0)) - E.mean(0)) <= 1e-6 * np.abs(E).max(0) + 1e-37)
 
 
+# rows of P (and of M) from 1 down to 1e-9 of the largest: the reconstruction of
+# a row is held to that row's own size
+@pytest.mark.parametrize("rank", [5, 17, 64, 128, 200])
+@pytest.mark.parametrize("shape", [(299, 330), (330, 299)])
+@pytest.mark.parametrize("store", ["fp32", "bf16"])
+def test_reconstruction_of_small_rows(gpu_lib, rank, shape, store):
+    m, n = shape
+    d, D, N = min(shape), max(shape), 3
+    rng = np.random.default_rng([m, rank])
+    size = 10.0 ** rng.uniform(-9, 0, d)
+    U = (_orthonormal(d, rng) * size).astype(np.float32)          # row j: u_j
+    M = rng.standard_normal((N, d, D)) * size[:, None]
+    dt = torch.bfloat16 if store == "bf16" else torch.float32
+    G = torch.from_numpy((M.transpose(0, 2, 1) if m > n else M).astype(np.float32)).to(dt)
+    comp = gpu_lib.GreedyLore([shape], N, rank, 1000, opt="msgd", lr=1.0, beta1=0.0, select="exact", store=store)
+    comp.write_state(0, Ut=torch.from_numpy(U).cuda())
+    comp.resume(1)
+    X = torch.zeros(m, n, device="cuda")
+    comp.step([X], [G.cuda().contiguous()], 1)
+    comp.check_status()
+
+    def oriented(x):
+        x = x.double().cpu().numpy()
+        return np.swapaxes(x, -1, -2) if m > n else x
+
+    P = U[comp.J(0).cpu().numpy()].astype(np.float64).T
+    Mo = oriented(G)
+    C = P @ (P.T @ Mo)
+    # Q within 4e-6 of |M_b| (|P| <= 1), each product of a row within 2^-21
+    bound = 5e-6 * np.linalg.norm(P, axis=1)[:, None] * np.linalg.norm(Mo, axis=1, keepdims=True)
+    assert np.all(np.abs(-oriented(X) - C.mean(0)) <= bound.max(0))
+    if store == "fp32":
+        assert np.all(np.abs(oriented(comp.E(0)) - (Mo - C)) <= bound + 2.0 ** -22 * np.abs(Mo - C))
+
+
 # more row tiles than a grid's y extent holds (65535): the rows on both sides of
 # that tile, against fp64
 def test_residual_of_more_row_tiles_than_a_grid_extent(gpu_lib):
