@@ -48,9 +48,9 @@
  * alone.  GLR_JAC_JOINT=0, read by glr_create, turns this off.  Likewise a
  * selection step of several matrices that all have d <= 2048 and the same rank
  * r < d, r <= 128, launches each of its kernels once for all matrices of a
- * side (m > n or not) on `stream` or one of the handle's streams, after uploading that step's table
- * of matrix views from pinned host memory the handle owns; GLR_GROUPED=0 turns
- * this off.
+ * side (m > n or not) on `stream` or one of the handle's streams, after
+ * uploading that step's table of matrix views from pinned host memory the
+ * handle owns; GLR_GROUPED=0 turns this off.
  * While profiling is enabled the matrices run in order on `stream`.  The
  * environment variable GLR_LANES, read by glr_create, lowers the stream count.
  * Tuning switches of the refresh, also read by glr_create (defaults in
@@ -60,16 +60,21 @@
  * every sweep or before the first only [1]; GLR_JAC_INNER=1..16 sets the
  * cyclic sweeps of each group solve [1]; GLR_SUB_ITERS sets the cap of the
  * tau = 1 block iterations after a warm start [4].  GLR_GROUP_PARTS and
- * GLR_GROUP_SPLIT=0 set the parts of a grouped selection step [2 when there
- * are streams for them] (same results).
+ * GLR_GROUP_SPLIT=0 set the parts of a grouped selection step of matrices of
+ * one side [2 when there are streams for them] (same results; a set with both
+ * sides has one part a side).
  *
  * glr_step only enqueues: it never waits for the device (refresh steps
  * included).  A refresh enqueues a budget of Jacobi sweeps; the sweeps after
- * convergence return at once on the device.  The budget is max_sweeps until a
- * refresh of that matrix has been seen converged, then the most sweeps a
- * converged refresh of it took plus half of that (at least four), capped at
- * max_sweeps; the sweep counts come back through
- * pinned host memory the handle owns, read only once their copy has completed.
+ * convergence return at once on the device.  For Jacobi dimensions (d, or the
+ * block of a tau = 1 refresh) up to 640 the budget is 16 until a refresh of
+ * that matrix has been seen converged, then the most sweeps a converged refresh
+ * of it took plus one (above 128: plus three), and one launch follows that runs
+ * what max_sweeps still allows until convergence, slowly.  Above 640 it is
+ * max_sweeps until a refresh of that matrix has been seen converged, then the
+ * most sweeps plus half of that (at least four), capped at max_sweeps.  The
+ * sweep counts come back through pinned host memory the handle owns, read only
+ * once their copy has completed.
  * A refresh that ends its budget above tol reports GLR_ERR_NOT_CONVERGED and
  * the next one gets max_sweeps again.  (Grouped selection steps reuse a
  * two-slot pinned ring: the host waits only if it runs two such steps ahead
@@ -233,7 +238,8 @@ glr_status glr_create(const glr_config* cfg, void* d_state, size_t state_bytes,
  * a handle calls no hipMalloc, hipFree, hipHostMalloc nor stream or event
  * creation (profiling, if enabled, creates events).  Such a handle runs every
  * matrix on `stream`, without grouped selection steps, and enqueues
- * max_sweeps sweeps per refresh (no sweep counts come back to the host).
+ * max_sweeps sweeps per refresh (no sweep counts come back to the host; up to
+ * a Jacobi dimension of 128, 16 and one launch for the rest).
  * GLR_ERR_BUFFER_TOO_SMALL when the configuration's workspace
  * (glr_workspace_bytes) exceeds the array.  The array is shared by the handle
  * and keeps its contents between handles (creation clears what must start

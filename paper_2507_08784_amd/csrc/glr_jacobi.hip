@@ -1239,14 +1239,16 @@ hipError_t launch_jac_finish(const MatView& v, int max_sweeps, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // Trailing sweeps: up to n more sweeps (until convergence) by one workgroup
 // per matrix in one launch, each sweep the launches of an enqueued sweep one
-// after another, so the same bits.  Every refresh enqueues the sweeps its
-// matrix has been seen to need and one more; what it may need beyond them is
-// left to this launch, which nearly always finds the matrix converged and
-// returns.  Enqueued as sweeps of their own, each of them cost its 3 + 2
-// rounds empty launches: about 45 us at d = 128 (of a 1.5 ms refresh, eight of
-// them) and 350 us for the fifty layers at d <= 512 (of 21.6 ms, nine).  The
-// price is a slow sweep when one is needed: some 50 us of every round's
-// groups one by one, so only up to kTailMaxDim.
+// after another, so the same bits.  A refresh enqueues the sweeps its matrix
+// has been seen to need and a few more; what it may need beyond them is left to
+// this launch, which nearly always finds the matrix converged and returns.
+// Enqueued as sweeps of their own, each of them cost its 3 + 2 rounds empty
+// launches: about 45 us at d = 128 (of a 1.4 ms refresh) and 360 us for the
+// fifty layers at d <= 512 (of 22 ms).  The price is a slow sweep when one is
+// needed: a round's group solves, then its groups (groups + 1) / 2 block
+// updates, one by one (0.6 ms a sweep at d = 128 against 0.2 enqueued, 18 against
+// 0.75 at 512, 36 against 1 at 640), so only up to kTailMaxDim, and with a
+// margin of enqueued sweeps where it is dear.
 // The sorts swap Apk <-> Apk2 and Utw <-> W; an odd count of sweeps is copied
 // back, so the result is where it was.
 // ---------------------------------------------------------------------------

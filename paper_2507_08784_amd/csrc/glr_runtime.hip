@@ -568,20 +568,30 @@ hipError_t prof_collect(glr_handle* h) {
   } while (0)
 
 // Sweeps to enqueue for a refresh of `mat`, with Jacobi dimension jd.  Where
-// trailing sweeps can follow in one launch (jac_has_tail) the largest count
-// read back so far and one more (kFirstSweeps before any): the trailing launch
-// covers every allowed sweep beyond them.  Else every allowed sweep until a
-// refresh of this matrix has been read back converged, then the largest count
-// read back so far plus a margin of half of it (at least four): a warm
-// refresh can need more sweeps than the cold one before it (7 then 10 have
-// been seen on the gradients of a small network).  A refresh that runs out of
-// its budget reports GLR_ERR_NOT_CONVERGED like one that runs out of
-// max_sweeps, and the next refresh gets every allowed sweep again.
+// trailing sweeps can follow in one launch (jac_has_tail), which covers every
+// allowed sweep beyond the enqueued ones, the largest count read back so far
+// and a margin (kFirstSweeps before any).  A sweep enqueued and not needed is
+// empty launches; one needed and not enqueued runs in one workgroup:
+//   d                            64    128    256    320    512    640
+//   enqueued sweep, run (ms)   0.12   0.21   0.39   0.50   0.75   0.99
+//   trailing sweep, run (ms)   0.14   0.59    3.0    5.9     18     36
+// (an empty one: 0.05 ms at 128, 0.36 for the fifty layers at d <= 512).  So
+// one more up to kTailCheap; above, where a trailing sweep costs several
+// enqueued ones, three more: a warm refresh can need more sweeps than the cold
+// one before it (7 then 10 have been seen on the gradients of a small network).
+// Without a trailing launch every allowed sweep until a refresh of this matrix
+// has been read back converged, then that count plus a margin of half of it
+// (at least four).  A refresh that runs out of its budget reports
+// GLR_ERR_NOT_CONVERGED like one that runs out of max_sweeps, and the next
+// refresh gets every allowed sweep again.  Without read-backs (glr_create_static)
+// what the handle needs is never known: every allowed sweep above kTailCheap.
 constexpr int kFirstSweeps = 16;
+constexpr int64_t kTailCheap = 128;
 int sweep_budget(glr_handle* h, int mat, int64_t jd) {
   const int mx = h->cfg.max_sweeps;
   const bool tail = jac_has_tail(jd);
-  if (!h->info_host) return tail ? std::min(mx, kFirstSweeps) : mx;   // no read-back buffer (glr_create_static)
+  const bool cheap = tail && jd <= kTailCheap;
+  if (!h->info_host) return cheap ? std::min(mx, kFirstSweeps) : mx;
   if (h->info_pending[(size_t)mat] && hipEventQuery(h->info_ev[(size_t)mat]) == hipSuccess) {
     h->info_pending[(size_t)mat] = 0;
     const int seen = h->info_host[2 * mat], conv = h->info_host[2 * mat + 1];
@@ -592,7 +602,7 @@ int sweep_budget(glr_handle* h, int mat, int64_t jd) {
   const int k = h->known_sweeps[(size_t)mat];
   if (k == -1) return tail ? std::min(mx, kFirstSweeps) : mx;
   if (k < 0 || !h->known_conv[(size_t)mat]) return mx;
-  return std::min(mx, tail ? k + 1 : k + std::max(4, k / 2));
+  return std::min(mx, k + (cheap ? 1 : tail ? 3 : std::max(4, k / 2)));
 }
 
 // after a refresh's finish: its sweep count and converged flag to the host

@@ -1065,8 +1065,7 @@ __global__ void __launch_bounds__(256, KS <= 4 ? 3 : 2)
 k_resid_packed(const ST* __restrict__ G, ST* __restrict__ E, float* __restrict__ Ebar, const u32x4* __restrict__ Qf,
                const int* __restrict__ Qe, const u32x4* __restrict__ Pf, const int* __restrict__ Pe,
                float* __restrict__ X, float* __restrict__ S1, float* __restrict__ S2, int64_t m, int64_t n, int r,
-               int N, OptParams op,
-               int rows_fast) {
+               int N, OptParams op, int rows_fast) {
   resid_packed_at<OPT, RIGHT, KS, ST>(G, E, Ebar, Qf, Qe, Pf, Pe, X, S1, S2, m, n, r, N, op,
                                       rows_fast ? blockIdx.y : blockIdx.x, rows_fast ? blockIdx.x : blockIdx.y);
 }
