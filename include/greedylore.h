@@ -240,8 +240,9 @@ glr_status glr_create(const glr_config* cfg, void* d_state, size_t state_bytes,
  * matrix on `stream`, without grouped selection steps, and enqueues
  * max_sweeps sweeps per refresh (no sweep counts come back to the host; up to
  * a Jacobi dimension of 128, 16 and one launch for the rest).
- * GLR_ERR_BUFFER_TOO_SMALL when the configuration's workspace
- * (glr_workspace_bytes) exceeds the array.  The array is shared by the handle
+ * GLR_ERR_BUFFER_TOO_SMALL when the configuration's workspace exceeds the
+ * array (glr_workspace_bytes; sets whose selection steps other handles group
+ * may need less here, without what the grouped launches take).  The array is shared by the handle
  * and keeps its contents between handles (creation clears what must start
  * at zero), so only one such handle may live per device at a time
  * (GLR_ERR_STATE otherwise): calls of two handles on one device would race. */

@@ -116,6 +116,7 @@ struct MatView {
   float* X;      const void* G;
   // workspace
   float* Mbar;   float* Q;     float* Qpart; float* lam_part;
+  bool packed;     // the residual pass takes packed operands (else fp32 Q^(i), or no error feedback)
   void* Qf; int* Qe; void* Pf; int* Pe;   // packed pieces of Q^(i) and of P, and their exponents
   float* amax;     // largest |Mbar| of each block of the worker mean (ef_mean_blocks of them)
   float* W;      float* Utw;   double* Apk;  double* Apk2; float* Vrot;   double* V64;   int* skip;
@@ -207,7 +208,7 @@ hipError_t launch_topr(const MatView& v, bool approx, hipStream_t s);
 hipError_t launch_iota_J(const MatView& v, hipStream_t s);
 hipError_t launch_proj(const MatView& v, hipStream_t s);
 // Rbar, and Q^(i): as fp32, or packed with P for the split residual pass
-hipError_t launch_rbar(const MatView& v, bool packed, hipStream_t s);
+hipError_t launch_rbar(const MatView& v, hipStream_t s);
 hipError_t launch_resid_opt(const MatView& v, const OptParams& o, hipStream_t s);
 hipError_t launch_full_refresh(const MatView& v, const OptParams& o, hipStream_t s);
 // Algorithm 5 (GaLore Adam in the r x D subspace): S1, S2 <- the moments of

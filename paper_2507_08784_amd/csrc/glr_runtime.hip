@@ -42,6 +42,7 @@ struct WsLayout {
   uint64_t off_rUtw, off_rY, off_rgram, off_rV, off_rV64, off_rgpart, off_rskip, off_rctl, off_rsigw,
       off_rperm;
   uint64_t bytes;
+  bool packed = false;   // Qf, Qe, Pf, Pe and no Q
 };
 
 // The workspace: one scratch region per matrix, sized by that matrix (so that
@@ -169,31 +170,46 @@ uint64_t state_bytes_of(const glr_config* c) {
   return o;
 }
 
-// whether the residual pass takes packed operands: error feedback on and a
-// rank it holds P of in registers (GaLore Adam keeps no error buffers)
 bool error_feedback(const glr_config* c) { return !(c->flags & GLR_NO_EF) && c->opt != GLR_GALORE_ADAM; }
-bool packed_resid(const glr_config* c, const Dims& x) { return x.r <= kPackRank && error_feedback(c); }
+// bytes of the packed pieces of Q^(i), padded to whole 32 x 16 fragments
+uint64_t packed_bytes(const glr_config* c, const Dims& x) {
+  return (uint64_t)c->num_workers * ((uint64_t)(x.D + 31) / 32 * 32) * 16 * (uint64_t)pack_steps(x.r) *
+         (uint64_t)pack_bytes(x.r);
+}
+// Whether the residual pass takes packed operands: error feedback on (GaLore
+// Adam keeps no error buffers), a rank it holds P of in registers, and pieces
+// that are not the bulk of the step's memory: a large matrix with a handful of
+// rows (96 bytes a column and worker at rank 1, against the 8 d of G and E)
+// keeps fp32 Q^(i), 4 r bytes.
+bool packed_resid(const glr_config* c, const Dims& x) {
+  if (x.r > kPackRank || !error_feedback(c)) return false;
+  const uint64_t pieces = packed_bytes(c, x);
+  return pieces <= GLR_STATIC_SCRATCH_BYTES ||
+         pieces <= 4 * elem_bytes(c) * (uint64_t)c->num_workers * (uint64_t)(x.m * x.n);
+}
 
-WsLayout ws_layout(const glr_config* c, int first, int last) {
+WsLayout ws_layout(const glr_config* c, int first, int last, bool pack) {
   uint64_t mx_mn = 0, mx_Q = 0, mx_Qp = 0, mx_lam = 0, mx_dD = 0, mx_dd = 0, mx_gram = 0, mx_groups = 0, mx_vbuf = 0, mx_d = 0;
   uint64_t p_Q = 0, p_Qe = 0, p_P = 0, p_Pe = 0;
   uint64_t s_Kd = 0, s_KD = 0, s_part = 0, s_KK = 0, s_Kp2 = 0, s_nt = 0, s_sums = 0, s_Kp = 0;
   uint64_t r_gram = 0, r_groups = 0, r_vbuf = 0, r_gpart = 0, mx_gpart = 0;
+  WsLayout w;
   auto mx = [](uint64_t& a, uint64_t b) { if (b > a) a = b; };
   for (int i = first; i < last; ++i) {
     const Dims x = dims_of(c, i);
     mx(mx_mn, (uint64_t)(x.m * x.n));
     const int ps = proj_splits(x.d, x.D, x.r, c->num_workers);
-    mx(mx_Qp, (uint64_t)ps * c->num_workers * (uint64_t)x.r * (uint64_t)x.D);
-    if (packed_resid(c, x)) {
-      // 16-bit pieces, padded to whole 32 x 16 fragments
-      const uint64_t k16 = 16 * (uint64_t)pack_steps(x.r), D32 = (uint64_t)(x.D + 31) / 32 * 32;
-      mx(p_Q, c->num_workers * D32 * k16 * pack_bytes(x.r));
-      mx(p_Qe, c->num_workers * D32 * 4);
-      mx(p_P, (uint64_t)(x.d + 31) / 32 * 32 * k16 * pack_bytes(x.r));
+    const uint64_t nrD = (uint64_t)c->num_workers * (uint64_t)x.r * (uint64_t)x.D;
+    if (pack && packed_resid(c, x)) {
+      w.packed = true;
+      mx(mx_Qp, (uint64_t)ps * nrD);
+      mx(p_Q, packed_bytes(c, x));
+      mx(p_Qe, c->num_workers * ((uint64_t)(x.D + 31) / 32 * 32) * 4);
+      mx(p_P, (uint64_t)(x.d + 31) / 32 * 32 * 16 * (uint64_t)pack_steps(x.r) * pack_bytes(x.r));
       mx(p_Pe, (uint64_t)(x.d + 31) / 32 * 33 * 4);   // each row's and a flag a block
     } else {
-      mx(mx_Q, (uint64_t)c->num_workers * (uint64_t)x.r * (uint64_t)x.D);
+      mx(mx_Q, nrD);   // (one slice: the projection writes Q^(i) itself)
+      if (ps > 1) mx(mx_Qp, (uint64_t)ps * nrD);
     }
     mx(mx_lam, (uint64_t)((x.D + 63) / 64) * (uint64_t)x.d);
     mx(mx_d, (uint64_t)x.d);
@@ -224,7 +240,6 @@ WsLayout ws_layout(const glr_config* c, int first, int last) {
       mx(mx_vbuf, (uint64_t)jac_vbuf(x.d));
     }
   }
-  WsLayout w;
   uint64_t o = 0;
   auto take = [&](uint64_t bytes) {
     uint64_t at = o;
@@ -232,11 +247,14 @@ WsLayout ws_layout(const glr_config* c, int first, int last) {
     return at;
   };
   w.off_Mbar = take(mx_mn * 4);
-  w.off_lam = take(mx_lam * 4);
   w.off_amax = take((uint64_t)ef_mean_blocks((int64_t)mx_mn) * 4);
-  // the projection's outputs share their place with the scratch of the
+  // one place for the score partials, which the top-r has read before the
+  // projection starts, the projection's outputs, and the scratch of the
   // refresh, which is done with it before the projection starts
   const uint64_t shared = o;
+  w.off_lam = take(mx_lam * 4);
+  const uint64_t lam_end = o;
+  o = shared;
   w.off_Q = take(mx_Q * 4);
   w.off_Qpart = take(mx_Qp * 4);
   w.off_Qf = take(p_Q);
@@ -282,15 +300,15 @@ WsLayout ws_layout(const glr_config* c, int first, int last) {
   w.off_rctl = take(sizeof(JacCtl));
   w.off_rsigw = take(s_Kd ? 2 * kMaxSubK * 4 : 4);
   w.off_rperm = take(s_Kd ? 2 * kMaxSubK * 4 : 4);
-  w.bytes = o > proj_end ? o : proj_end;
+  w.bytes = std::max(o, std::max(proj_end, lam_end));
   return w;
 }
 
-WsPlan ws_plan(const glr_config* c) {
+WsPlan ws_plan_for(const glr_config* c, bool pack) {
   WsPlan p;
   uint64_t o = 0;
   for (int i = 0; i < c->num_mats; ++i) {
-    p.mats.push_back(ws_layout(c, i, i + 1));
+    p.mats.push_back(ws_layout(c, i, i + 1, pack));
     p.base.push_back(o);
     o = align_up(o + p.mats.back().bytes);
   }
@@ -304,6 +322,33 @@ WsPlan ws_plan(const glr_config* c) {
   o = align_up(o + (uint64_t)kGrpKinds * ((uint64_t)c->num_mats + kMaxLanes) * 4);
   p.bytes = o;
   p.lanes = c->num_mats < kMaxLanes ? c->num_mats : kMaxLanes;
+  return p;
+}
+
+// Whether the selection steps may run grouped: several matrices with d <=
+// kJointMaxDim and one rank, below d and at most 128 (so the same kernel
+// variants but for the side: the matrices of either side are parts of their own).
+constexpr int64_t kJointMaxDim = 2048;
+bool group_config(const glr_config* c) {
+  if (c->num_mats < 2 || c->tau == 1 || c->select == GLR_SELECT_LAZY || !error_feedback(c)) return false;
+  const int r0 = dims_of(c, 0).r;
+  for (int i = 0; i < c->num_mats; ++i) {
+    const Dims x = dims_of(c, i);
+    if (x.d > kJointMaxDim || x.r >= x.d || x.r > kGroupMaxRank || x.r != r0 || !packed_resid(c, x)) return false;
+  }
+  return true;
+}
+
+// The packed pieces are padded to 16 ranks and more, so a configuration may fit
+// the static scratch (glr_create_static) only without them: it runs without,
+// but for sets whose grouped selection steps need them (other handles than
+// static ones: `stat`).
+WsPlan ws_plan(const glr_config* c, bool stat) {
+  WsPlan p = ws_plan_for(c, true);
+  if (p.bytes > GLR_STATIC_SCRATCH_BYTES && (stat || !group_config(c))) {
+    const WsPlan q = ws_plan_for(c, false);
+    if (q.bytes <= GLR_STATIC_SCRATCH_BYTES) return q;
+  }
   return p;
 }
 
@@ -444,8 +489,11 @@ MatView view_of(glr_handle* h, int mat, float* X, const void* G, int lane) {
   const WsLayout& WL = h->ws.mats[(size_t)mat];
   char* w = h->work + h->ws.base[(size_t)mat];
   v.Mbar = (float*)(w + WL.off_Mbar);
+  v.packed = WL.packed;
   v.Q = (float*)(w + WL.off_Q);
-  v.Qpart = (float*)(w + WL.off_Qpart);
+  // one slice and no packing: the projection writes Q^(i) itself
+  const bool direct = !v.packed && proj_splits(v.d, v.D, v.r, v.N) == 1;
+  v.Qpart = direct ? v.Q : (float*)(w + WL.off_Qpart);
   v.lam_part = (float*)(w + WL.off_lam);
   v.amax = (float*)(w + WL.off_amax);
   v.Qf = w + WL.off_Qf;
@@ -737,7 +785,7 @@ glr_status step_tail(glr_handle* h, const MatView& v, bool refresh, hipStream_t 
   }
   {
     ProfScope p(h, s, GLR_PROF_RBAR);
-    GLR_HIP(h, launch_rbar(v, h->ef && v.r <= kPackRank, s));
+    GLR_HIP(h, launch_rbar(v, s));
   }
   if (galore) GLR_HIP(h, launch_galore_adam(v, op, refresh, s));
   if (refresh && c.refresh == GLR_REFRESH_FULL) {
@@ -913,7 +961,6 @@ hipError_t joint_setup(glr_handle* h, hipStream_t s) {
 // refresh with one group size, the sweeps reorder every time, and no matrix is
 // large enough to fill the chip with its own launches (from d = 4096 on, the
 // per-matrix sweeps on concurrent streams measured a few per cent faster)
-constexpr int64_t kJointMaxDim = 2048;
 bool joint_allowed(const glr_handle* h) {
   const glr_config& c = h->cfg;
   if (c.num_mats < 2 || c.tau == 1 || h->jac_sort != 1) return false;
@@ -967,19 +1014,10 @@ glr_status step_grouped(glr_handle* h, float* const* X, const void* const* G, in
   return GLR_OK;
 }
 
-// selection steps are grouped when every matrix has d <= 2048 and the same
-// rank, below d and at most 128 (so the same kernel variants but for the side:
-// the matrices of either side are parts of their own)
 bool group_allowed(const glr_handle* h) {
-  const glr_config& c = h->cfg;
-  if (c.num_mats < 2 || c.tau == 1 || h->static_ws || h->lazy || !h->ef || c.opt == GLR_GALORE_ADAM) return false;
+  if (h->static_ws || !group_config(&h->cfg)) return false;
   if (const char* e = getenv("GLR_GROUPED"))
     if (atoi(e) == 0) return false;
-  const glr_mat_layout& L0 = h->lay[0];
-  for (int i = 0; i < c.num_mats; ++i) {
-    const glr_mat_layout& L = h->lay[(size_t)i];
-    if (L.d > kJointMaxDim || L.r >= L.d || L.r > kGroupMaxRank || L.r != L0.r) return false;
-  }
   return true;
 }
 
@@ -1110,7 +1148,7 @@ glr_status glr_workspace_bytes(const glr_config* cfg, size_t* state_bytes, size_
   if (s != GLR_OK) { g_create_error = why; return s; }
   if (!state_bytes || !ws_bytes) { g_create_error = "output pointer is NULL"; return GLR_ERR_INVALID_ARG; }
   *state_bytes = (size_t)state_bytes_of(cfg);
-  *ws_bytes = (size_t)ws_plan(cfg).bytes;
+  *ws_bytes = (size_t)ws_plan(cfg, false).bytes;
   return GLR_OK;
 }
 
@@ -1160,7 +1198,7 @@ glr_status create_impl(const glr_config* cfg, void* d_state, size_t state_bytes,
   if (!aligned(d_state) || !aligned(d_ws))
     return fail(nullptr, GLR_ERR_INVALID_ARG, "state and workspace must be 256-byte aligned");
   const uint64_t need_s = state_bytes_of(cfg);
-  const WsPlan wl = ws_plan(cfg);
+  const WsPlan wl = ws_plan(cfg, static_ws);
   if (state_bytes < need_s || ws_bytes < wl.bytes)
     return fail(nullptr, GLR_ERR_BUFFER_TOO_SMALL,
                 fmt("need %llu state bytes and %llu workspace bytes", (unsigned long long)need_s,
@@ -1250,7 +1288,7 @@ glr_status glr_create_static(const glr_config* cfg, void* d_state, size_t state_
   if (s != GLR_OK) return fail(nullptr, s, why);
   if (!out) return fail(nullptr, GLR_ERR_INVALID_ARG, "out is NULL");
   *out = nullptr;
-  const uint64_t need = ws_plan(cfg).bytes;
+  const uint64_t need = ws_plan(cfg, true).bytes;
   if (need > kStaticScratchBytes)
     return fail(nullptr, GLR_ERR_BUFFER_TOO_SMALL,
                 fmt("the configuration needs %llu workspace bytes; the static scratch holds %llu "

@@ -600,6 +600,7 @@ hipError_t launch_proj(const MatView& v, hipStream_t s) {
 
 // S6 (with the slices of the projection): Q^(i) = sum over slices of the
 // partial products, Rbar = (1/N) sum_i Q^(i); both sums in a fixed order, fp64
+// (Q null: the one slice is Q^(i) already)
 __device__ __forceinline__ void proj_reduce_at(const float* __restrict__ part, int splits, int N, int64_t rD,
                                                float* __restrict__ Q, float* __restrict__ Rbar, int64_t bx,
                                                int64_t gx) {
@@ -609,7 +610,7 @@ __device__ __forceinline__ void proj_reduce_at(const float* __restrict__ part, i
     for (int w = 0; w < N; ++w) {
       double q = 0.0;
       for (int z = 0; z < splits; ++z) q += (double)part[((int64_t)z * N + w) * rD + i];
-      Q[(int64_t)w * rD + i] = (float)q;
+      if (Q) Q[(int64_t)w * rD + i] = (float)q;
       rsum += q;
     }
     Rbar[i] = (float)(rsum / (double)N);
@@ -867,9 +868,9 @@ k_pack_waves(const float* __restrict__ part, int splits, int N, int r, int64_t d
   pack_waves<KS>(part, splits, N, r, d, D, Ut, J, Qf, Qe, Pf, Pe, Rbar, blockIdx.x);
 }
 
-hipError_t launch_rbar(const MatView& v, bool packed, hipStream_t s) {
+hipError_t launch_rbar(const MatView& v, hipStream_t s) {
   const int splits = proj_splits(v.d, v.D, v.r, v.N);
-  if (packed) {
+  if (v.packed) {
     const int KS = pack_steps(v.r);
     const dim3 grid((unsigned)pack_blocks(v.d, v.D, v.N, v.r));
 #define GLR_PW(K)                                                                                                  \
@@ -889,8 +890,8 @@ hipError_t launch_rbar(const MatView& v, bool packed, hipStream_t s) {
     return hipGetLastError();
   }
   const int64_t rD = (int64_t)v.r * v.D;
-  hipLaunchKernelGGL(k_proj_reduce, dim3(grid_for(rD)), dim3(kThreads), 0, s, v.Qpart, splits, v.N, rD, v.Q,
-                     v.Rbar);
+  hipLaunchKernelGGL(k_proj_reduce, dim3(grid_for(rD)), dim3(kThreads), 0, s, v.Qpart, splits, v.N, rD,
+                     v.Qpart == v.Q ? nullptr : v.Q, v.Rbar);
   return hipGetLastError();
 }
 
@@ -1125,7 +1126,8 @@ k_recon_opt(float* __restrict__ Ebar, const float* __restrict__ Rbar, const floa
   }
 }
 
-// S5 + S7 + S8 above rank 256, the workers side by side: one 64 x 64 output
+// S5 + S7 + S8 from fp32 Q^(i) (above rank 256, and where the packed pieces
+// would take too much memory), the workers side by side: one 64 x 64 output
 // tile of the m x n layout per workgroup (a 32 x 32 MFMA block per wave).
 // Each k-slice of P (gathered rows of U^T) is staged once and multiplied
 // with the slices of Q^(w) of up to kNW workers into one accumulator per
@@ -1303,7 +1305,7 @@ static hipError_t launch_resid_opt_st(const MatView& v, const OptParams& o, hipS
   const ST* G = static_cast<const ST*>(v.G);
   ST* E = static_cast<ST*>(v.E);
   const dim3 grid((unsigned)((v.n + 63) / 64), (unsigned)((v.m + 63) / 64));
-  if (v.r <= kPackRank && o.ef) {
+  if (v.packed) {
     // row tiles on x when they exceed a grid's y extent (65535: m above
     // 4194240; the column tiles are few then, m n being below 2^30)
     const int rows_fast = grid.y > 65535u ? 1 : 0;
@@ -1328,7 +1330,8 @@ static hipError_t launch_resid_opt_st(const MatView& v, const OptParams& o, hipS
     return hipGetLastError();
   }
   if (o.ef) {
-    // above rank 256: one fused pass with the workers side by side
+    // without packed operands (above rank 256, or packed_resid): one fused pass
+    // with the workers side by side
     const bool multi = v.N > kNW;
     const unsigned rt = (unsigned)((v.m + kNWTile - 1) / kNWTile), ct = (unsigned)((v.n + kNWTile - 1) / kNWTile);
     const int rows_fast = ct <= 65535u ? 1 : 0;

@@ -152,3 +152,30 @@ def test_state_copies_reject_bad_arguments_without_touching_the_device():
     assert lib.glr_status_string(8) == b"orthonormalisation breakdown"
     assert glr.STATUS_NAMES[8] == "GLR_ERR_BREAKDOWN"
     assert [f[0] for f in glr.StateView._fields_] == list(glr.STATE_PARTS)
+
+
+# configurations that fit the static scratch only without the packed operands
+# of the residual pass (padded to 16 ranks and more), found among random ones
+# by an fp32 Q^(i)'s workspace: accepted (here, without a GPU, the call then
+# stops at the device), and their reported workspace fits
+@pytest.mark.parametrize("shapes,workers,rank,tau,opt,flags", [
+    ([(1588, 241)], 32, 259, 1, "adam", glr.STORE_BF16), ([(335, 614)], 64, 338, 5, "adam", 0),
+    ([(80752, 20)], 8, 17, 5, "galore_adam", 0), ([(802, 312)], 64, 238, 1, "adam", 0),
+    ([(588, 2356)], 16, 181, 5, "adam", 0), ([(467, 2613)], 32, 128, 5, "msgd", 0),
+    ([(126, 6636)], 16, 368, 5, "adam", glr.STORE_BF16), ([(405, 3163)], 8, 405, 1, "adam", glr.STORE_BF16),
+    ([(92, 2067)], 64, 236, 1, "adam", 0)])
+def test_static_scratch_takes_what_fits_without_packed_operands(shapes, workers, rank, tau, opt, flags):
+    cfg, _keep = _cfg(shapes=shapes, workers=workers, rank=rank, tau=tau, opt=opt, flags=flags)
+    assert glr.workspace_bytes(cfg)[1] <= glr.STATIC_SCRATCH_BYTES
+    h = ctypes.c_void_p()
+    # (state_bytes 0: refused for the state buffer, not for the workspace)
+    st = glr.load().glr_create_static(ctypes.byref(cfg), ctypes.c_void_p(0x100000), 0, None, ctypes.byref(h))
+    assert st != 0 and "static scratch" not in glr.load().glr_last_error(None).decode()
+
+
+# a large matrix with a handful of rows: the pieces would take many times what
+# the gradients take
+@pytest.mark.parametrize("shape,workers,rank", [((1, 50_000_000), 4, 1), ((30_000_000, 2), 8, 2), ((4, 20_000_000), 16, 3)])
+def test_workspace_of_a_few_long_rows(shape, workers, rank):
+    cfg, _keep = _cfg(shapes=[shape], workers=workers, rank=rank, tau=10)
+    assert glr.workspace_bytes(cfg)[1] < 3 * 4 * (workers + 4) * shape[0] * shape[1]

@@ -1,5 +1,7 @@
 """Products on the 16-bit matrix cores from split fp32 operands, at the edges
 of their tiles and of the operands' range, against fp64."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -162,6 +164,52 @@ def test_residual_of_more_row_tiles_than_a_grid_extent(gpu_lib):
         col = M.norm(dim=1, keepdim=True)
         assert bool(((comp.E(0)[0, a:a + 64].double() - (M - C)).abs() <= 4e-6 * col).all())
         assert bool(((X[a:a + 64].double() + C).abs() <= 4e-6 * col).all())
+
+
+# fp32 Q^(i) below rank 257, where the packed operands would take too much (a
+# configuration that fits the static scratch only so; long rows): against fp64,
+# and a static handle against one with its own workspace
+@pytest.mark.parametrize("shape,workers,rank,opt,select", [((588, 2356), 16, 181, "adam", "approx"),
+                                                           ((2613, 467), 32, 128, "msgd", "exact"),
+                                                           ((3, 900_001), 2, 2, "adam", "exact"),
+                                                           ((900_001, 1), 2, 1, "msgd", "approx")])
+def test_residual_without_packed_operands(gpu_lib, shape, workers, rank, opt, select):
+    m, n = shape
+    d, D = min(shape), max(shape)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    U = torch.from_numpy(_orthonormal(d, np.random.default_rng(d)).astype(np.float32)).cuda()
+    G = torch.randn(workers, m, n, generator=gen, device="cuda")
+    lib, runs = gpu_lib.load(), []
+    cfg, _keep = gpu_lib.make_config([shape], workers, rank, 1000, opt=opt, lr=1.0, beta1=0.0, select=select, seed=3)
+    sb, wb = gpu_lib.workspace_bytes(cfg)
+    comp = gpu_lib.GreedyLore([shape], workers, rank, 1000, opt=opt, lr=1.0, beta1=0.0, select=select, seed=3)
+    comp.write_state(0, Ut=U)
+    comp.resume(1)
+    X = torch.zeros(m, n, device="cuda")
+    comp.step([X], [G], 1)
+    comp.check_status()
+    P = U.double()[comp.J(0).long()].T
+    o = (lambda x: x.transpose(-1, -2)) if m > n else (lambda x: x)
+    for w in range(workers):
+        M = o(G[w].double())
+        R = M - P @ (P.T @ M)
+        assert bool(((o(comp.E(0)[w]).double() - R).abs() <= 4e-6 * M.norm(dim=0)).all())
+    if wb > gpu_lib.STATIC_SCRATCH_BYTES:
+        return
+    state = torch.empty(sb + 256, dtype=torch.uint8, device="cuda")
+    s0 = (-state.data_ptr()) % 256
+    stream, h = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream), ctypes.c_void_p()
+    assert lib.glr_create_static(ctypes.byref(cfg), ctypes.c_void_p(state.data_ptr() + s0), sb, stream,
+                                 ctypes.byref(h)) == 0
+    try:
+        view = gpu_lib.StateView(Ut=ctypes.c_void_p(U.data_ptr()))
+        assert lib.glr_write_state(h, 0, ctypes.byref(view), stream) == 0 and lib.glr_resume(h, 1) == 0
+        X2 = torch.zeros(m, n, device="cuda")
+        assert lib.glr_step(h, (ctypes.c_void_p * 1)(X2.data_ptr()), (ctypes.c_void_p * 1)(G.data_ptr()), 1, stream) == 0
+        assert lib.glr_sync_status(h, stream) == 0
+        assert torch.equal(X, X2)
+    finally:
+        assert lib.glr_destroy(h) == 0
 
 
 # one and several keys a thread, the fold inside and outside the selecting
