@@ -26,7 +26,10 @@ struct JacCtl {
   uint32_t sweeps;
   uint32_t sweep_max_bits;     // float bits of the largest pair off-norm this sweep
   uint32_t pad;
-  uint64_t rowmax2_bits;       // double bits of the largest squared row norm seen
+  // double bits of the largest squared row norm seen: the solves of a round
+  // read what the rounds before left in the other slot and write their own, so
+  // that no group's measure depends on which others of its launch ran first
+  uint64_t rowmax2_bits[2];
   uint32_t history[kHistory];  // float bits of each sweep's largest off-norm
 };
 

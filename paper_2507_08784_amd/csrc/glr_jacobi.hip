@@ -135,7 +135,7 @@ __global__ void k_ctl_reset(JacCtl* ctl) {
     ctl->converged = 0;
     ctl->sweeps = 0;
     ctl->sweep_max_bits = 0;
-    ctl->rowmax2_bits = 0;
+    ctl->rowmax2_bits[0] = ctl->rowmax2_bits[1] = 0;
   }
 }
 
@@ -678,7 +678,7 @@ __device__ __forceinline__ void solve_group(const double* __restrict__ Apk, JacC
   double* red = L.red;
   double* redw = L.redw;
   constexpr int NE = NR * NR / NT;
-  const double rm_prev = __longlong_as_double((long long)ld_fresh(&ctl->rowmax2_bits));
+  const double rm_prev = __longlong_as_double((long long)ld_fresh(&ctl->rowmax2_bits[~round & 1]));
   // the group's diagonal NR x NR block of A; element k of this thread is
   // (x, y) = (tid / NR + k (NT / NR), tid % NR)
   double g[NE];
@@ -706,9 +706,9 @@ __device__ __forceinline__ void solve_group(const double* __restrict__ Apk, JacC
 #pragma unroll
   for (int i = 0; i < NW; ++i) dmax = fmax(dmax, red[i]);
   __syncthreads();
-  if (tid == 0 && dmax > 0.0)
-    atomicMax((unsigned long long*)&ctl->rowmax2_bits, (unsigned long long)__double_as_longlong(dmax));
   const double rowmax2 = fmax(dmax, rm_prev);
+  if (tid == 0 && rowmax2 > 0.0)
+    atomicMax((unsigned long long*)&ctl->rowmax2_bits[round & 1], (unsigned long long)__double_as_longlong(rowmax2));
   const double floor2 = floor_rel2 * rowmax2;
   double m2 = 0.0, mw2 = 0.0;   // all pairs / pairs inside one block
 #pragma unroll

@@ -658,71 +658,65 @@ __device__ __forceinline__ void pack_store(const float (&x)[8], float scale, u32
 #pragma unroll
   for (int i = 0; i < PC; ++i) dst[64 * i] = f[i];
 }
-// The KS fragments of block blk of P, by one wave, KC steps at a time (two
-// passes when they are not all in registers).  Rows whose largest entry lies in
-// [kUnitLow, kUnitHigh), nearly all of an orthonormal basis, are scaled by
-// 2^kUnitExp (their pieces resolve 2^-24 of it); a row outside, by a power of
-// its own: Pe holds its exponent beyond kUnitExp and, past the rows, whether a
-// block has any.  The residual then corrects that block's products; doing so
-// for every block cost it 12 % at rank 128 (registers of loads in flight).
+// The KS fragments of block blk of P, by NW waves, KC = KS / NW steps (at least
+// one) each.  Rows whose largest entry lies in [kUnitLow, kUnitHigh), nearly
+// all of an orthonormal basis, are scaled by 2^kUnitExp (their pieces resolve
+// 2^-24 of it); a row outside, by a power of its own: Pe holds its exponent
+// beyond kUnitExp and, past the rows, whether a block has any.  The residual
+// then corrects that block's products; doing so for every block cost it 12 % at
+// rank 128 (registers of loads in flight).  red: 32 floats a wave.
 constexpr float kUnitLow = 0x1p-7f, kUnitHigh = 0x1p+9f;
-template <SplitFmt F, int KC>
+template <SplitFmt F, int NW, int KC>
 __device__ __forceinline__ void pack_p(int blk, int r, int KS, int64_t d, const float* __restrict__ Ut,
-                                       const int* __restrict__ J, u32x4* __restrict__ Pf, int* __restrict__ Pe) {
-  const int lane = lane_id();
-  if (blk >= (int)((d + 31) / 32)) return;
+                                       const int* __restrict__ J, u32x4* __restrict__ Pf, int* __restrict__ Pe,
+                                       float* red) {
+  const int lane = lane_id(), w = NW == 1 ? 0 : wave_id(), k0 = w * KC;
   const int a = blk * 32 + (lane & 31);
-  float x[KC][8];
-  auto load = [&](int k0) {
+  float x[KC][8], scale = 1.f;
 #pragma unroll
-    for (int ks = 0; ks < KC; ++ks)
+  for (int ks = 0; ks < KC; ++ks)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int k = 16 * (k0 + ks) + 8 * (lane >> 5) + e;
-        x[ks][e] = (k < r && a < d) ? Ut[(int64_t)J[k] * d + a] : 0.f;
-      }
-  };
-  float scale = 1.f;
-  load(0);
+    for (int e = 0; e < 8; ++e) {
+      const int k = 16 * (k0 + ks) + 8 * (lane >> 5) + e;
+      x[ks][e] = (k < r && a < d) ? Ut[(int64_t)J[k] * d + a] : 0.f;
+    }
   if constexpr (F == kF16x2) {
     float mx = 0.f;
-    for (int k0 = 0;;) {
-#pragma unroll
-      for (int ks = 0; ks < KC; ++ks)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(x[ks][e]));
-      if ((k0 += KC) >= KS) break;
-      load(k0);
-    }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const int own = mx >= kUnitLow && mx < kUnitHigh ? 0 : mx > 0.f ? split_exp(mx) - kUnitExp : 0;
-    const uint64_t odd = __ballot(own != 0);
-    if (lane < 32) Pe[blk * 32 + lane] = own;
-    if (lane == 0) Pe[(int64_t)((d + 31) / 32) * 32 + blk] = odd != 0;
-    scale = ldexpf(1.f, kUnitExp + own);
-  }
-  for (int k0 = 0; k0 < KS; k0 += KC) {
-    if (KC < KS) load(k0);
 #pragma unroll
     for (int ks = 0; ks < KC; ++ks)
-      pack_store<F>(x[ks], scale, Pf + ((int64_t)blk * KS + k0 + ks) * (64 * split_pieces(F)) + lane);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(x[ks][e]));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    if (lane < 32) red[w * 32 + lane] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NW; ++i) mx = fmaxf(mx, red[i * 32 + (lane & 31)]);
+    const int own = mx >= kUnitLow && mx < kUnitHigh ? 0 : mx > 0.f ? split_exp(mx) - kUnitExp : 0;
+    const uint64_t odd = __ballot(own != 0);
+    if (w == 0 && lane < 32) Pe[blk * 32 + lane] = own;
+    if (w == 0 && lane == 0) Pe[(int64_t)((d + 31) / 32) * 32 + blk] = odd != 0;
+    scale = ldexpf(1.f, kUnitExp + own);
   }
+#pragma unroll
+  for (int ks = 0; ks < KC; ++ks)
+    if (k0 + ks < KS)
+      pack_store<F>(x[ks], scale, Pf + ((int64_t)blk * KS + k0 + ks) * (64 * split_pieces(F)) + lane);
 }
-// blocks of kThreads: four fragments columns of Q each, then four blocks of P
-// each, then Rbar
+// blocks of kThreads: four fragments columns of Q each, then a block of P each
+// (four at one step), then Rbar
 struct PackGrid {
   int q, p, rbar;
 };
-__host__ __device__ inline PackGrid pack_grid(int64_t d, int64_t D, int N, int r) {
+__host__ __device__ inline PackGrid pack_grid(int64_t d, int64_t D, int N, int r, int KS) {
   const int64_t q = (D + 31) / 32 * N, p = (d + 31) / 32, rb = ((int64_t)r * D + kThreads - 1) / kThreads;
-  return {(int)((q + 3) / 4), (int)((p + 3) / 4), (int)rb};
+  return {(int)((q + 3) / 4), KS == 1 ? (int)((p + 3) / 4) : (int)p, (int)rb};
 }
 template <int KS>
 __device__ __forceinline__ void pack_waves(const float* __restrict__ part, int splits, int N, int r, int64_t d,
                                            int64_t D, const float* __restrict__ Ut, const int* __restrict__ J,
                                            u32x4* __restrict__ Qf, int* __restrict__ Qe, u32x4* __restrict__ Pf,
                                            int* __restrict__ Pe, float* __restrict__ Rbar, int bid) {
-  const PackGrid g = pack_grid(d, D, N, r);
+  const PackGrid g = pack_grid(d, D, N, r, KS);
   const int64_t rD = (int64_t)r * D;
   const int lane = lane_id();
   if (bid < g.q) {
@@ -776,7 +770,13 @@ __device__ __forceinline__ void pack_waves(const float* __restrict__ part, int s
         pack_store<pack_fmt(KS)>(x[ks], ldexpf(1.f, e2),
                                  Qf + ((int64_t)item * KS + ks) * (64 * split_pieces(pack_fmt(KS))) + lane);
   } else if (bid < g.q + g.p) {
-    pack_p<pack_fmt(KS), KS>((bid - g.q) * 4 + wave_id(), r, KS, d, Ut, J, Pf, Pe);
+    if constexpr (KS == 1) {
+      const int blk = (bid - g.q) * 4 + wave_id();
+      if (blk < (int)((d + 31) / 32)) pack_p<pack_fmt(KS), 1, 1>(blk, r, KS, d, Ut, J, Pf, Pe, nullptr);
+    } else {
+      __shared__ float red[4 * 32];
+      pack_p<pack_fmt(KS), 4, (KS + 3) / 4>(bid - g.q, r, KS, d, Ut, J, Pf, Pe, red);
+    }
   } else {
     const int64_t i = (int64_t)(bid - g.q - g.p) * kThreads + threadIdx.x;
     if (i >= rD) return;
@@ -795,7 +795,8 @@ __device__ __forceinline__ void pack_block(const float* __restrict__ part, int s
                                         int* __restrict__ Pe, float* __restrict__ Rbar, int bid, float* dyn) {
   const int tid = threadIdx.x, nqb = (int)((D + 31) / 32);
   if (bid >= nqb) {
-    pack_p<kF16x2, 4>((bid - nqb) * (kPackThreads / 64) + (tid >> 6), r, KS, d, Ut, J, Pf, Pe);
+    static_assert(kPackRank == 16 * (kPackThreads / 64), "a wave a step");
+    pack_p<kF16x2, kPackThreads / 64, 1>(bid - nqb, r, KS, d, Ut, J, Pf, Pe, dyn);
     return;
   }
   constexpr int KG = kPackThreads / 32;            // rows of k side by side
@@ -847,11 +848,10 @@ static size_t pack_lds(int KS) { return ((size_t)16 * KS * 33 + (size_t)kPackThr
 static int pack_blocks(int64_t d, int64_t D, int N, int r) {
   const int KS = pack_steps(r);
   if (KS <= kPackWaveSteps) {
-    const PackGrid g = pack_grid(d, D, N, r);
+    const PackGrid g = pack_grid(d, D, N, r, KS);
     return g.q + g.p + g.rbar;
   }
-  const int64_t pb = (d + 31) / 32;
-  return (int)((D + 31) / 32 + (pb + kPackThreads / 64 - 1) / (kPackThreads / 64));
+  return (int)((D + 31) / 32 + (d + 31) / 32);
 }
 __global__ void __launch_bounds__(kPackThreads)
 k_pack_block(const float* __restrict__ part, int splits, int N, int r, int KS, int64_t d, int64_t D,

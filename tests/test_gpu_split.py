@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from oracle.philox import gaussian_vectors
+from synth import get_workload, gradient_batch, planted_matrix
 
 pytestmark = pytest.mark.gpu
 
@@ -318,3 +319,23 @@ def test_trailing_sweeps_finish_a_refresh(gpu_lib, shapes, tau, opt):
         assert torch.equal(a.J(l), b.J(l)) and torch.equal(a.S1(l), b.S1(l))
         U = a.Ut(l).double()[:K]
         assert float((U @ U.T - torch.eye(K, device="cuda", dtype=torch.float64)).abs().max()) < 1e-5
+
+
+# the convergence measure does not depend on the order in which the groups of a
+# launch run: the same refresh many times over, in shared launches and alone,
+# to the last bit of its record
+def test_refresh_records_repeat(gpu_lib, monkeypatch):
+    wl = get_workload("mixed_small")
+    planted = [planted_matrix(wl, l) for l in range(len(wl.shapes))]
+    G = [torch.from_numpy(gradient_batch(wl, l, 0, planted[l])).cuda() for l in range(len(wl.shapes))]
+    seen = set()
+    for i in range(120):
+        if i % 2:
+            monkeypatch.setenv("GLR_JAC_JOINT", "0")
+        else:
+            monkeypatch.delenv("GLR_JAC_JOINT", raising=False)
+        comp = gpu_lib.GreedyLore(wl.shapes, wl.workers, wl.rank, wl.tau, seed=wl.seed)
+        comp.step([torch.zeros(m, n, device="cuda") for m, n in wl.shapes], G, 0)
+        torch.cuda.synchronize()
+        seen.add(tuple(tuple(comp.info(l).cpu().tolist()) for l in range(len(wl.shapes))))
+    assert len(seen) == 1
