@@ -291,7 +291,9 @@ glr_status glr_step_bf16(glr_handle* h, float* const* X, const uint16_t* const* 
 glr_status glr_sync_status(glr_handle* h, void* stream);
 
 /* Declares the caller-owned state valid again after the caller wrote it
- * (resume from a saved blob, or a hand-off) and sets the next step to t. */
+ * (resume from a saved blob, or a hand-off) and sets the next step to t.  (A
+ * U^T of entries above 512, no orthonormal basis, is written by
+ * glr_write_state, which lets the products scale for it.) */
 glr_status glr_resume(glr_handle* h, int64_t next_t);
 
 /* Buffers for one matrix's state (glr_read_state / glr_write_state): host or

@@ -122,6 +122,7 @@ struct MatView {
   bool packed;     // the residual pass takes packed operands (else fp32 Q^(i), or no error feedback)
   void* Qf; int* Qe; void* Pf; int* Pe;   // packed pieces of Q^(i) and of P, and their exponents
   float* amax;     // largest |Mbar| of each block of the worker mean (ef_mean_blocks of them)
+  float* umax;     // largest entry of U^T as a caller last wrote it (0: U^T is the library's)
   float* W;      float* Utw;   double* Apk;  double* Apk2; float* Vrot;   double* V64;   int* skip;
   double* gpart;   // split-contraction partials of the Gram (or null)
   JacCtl* ctl;   float* sigma_w; int* perm;
@@ -205,6 +206,7 @@ struct OptParams {
 // launchers (return the first launch error)
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_eye(float* Ut, int64_t d, hipStream_t s);
+hipError_t launch_absmax(const float* p, int64_t n, float* out, hipStream_t s);   // *out = max |p[i]|
 hipError_t launch_ef_mean(const MatView& v, bool check_finite, hipStream_t s);
 hipError_t launch_sel_scores(const MatView& v, bool approx, bool bf16, uint64_t seed, int64_t t, hipStream_t s);
 hipError_t launch_topr(const MatView& v, bool approx, hipStream_t s);

@@ -35,7 +35,7 @@ inline uint64_t align_up(uint64_t x) { return (x + kAlign - 1) / kAlign * kAlign
 thread_local std::string g_create_error;
 
 struct WsLayout {
-  uint64_t off_Mbar, off_Q, off_Qpart, off_Qf, off_Qe, off_Pf, off_Pe, off_lam, off_amax, off_W, off_Utw, off_gram, off_gram2, off_V, off_V64, off_gpart, off_skip,
+  uint64_t off_Mbar, off_Q, off_Qpart, off_Qf, off_Qe, off_Pf, off_Pe, off_lam, off_amax, off_umax, off_W, off_Utw, off_gram, off_gram2, off_V, off_V64, off_gpart, off_skip,
       off_ctl, off_sigw, off_perm;
   uint64_t off_sP, off_sPn, off_sZ, off_sZt, off_sR, off_spart, off_sS, off_sL, off_sDinv, off_sLi,
       off_sT, off_sLinv, off_sC, off_ssums, off_sctl, off_sbad;
@@ -248,6 +248,7 @@ WsLayout ws_layout(const glr_config* c, int first, int last, bool pack) {
   };
   w.off_Mbar = take(mx_mn * 4);
   w.off_amax = take((uint64_t)ef_mean_blocks((int64_t)mx_mn) * 4);
+  w.off_umax = take(4);
   // one place for the score partials, which the top-r has read before the
   // projection starts, the projection's outputs, and the scratch of the
   // refresh, which is done with it before the projection starts
@@ -410,6 +411,7 @@ struct glr_handle {
   std::vector<int> known_sweeps;       // most sweeps a converged refresh took (-1: none yet, -2: the last one missed)
   std::vector<int> known_conv;         // its converged flag
   std::vector<int> info_pending;       // a read-back is in flight
+  std::vector<char> u_given;           // U^T was written by the caller since the last refresh (umax)
   int64_t repaired_total = 0;          // status reads that found replaced (dependent) rows
   int* info_host = nullptr;            // pinned, 2 ints per matrix
   std::vector<hipEvent_t> info_ev;
@@ -496,6 +498,7 @@ MatView view_of(glr_handle* h, int mat, float* X, const void* G, int lane) {
   v.Qpart = direct ? v.Q : (float*)(w + WL.off_Qpart);
   v.lam_part = (float*)(w + WL.off_lam);
   v.amax = (float*)(w + WL.off_amax);
+  v.umax = (float*)(w + WL.off_umax);
   v.Qf = w + WL.off_Qf;
   v.Qe = (int*)(w + WL.off_Qe);
   v.Pf = w + WL.off_Pf;
@@ -653,6 +656,13 @@ int sweep_budget(glr_handle* h, int mat, int64_t jd) {
   return std::min(mx, k + (cheap ? 1 : tail ? 3 : std::max(4, k / 2)));
 }
 
+// after a refresh: U^T is the library's again
+hipError_t own_basis(glr_handle* h, const MatView& v, hipStream_t s) {
+  if (!h->u_given[(size_t)v.mat]) return hipSuccess;
+  h->u_given[(size_t)v.mat] = 0;
+  return launch_fill_zero(v.umax, 4, s);
+}
+
 // after a refresh's finish: its sweep count and converged flag to the host
 hipError_t read_back_info(glr_handle* h, int mat, const MatView& v, hipStream_t s) {
   if (!h->info_host || h->info_pending[(size_t)mat]) return hipSuccess;   // the previous read-back is still in flight
@@ -699,6 +709,7 @@ glr_status svd_end(glr_handle* h, const MatView& v, hipStream_t s) {
   ProfScope p(h, s, GLR_PROF_JAC_FINISH);
   GLR_HIP(h, launch_jac_finish(v, h->cfg.max_sweeps, s));
   GLR_HIP(h, launch_reorth(v, s));
+  GLR_HIP(h, own_basis(h, v, s));
   return GLR_OK;
 }
 
@@ -763,6 +774,7 @@ glr_status refresh_subspace(glr_handle* h, const MatView& v, int64_t t, hipStrea
   ProfScope p(h, s, GLR_PROF_JAC_FINISH);
   GLR_HIP(h, launch_jac_finish(rr, c.max_sweeps, s));
   GLR_HIP(h, launch_sub_rr_end(v, sub_tol, iters, s));
+  GLR_HIP(h, own_basis(h, v, s));
   GLR_HIP(h, read_back_info(h, v.mat, v, s));
   return GLR_OK;
 }
@@ -1247,6 +1259,7 @@ glr_status create_impl(const glr_config* cfg, void* d_state, size_t state_bytes,
   h->known_sweeps.assign((size_t)cfg->num_mats, -1);
   h->known_conv.assign((size_t)cfg->num_mats, 0);
   h->info_pending.assign((size_t)cfg->num_mats, 0);
+  h->u_given.assign((size_t)cfg->num_mats, 0);
   h->info_ev.assign((size_t)cfg->num_mats, nullptr);
   if (e == hipSuccess && !static_ws)
     e = hipHostMalloc((void**)&h->info_host, 2 * sizeof(int) * (size_t)cfg->num_mats, hipHostMallocDefault);
@@ -1441,6 +1454,13 @@ glr_status copy_state(glr_handle* h, int32_t mat, const glr_state_view* view, bo
     char* at = h->state + part[k].off;
     if (to_state) GLR_HIP(h, hipMemcpyAsync(at, ptr[k], part[k].bytes, hipMemcpyDefault, s));
     else GLR_HIP(h, hipMemcpyAsync(ptr[k], at, part[k].bytes, hipMemcpyDefault, s));
+  }
+  if (to_state && ptr[2]) {
+    // the split products scale U^T as an orthonormal basis; one with entries far
+    // above 1 (fp16 ends at 2^16) by its largest
+    const MatView v = view_of(h, mat, nullptr, nullptr, 0);
+    h->u_given[(size_t)mat] = 1;
+    GLR_HIP(h, launch_absmax(v.Ut, v.d * v.d, v.umax, s));
   }
   return GLR_OK;
 }

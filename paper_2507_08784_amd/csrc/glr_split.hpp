@@ -82,17 +82,29 @@ __device__ __forceinline__ int split_exp(float amax) {
 
 // Where an operand's scale comes from (kF16x2): the exponent `fixed`, or with
 // `amax` the one of the largest of n partial maxima times `mul` (a bound on
-// the operand's largest value).
+// the operand's largest value), at most `cap` (`fixed` when they are all zero).
+// `basis`: the bound is for an orthonormal basis of the product, and *basis the
+// largest entry of the one taken.
 struct SplitScale {
   const float* amax;
   int n;
   float mul;
   int fixed;
+  int cap = 127;
+  const float* basis = nullptr;
 };
 // rows of an orthonormal basis: |u| <= 1, with room for a basis that is not
 // quite one (fp16 ends at 2^16)
 constexpr int kUnitExp = 6;
 inline SplitScale split_unit() { return {nullptr, 0, 1.f, kUnitExp}; }
+// rows of a basis that a caller may have written: *umax its largest entry, 0
+// when the library computed it
+inline SplitScale split_basis(const float* umax) { return {umax, 1, 1.f, kUnitExp, kUnitExp}; }
+__device__ __forceinline__ int split_basis_exp(float umax) {
+  if (!(umax > 0.f)) return kUnitExp;
+  const int e = split_exp(umax);
+  return e < kUnitExp ? e : kUnitExp;
+}
 // the exponent, by a whole workgroup (red: one float per wave)
 __device__ __forceinline__ int split_block_exp(const SplitScale& sc, float* red) {
   if (!sc.amax) return sc.fixed;
@@ -104,7 +116,10 @@ __device__ __forceinline__ int split_block_exp(const SplitScale& sc, float* red)
   __syncthreads();
   mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])) * sc.mul;
   __syncthreads();
-  return split_exp(mx);
+  if (sc.basis && *sc.basis > 1.5f) mx *= *sc.basis * sc.mul;   // (its rows' norms: mul is sqrt(d))
+  if (mx == 0.f) return sc.fixed;
+  const int e = split_exp(mx);
+  return e < sc.cap ? e : sc.cap;
 }
 
 // A slice of one operand in LDS: PIECES planes of R rows (the operand's M or

@@ -40,6 +40,22 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
+__global__ void k_absmax(const float* __restrict__ p, int64_t n, float* __restrict__ out) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  float mx = 0.f;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += stride) mx = fmaxf(mx, fabsf(p[i]));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+  // (bits of non-negative floats order as unsigned integers)
+  if (lane_id() == 0 && mx > 0.f) atomicMax((unsigned int*)out, __float_as_uint(mx));
+}
+hipError_t launch_absmax(const float* p, int64_t n, float* out, hipStream_t s) {
+  hipError_t e = launch_fill_zero(out, 4, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_absmax, dim3(grid_for(n, 16)), dim3(kThreads), 0, s, p, n, out);
+  return hipGetLastError();
+}
+
 hipError_t launch_eye(float* Ut, int64_t d, hipStream_t s) {
   hipLaunchKernelGGL(k_eye, dim3(grid_for(d * d, 4)), dim3(kThreads), 0, s, Ut, d);
   return hipGetLastError();
@@ -141,15 +157,16 @@ constexpr int kSelFew = 256;
 template <int BT, bool RIGHT, bool APPROX, bool BF16>
 __device__ __forceinline__ void sel_scores_at(const float* __restrict__ Mbar, const float* __restrict__ Ut, int64_t d,
                                               int64_t D, float* __restrict__ part, uint32_t mat, uint32_t tstep,
-                                              uint32_t key0, uint32_t key1, const float* __restrict__ amax, int bx,
-                                              int by) {
+                                              uint32_t key0, uint32_t key1, const float* __restrict__ amax,
+                                              const float* __restrict__ umax, int bx, int by) {
   using T = SplitTile<BT, BT, 2, 2, BF16 ? kBf16 : kF16x2, BF16 ? kAccOne : kAccFlush>;
   __shared__ __align__(16) char smem[T::LDS_BYTES];
   __shared__ float red[2][BT];
   const int m0 = by * BT;   // rows: b in [0, D)
   const int n0 = bx * BT;   // cols: j in [0, d)
   const int em = BF16 ? 0 : split_block_exp({amax, ef_mean_blocks(d * D), 1.f, 0}, red[0]);
-  const float sm = ldexpf(1.f, em), su = BF16 ? 1.f : ldexpf(1.f, kUnitExp);
+  const int eu = BF16 ? 0 : split_basis_exp(*umax);
+  const float sm = ldexpf(1.f, em), su = ldexpf(1.f, eu);
   T tile;
   SplitK<BT, false, false> lb(Ut, nullptr, d * d, d, n0, (int)d, (int)d);
   if (RIGHT) {
@@ -162,7 +179,7 @@ __device__ __forceinline__ void sel_scores_at(const float* __restrict__ Mbar, co
     tile.run(la, lb, (int)d, smem, sm, su);
   }
   const int lane = lane_id();
-  const float unscale = BF16 ? 1.f : ldexpf(1.f, -em - kUnitExp);
+  const float unscale = ldexpf(1.f, -em - eu);
 #pragma unroll
   for (int tn = 0; tn < T::TN; ++tn) {
     const int j = n0 + tile.col(tn);
@@ -213,8 +230,9 @@ template <int BT, bool RIGHT, bool APPROX, bool BF16>
 __global__ void __launch_bounds__(256, BT == 64 ? 4 : 2)
 k_sel_scores(const float* __restrict__ Mbar, const float* __restrict__ Ut, int64_t d, int64_t D,
              float* __restrict__ part, uint32_t mat, uint32_t tstep, uint32_t key0, uint32_t key1,
-             const float* __restrict__ amax) {
-  sel_scores_at<BT, RIGHT, APPROX, BF16>(Mbar, Ut, d, D, part, mat, tstep, key0, key1, amax, blockIdx.x, blockIdx.y);
+             const float* __restrict__ amax, const float* __restrict__ umax) {
+  sel_scores_at<BT, RIGHT, APPROX, BF16>(Mbar, Ut, d, D, part, mat, tstep, key0, key1, amax, umax, blockIdx.x,
+                                         blockIdx.y);
 }
 
 static int sel_tiles(int64_t d, int64_t D, int bt) { return (int)(((d + bt - 1) / bt) * ((D + bt - 1) / bt)); }
@@ -227,7 +245,7 @@ hipError_t launch_sel_scores(const MatView& v, bool approx, bool bf16, uint64_t 
   const uint32_t tt = (uint32_t)((uint64_t)t & 0xFFFFFFFFu);
 #define GLR_SEL1(T, R, A, B)                                                                         \
   hipLaunchKernelGGL((k_sel_scores<T, R, A, B>), grid, dim3(kThreads), 0, s, v.Mbar, v.Ut, v.d, v.D, \
-                     v.lam_part, (uint32_t)v.mat, tt, k0, k1, v.amax)
+                     v.lam_part, (uint32_t)v.mat, tt, k0, k1, v.amax, v.umax)
 #define GLR_SEL(R, A, B)                    \
   do {                                      \
     if (few) GLR_SEL1(64, R, A, B);         \
@@ -1483,7 +1501,7 @@ k_g_sel_scores(const GroupMat* __restrict__ gm, const int* __restrict__ first, i
   const MatView& v = gm[m].v;
   const int local = blockIdx.x - first[m], gx = (int)((v.d + BT - 1) / BT);
   sel_scores_at<BT, RIGHT, APPROX, BF16>(v.Mbar, v.Ut, v.d, v.D, v.lam_part, (uint32_t)v.mat, tstep, key0, key1,
-                                     v.amax, local % gx, local / gx);
+                                     v.amax, v.umax, local % gx, local / gx);
 }
 
 // (many matrices: each one's workgroup folds its own partials, whatever their count)

@@ -226,10 +226,10 @@ hipError_t launch_warm_product(const MatView& v, hipStream_t s) {
   const GemmPlan p{1, (int)v.d};
   if (v.right)
     gemm_split_launch<true, 0>(v.Ut, v.d, v.Mbar, v.d, v.W, v.D, (int)v.d, (int)v.D, (int)v.d, p, 0, nullptr,
-                                       split_unit(), mb, s);
+                                       split_basis(v.umax), mb, s);
   else
     gemm_split_launch<false, 0>(v.Ut, v.d, v.Mbar, v.D, v.W, v.D, (int)v.d, (int)v.D, (int)v.d, p, 0, nullptr,
-                                        split_unit(), mb, s);
+                                        split_basis(v.umax), mb, s);
   return hipGetLastError();
 }
 
@@ -1091,18 +1091,18 @@ static hipError_t orth_rows(const MatView& v, float* Y, float* Ytmp, int K, int6
   return hipGetLastError();
 }
 
-// sub_Z = P^T Mo (K x D), skipped when *gate is set
-static void launch_z(const MatView& v, int K, const int* gate, hipStream_t s) {
+// sub_Z = P^T Mo (K x D), skipped when *gate is set; ps: the scale of P
+static void launch_z(const MatView& v, int K, const int* gate, SplitScale ps, hipStream_t s) {
   const int64_t d = v.d, D = v.D;
   const GemmPlan pz = plan_z(K, D, d);
   float* out = pz.splits > 1 ? v.sub_part : v.sub_Z;
   const SplitScale mb{v.amax, ef_mean_blocks(v.m * v.n), 1.f, 0};
   if (v.right)   // Mo[a][b] = Mbar[b][a]: B(k=a, j=b) at Mbar[b d + a]
     gemm_split_launch<true, 0>(v.sub_P, d, v.Mbar, d, out, D, K, (int)D, (int)d, pz, (int64_t)K * D, nullptr,
-                                       split_unit(), mb, s, gate);
+                                       ps, mb, s, gate);
   else           // Mo = Mbar (d x D): B(k=a, j=b) at Mbar[a D + b]
     gemm_split_launch<false, 0>(v.sub_P, d, v.Mbar, D, out, D, K, (int)D, (int)d, pz, (int64_t)K * D, nullptr,
-                                        split_unit(), mb, s, gate);
+                                        ps, mb, s, gate);
   if (pz.splits > 1)
     hipLaunchKernelGGL(k_reduce_splits, dim3(grid_n((int64_t)K * D)), dim3(256), 0, s, v.sub_part, pz.splits,
                        (int64_t)K * D, v.sub_Z, (double*)nullptr, gate);
@@ -1136,7 +1136,9 @@ hipError_t launch_sub_iter(const MatView& v, float tol, uint64_t seed, int64_t t
   hipLaunchKernelGGL(k_gate, dim3(1), dim3(64), 0, s, &sc->gate_iter, &sc->stop, (const int*)nullptr);
   // Z = P^T Mo  (K x D)
   prof.begin(GLR_PROF_SUB_Z);
-  launch_z(v, K, g, s);
+  // (the first product of a warm start takes the basis as it stands in the state)
+  const bool given = it == 0 && !cold;
+  launch_z(v, K, g, given ? split_basis(v.umax) : split_unit(), s);
   prof.end(GLR_PROF_SUB_Z);
   block_energy(v, v.sub_Z, K, D, &sc->e_in, g, s);
   // Z only carries the span into the next product.  From a cold start one
@@ -1155,7 +1157,8 @@ hipError_t launch_sub_iter(const MatView& v, float tol, uint64_t seed, int64_t t
   // the scale of Z: orthonormal rows from a cold start, else P^T Mo of
   // orthonormal rows, below sqrt(d) times the largest |Mbar|
   const SplitScale mb{v.amax, ef_mean_blocks(v.m * v.n), 1.f, 0};
-  const SplitScale zs = cold ? split_unit() : SplitScale{mb.amax, mb.n, sqrtf((float)d), 0};
+  SplitScale zs = cold ? split_unit() : SplitScale{mb.amax, mb.n, sqrtf((float)d), 0};
+  if (given) zs.basis = v.umax;
   if (v.right)   // Mbar[b d + a]: contiguous along j
     gemm_split_launch<false, 0>(v.sub_Z, D, v.Mbar, d, v.sub_part, d, K, (int)d, (int)D, p2, (int64_t)K * d,
                                         nullptr, zs, mb, s, g);
@@ -1196,7 +1199,7 @@ hipError_t launch_sub_rr_begin(const MatView& v, MatView* rr, hipStream_t s) {
   const int K = sub_block(v.r, v.d);
   const int64_t D = v.D;
   // B = P^T Mo, or the last iteration's Z when it is that product already
-  launch_z(v, K, &v.sub_ctl->reuse_z, s);
+  launch_z(v, K, &v.sub_ctl->reuse_z, split_unit(), s);
   block_energy(v, v.sub_Z, K, D, &v.sub_ctl->e_out, nullptr, s);
   *rr = v;
   rr->d = K;

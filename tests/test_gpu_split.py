@@ -145,6 +145,55 @@ def test_reconstruction_of_small_rows(gpu_lib, rank, shape, store):
         assert np.all(np.abs(oriented(comp.E(0)) - (Mo - C)) <= bound + 2.0 ** -22 * np.abs(Mo - C))
 
 
+# a basis far above 1 written into the state (a multiple of an orthonormal one:
+# the scores and residuals scale with it, and the span that a tau = 1 refresh
+# starts from is the same): no overflow, the same relative bounds
+@pytest.mark.parametrize("scale", [1.0, 3000.0, 2.0 ** 20])
+@pytest.mark.parametrize("shape", [(150, 333), (333, 150)])
+@pytest.mark.parametrize("rank", [7, 40])
+def test_basis_of_large_entries(gpu_lib, scale, shape, rank):
+    m, n = shape
+    d, D = min(shape), max(shape)
+    rng = np.random.default_rng([m, rank])
+    U = (_orthonormal(d, rng) * scale).astype(np.float32)
+    M = rng.standard_normal((d, D))
+    G = torch.from_numpy((M.T if m > n else M).astype(np.float32))[None].cuda().contiguous()
+    Mo = G[0].double().cpu().numpy()
+    Mo = Mo.T if m > n else Mo
+    comp = gpu_lib.GreedyLore([shape], 1, rank, 1000, lr=1.0, beta1=0.0, select="exact")
+    comp.write_state(0, Ut=torch.from_numpy(U).cuda())
+    comp.resume(1)
+    X = torch.zeros(m, n, device="cuda")
+    comp.step([X], [G], 1)
+    comp.check_status()
+    ref = ((U.astype(np.float64) @ Mo) ** 2).sum(1)
+    assert np.all(np.abs(comp.score(0).double().cpu().numpy() - ref) <= 1e-5 * ref)
+    P = U[comp.J(0).cpu().numpy()].astype(np.float64).T
+    C = P @ (P.T @ Mo)
+    x = -X.double().cpu().numpy()
+    bound = 5e-6 * scale * scale * np.linalg.norm(Mo, axis=0)
+    assert np.all(np.abs((x.T if m > n else x) - C) <= bound)
+    # tau = 1: the refreshed basis is that of the orthonormal start, and the
+    # handle's later steps are
+    low = (P[:, :rank] / scale) @ rng.standard_normal((rank, D)) * 30
+    runs = []
+    for s in (1.0, scale):
+        comp = gpu_lib.GreedyLore([shape], 1, rank, 1, lr=1.0, beta1=0.0)
+        comp.write_state(0, Ut=torch.from_numpy((U / scale * s).astype(np.float32)).cuda(),
+                         sigma=torch.linspace(2.0, 1.0, d, device="cuda"))
+        comp.resume(1)
+        x = Mo + low
+        g = torch.from_numpy((x.T if m > n else x).astype(np.float32))[None].cuda().contiguous()
+        for t in (1, 2):
+            comp.step([X], [g], t)
+        assert comp.sync_status() in (0, 7)
+        V = comp.Ut(0).double()[:rank]
+        assert bool(torch.isfinite(V).all())
+        assert float((V @ V.T - torch.eye(rank, device="cuda", dtype=torch.float64)).abs().max()) < 1e-5
+        runs.append(V.T @ V)
+    assert float((runs[0] - runs[1]).norm()) < 1e-3 * rank ** 0.5
+
+
 # more row tiles than a grid's y extent holds (65535): the rows on both sides of
 # that tile, against fp64
 def test_residual_of_more_row_tiles_than_a_grid_extent(gpu_lib):
