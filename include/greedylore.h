@@ -50,7 +50,8 @@
  * r < d, r <= 128, launches each of its kernels once for all matrices of a
  * side (m > n or not) on `stream` or one of the handle's streams, after
  * uploading that step's table of matrix views from pinned host memory the
- * handle owns; GLR_GROUPED=0 turns this off.
+ * handle owns; GLR_GROUPED=0 turns this off, and a stream that is being captured
+ * into a graph (the table would be rewritten between replays).
  * While profiling is enabled the matrices run in order on `stream`.  The
  * environment variable GLR_LANES, read by glr_create, lowers the stream count.
  * Tuning switches of the refresh, also read by glr_create (defaults in

@@ -1333,6 +1333,17 @@ glr_status glr_create_static(const glr_config* cfg, void* d_state, size_t state_
 }
 
 namespace {
+// Whether `s` is being captured into a graph: a grouped step's table goes up
+// from a pinned slot that later steps rewrite, so a replay would run on their
+// buffers; the per-matrix launches hold the pointers of the captured call.
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
 glr_status step_impl(glr_handle* h, float* const* X, const void* const* G, int64_t t, void* stream) {
   if (h->suspect) return fail(h, GLR_ERR_STATE, "state is suspect after an earlier error; call glr_resume");
   if (t != h->next_t)
@@ -1347,7 +1358,7 @@ glr_status step_impl(glr_handle* h, float* const* X, const void* const* G, int64
   if (h->joint && !h->prof && t % h->cfg.tau == 0) {
     glr_status st = step_joint(h, X, G, t, s);
     if (st != GLR_OK) return st;
-  } else if (h->grouped && !h->prof && t % h->cfg.tau != 0) {
+  } else if (h->grouped && !h->prof && t % h->cfg.tau != 0 && !capturing(s)) {
     glr_status st = step_grouped(h, X, G, t, s);
     if (st != GLR_OK) return st;
   } else if (h->lanes > 1 && !h->prof) {

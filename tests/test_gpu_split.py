@@ -370,6 +370,39 @@ def test_trailing_sweeps_finish_a_refresh(gpu_lib, shapes, tau, opt):
         assert float((U @ U.T - torch.eye(K, device="cuda", dtype=torch.float64)).abs().max()) < 1e-5
 
 
+# a captured selection step of a set (of one side and of both) replays on the
+# buffers it was captured with, whatever steps ran since, and those steps are
+# none the worse for the capture
+@pytest.mark.parametrize("shapes", [[(90, 200), (200, 90), (64, 64)], [(90, 200), (64, 130)]])
+def test_captured_selection_step_of_a_set(gpu_lib, shapes):
+    gen = torch.Generator(device="cuda").manual_seed(len(shapes))
+    G = [[torch.randn(2, m, n, generator=gen, device="cuda") for m, n in shapes] for _ in range(4)]
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        comp, ref = (gpu_lib.GreedyLore(shapes, 2, 8, 1000, select="exact") for _ in range(2))
+        Xa, Xb, Ya, Yb = ([torch.zeros(m, n, device="cuda") for m, n in shapes] for _ in range(4))
+        for c, x in ((comp, Xa), (ref, Ya)):
+            c.resume(1)
+            c.step(x, G[0], 1)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            comp.step(Xa, G[1], 2)
+        t = 3
+        for _ in range(4):
+            graph.replay()
+            torch.cuda.synchronize()
+            ref.resume(t - 1)
+            ref.step(Ya, G[1], t - 1)
+            for k in (2, 3):                       # other buffers, both slots of the table
+                comp.step(Xb, G[k], t)
+                ref.step(Yb, G[k], t)
+                t += 1
+            torch.cuda.synchronize()
+            for l in range(len(shapes)):
+                assert torch.equal(Xa[l], Ya[l]) and torch.equal(Xb[l], Yb[l]) and torch.equal(comp.E(l), ref.E(l))
+
+
 # the convergence measure does not depend on the order in which the groups of a
 # launch run: the same refresh many times over, in shared launches and alone,
 # to the last bit of its record
