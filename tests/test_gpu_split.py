@@ -16,7 +16,7 @@ def _orthonormal(d, rng):
     return np.linalg.qr(rng.standard_normal((d, d)))[0]
 
 
-# d and D around the 128-wide tiles, the 32-deep slices and the 256-deep
+# d and D around the 64-wide tiles, the 32-deep slices and the 256-deep
 # flush; rows of 1 to 3 elements past a quad; operands far from 1, with
 # columns of very different size, and zero
 @pytest.mark.parametrize("shape", [(1, 37), (2, 3), (31, 33), (33, 130), (127, 129), (128, 128), (257, 300), (300, 257),
@@ -53,6 +53,71 @@ def test_scores_against_fp64(gpu_lib, shape, select, scale):
         bound = (2.0 ** -21 * fro + 1e-5 * np.linalg.norm(C, axis=1)) * np.linalg.norm(v, axis=1)
         got = np.sqrt(got)
     assert np.all(np.abs(got - ref) <= bound)
+
+
+# at least 256 tiles of 128 x 128, which then run (fewer: 64 x 64 ones): d past
+# a tile, D a few columns and more than half a tile past one, odd rows; against
+# fp64 of the operands as the mode rounds them
+@pytest.mark.parametrize("shape", [(1930, 1953), (1953, 1930), (1931, 2040), (2040, 1930)])
+@pytest.mark.parametrize("select", ["exact", "approx", "approx_bf16"])
+def test_scores_in_large_tiles(gpu_lib, shape, select):
+    m, n = shape
+    d, D = min(shape), max(shape)
+    gen = torch.Generator(device="cuda").manual_seed(d + n)
+    U = torch.linalg.qr(torch.randn(d, d, generator=gen, device="cuda", dtype=torch.float64))[0].float().contiguous()
+    G = torch.randn(1, m, n, generator=gen, device="cuda") * torch.logspace(0, -2, n, device="cuda")
+    comp = gpu_lib.GreedyLore([shape], 1, 4, 1000, select=select, seed=11)
+    comp.write_state(0, Ut=U)
+    comp.resume(1)
+    comp.step([torch.zeros(m, n, device="cuda")], [G], 1)
+    comp.check_status()
+    got = comp.score(0).double()
+    Mo = G[0].T if m > n else G[0]
+    if select == "approx_bf16":
+        U, Mo = U.bfloat16(), Mo.bfloat16()
+    C = U.double() @ Mo.double()
+    fro = float(Mo.double().norm())
+    # as for the small tiles (exact products of bf16 operands in the bf16 mode,
+    # their fp32 sums of up to 2000 terms within 1e-5 of the terms' norm)
+    if select == "exact":
+        ref = C.square().sum(1)
+        bound = 2 * 2.0 ** -21 * ref.sqrt() * fro + (2.0 ** -21 * fro) ** 2 + 1e-5 * ref
+    else:
+        v = torch.from_numpy(np.asarray(gaussian_vectors(11, 1, 0, range(d), D), dtype=np.float64)).cuda()
+        ref = (C * v).sum(1).abs()
+        bound = (2.0 ** -21 * fro + 1e-5 * C.norm(dim=1)) * v.norm(dim=1)
+        got = got.sqrt()
+    assert bool(((got - ref).abs() <= bound).all())
+
+
+# a group of at least 256 large tiles whose matrices have fewer each: the bits of
+# the small tiles that they take alone
+@pytest.mark.parametrize("select", ["exact", "approx", "approx_bf16"])
+@pytest.mark.parametrize("right", [False, True])
+def test_grouped_scores_across_the_tile_sizes(gpu_lib, monkeypatch, select, right):
+    shapes = [(768, 768)] * 4 + [(700, 790), (640, 1100), (513, 911), (129, 3000)]
+    assert sum(-(-a // 128) * -(-b // 128) for a, b in shapes) >= 256
+    if right:
+        shapes = [(b, a) for a, b in shapes if b > a] * 3
+    gen = torch.Generator(device="cuda").manual_seed(int(right))
+    G = [torch.randn(1, m, n, generator=gen, device="cuda") for m, n in shapes]
+    U = [torch.linalg.qr(torch.randn(min(s), min(s), generator=gen, device="cuda"))[0].contiguous() for s in shapes]
+    runs = []
+    for grouped in ("0", None):
+        if grouped is None:
+            monkeypatch.delenv("GLR_GROUPED", raising=False)
+        else:
+            monkeypatch.setenv("GLR_GROUPED", grouped)
+        comp = gpu_lib.GreedyLore(shapes, 1, 12, 1000, select=select)
+        for l, u in enumerate(U):
+            comp.write_state(l, Ut=u)
+        comp.resume(1)
+        comp.step([torch.zeros(m, n, device="cuda") for m, n in shapes], G, 1)
+        comp.check_status()
+        runs.append(comp)
+    for l in range(len(shapes)):
+        assert torch.equal(runs[0].score(l), runs[1].score(l)) and torch.equal(runs[0].J(l), runs[1].J(l))
+        assert torch.equal(runs[0].E(l), runs[1].E(l))
 
 
 # hundreds of partials a column: their fold adds no error of its own.  A
@@ -108,6 +173,33 @@ def test_residual_against_fp64(gpu_lib, rank, shape, workers, store):
     assert np.all(np.abs(E - (Mo - C)) <= 4e-6 * col + (2.0 ** -8 if store == "bf16" else 2.0 ** -22) * np.abs(Mo - C))
     assert np.all(np.abs(-oriented(X) - C.mean(0)) <= 4e-6 * col.max(0))
     assert np.all(np.abs(oriented(comp.Ebar(0)) - E.mean(0)) <= 1e-6 * np.abs(E).max(0) + 1e-37)
+
+
+# a second, ragged slice of the projection above rank 64 (slices of 1024 terms of
+# d), with odd rows
+@pytest.mark.parametrize("rank", [65, 130])
+@pytest.mark.parametrize("shape", [(1031, 1100), (1101, 1031), (1033, 1061)])
+@pytest.mark.parametrize("store", ["fp32", "bf16"])
+def test_residual_of_two_projection_slices(gpu_lib, rank, shape, store):
+    m, n = shape
+    d, N = min(shape), 2
+    gen = torch.Generator(device="cuda").manual_seed(rank + n)
+    U = torch.linalg.qr(torch.randn(d, d, generator=gen, device="cuda", dtype=torch.float64))[0].float().contiguous()
+    G = torch.randn(N, m, n, generator=gen, device="cuda").to(torch.bfloat16 if store == "bf16" else torch.float32)
+    comp = gpu_lib.GreedyLore([shape], N, rank, 1000, opt="msgd", lr=1.0, beta1=0.0, select="exact", store=store)
+    comp.write_state(0, Ut=U)
+    comp.resume(1)
+    X = torch.zeros(m, n, device="cuda")
+    comp.step([X], [G], 1)
+    comp.check_status()
+    o = (lambda x: x.double().transpose(-1, -2)) if m > n else (lambda x: x.double())
+    P, Mo = U.double()[comp.J(0).long()].T, o(G)
+    C = P @ (P.T @ Mo)
+    col = Mo.norm(dim=1, keepdim=True)
+    rounding = (2.0 ** -8 if store == "bf16" else 2.0 ** -22) * (Mo - C).abs()
+    assert bool(((o(comp.E(0)) - (Mo - C)).abs() <= 4e-6 * col + rounding).all())
+    assert bool(((-o(X) - C.mean(0)).abs() <= 4e-6 * col.amax(0)).all())
+    assert bool(((o(comp.Rbar(0)) if m <= n else comp.Rbar(0).double()) - (P.T @ Mo).mean(0)).abs().max() <= 4e-6 * col.max())
 
 
 # rows of P (and of M) from 1 down to 1e-9 of the largest: the reconstruction of
