@@ -43,9 +43,8 @@
  * computes exactly what it computes alone (results are bitwise those of
  * running the matrices in order).  On refresh steps (tau > 1) of several
  * matrices with d <= 2048 and one Jacobi group size, the sweeps of all of them
- * run in shared launches on `stream` itself, with one convergence read per
- * sweep for all matrices; each matrix still computes exactly what it computes
- * alone.  GLR_JAC_JOINT=0, read by glr_create, turns this off.  Likewise a
+ * run in shared launches on `stream` itself; each matrix still computes exactly
+ * what it computes alone.  GLR_JAC_JOINT=0, read by glr_create, turns this off.  Likewise a
  * selection step of several matrices that all have d <= 2048 and the same rank
  * r < d, r <= 128, launches each of its kernels once for all matrices of a
  * side (m > n or not) on `stream` or one of the handle's streams, after

@@ -845,8 +845,8 @@ glr_status run_lane(glr_handle* h, int lane, const MatFn& fn, hipStream_t s) {
 }
 
 // Lanes run concurrently: each on its own stream, driven by its own host thread
-// (a refresh blocks its thread once per sweep on the convergence flag, so one
-// thread could not keep the other streams fed).  The lanes start after the work
+// (a refresh is hundreds of launches: one thread enqueueing all lanes could not
+// keep their streams fed).  The lanes start after the work
 // already on `s` and `s` waits for all of them.
 glr_status on_lanes(glr_handle* h, hipStream_t s, const MatFn& fn) {
   const int L = h->lanes;
@@ -884,9 +884,8 @@ glr_status on_lanes(glr_handle* h, hipStream_t s, const MatFn& fn) {
 
 // A refresh step of several matrices: M-bar and the Jacobi start of every
 // matrix on the lanes; then the sweeps of all matrices in shared launches on
-// `s`, one convergence read per sweep for all of them (a matrix that has
-// converged leaves the launches); then sigma, U and the rest of the step on the
-// lanes.  Each matrix runs the same kernels on the same data as its own
+// `s` (a matrix that has converged leaves them at once); then sigma, U and the
+// rest of the step on the lanes.  Each matrix runs the same kernels on the same data as its own
 // refresh, so the results are bitwise those of the per-matrix order.
 glr_status step_joint(glr_handle* h, float* const* X, const void* const* G, int64_t t, hipStream_t s) {
   const glr_config& c = h->cfg;

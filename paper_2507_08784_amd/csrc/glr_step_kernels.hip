@@ -1504,7 +1504,10 @@ k_g_sel_scores(const GroupMat* __restrict__ gm, const int* __restrict__ first, i
                                      v.amax, v.umax, local % gx, local / gx);
 }
 
-// (many matrices: each one's workgroup folds its own partials, whatever their count)
+// (each matrix's workgroup folds its own partials, whatever their count: a
+// selection step of four 2048 x 2048 matrices, 65536 partials each, takes 488 us
+// so and 498 with a fold over the chip before it; four 2048 x 8192, 262144, the
+// same; two 2048 x 28672, 917504, 3.41 and 3.36 ms)
 __global__ void __launch_bounds__(kToprThreads)
 k_g_topr(const GroupMat* __restrict__ gm, int approx) {
   const MatView& v = gm[blockIdx.x].v;
