@@ -39,7 +39,8 @@
  * enqueues its kernels on the stream itself.  With several, the matrices are
  * spread over up to four non-blocking streams of the handle (created by
  * glr_create, destroyed by glr_destroy), each with its own host thread inside
- * glr_step, forked from and joined back to `stream` with events; every matrix
+ * glr_step (the calling thread alone while `stream` is being captured into a
+ * graph), forked from and joined back to `stream` with events; every matrix
  * computes exactly what it computes alone (results are bitwise those of
  * running the matrices in order).  On refresh steps (tau > 1) of several
  * matrices with d <= 2048 and one Jacobi group size, the sweeps of all of them

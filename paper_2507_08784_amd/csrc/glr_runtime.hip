@@ -831,6 +831,16 @@ glr_status step_one(glr_handle* h, int mat, float* X, const void* G, int64_t t, 
   return step_tail(h, v, refresh, s);
 }
 
+// Whether `s` is being captured into a graph.
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
 // per-matrix work (matrix, lane, the lane's stream)
 using MatFn = std::function<glr_status(int, int, hipStream_t)>;
 
@@ -847,7 +857,9 @@ glr_status run_lane(glr_handle* h, int lane, const MatFn& fn, hipStream_t s) {
 // Lanes run concurrently: each on its own stream, driven by its own host thread
 // (a refresh is hundreds of launches: one thread enqueueing all lanes could not
 // keep their streams fed).  The lanes start after the work
-// already on `s` and `s` waits for all of them.
+// already on `s` and `s` waits for all of them.  Under capture the calling
+// thread enqueues every lane: the launches of all of them become nodes of one
+// graph, a host object that several threads must not add to at once.
 glr_status on_lanes(glr_handle* h, hipStream_t s, const MatFn& fn) {
   const int L = h->lanes;
   if (L <= 1) return run_lane(h, 0, fn, s);
@@ -855,8 +867,10 @@ glr_status on_lanes(glr_handle* h, hipStream_t s, const MatFn& fn) {
   for (int k = 0; k < L; ++k) GLR_HIP(h, hipStreamWaitEvent(h->lane_s[k], h->ev_fork, 0));
   glr_status st[kMaxLanes];
   std::thread th[kMaxLanes];
+  const bool threads = !capturing(s);
   for (int k = 1; k < L; ++k) {
     st[k] = GLR_OK;
+    if (!threads) continue;   // this lane runs on the calling thread after lane 0
     try {
       th[k] = std::thread([h, k, &fn, &st] {
         const hipError_t e = hipSetDevice(h->device);
@@ -1332,17 +1346,6 @@ glr_status glr_create_static(const glr_config* cfg, void* d_state, size_t state_
 }
 
 namespace {
-// Whether `s` is being captured into a graph: a grouped step's table goes up
-// from a pinned slot that later steps rewrite, so a replay would run on their
-// buffers; the per-matrix launches hold the pointers of the captured call.
-bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return st != hipStreamCaptureStatusNone;
-}
 glr_status step_impl(glr_handle* h, float* const* X, const void* const* G, int64_t t, void* stream) {
   if (h->suspect) return fail(h, GLR_ERR_STATE, "state is suspect after an earlier error; call glr_resume");
   if (t != h->next_t)
@@ -1358,6 +1361,9 @@ glr_status step_impl(glr_handle* h, float* const* X, const void* const* G, int64
     glr_status st = step_joint(h, X, G, t, s);
     if (st != GLR_OK) return st;
   } else if (h->grouped && !h->prof && t % h->cfg.tau != 0 && !capturing(s)) {
+    // (a captured step's table would go up from a pinned slot that later steps
+    // rewrite, so a replay would run on their buffers: the per-matrix launches
+    // hold the pointers of the captured call)
     glr_status st = step_grouped(h, X, G, t, s);
     if (st != GLR_OK) return st;
   } else if (h->lanes > 1 && !h->prof) {
